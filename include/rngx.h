@@ -73,8 +73,8 @@ int rngx_init(uint64_t seed, uint32_t n_states);
  * iteration-major, i.e. the byte order the paper's program writes to its
  * standard output; then cursor += n_iters.
  * out: device memory of at least 8 * n_states * n_iters bytes, 8-byte
- *      aligned (16-byte alignment and an even n_states give the fastest
- *      stores). n_iters == 0 is a successful no-op.
+ *      aligned (a 128-byte aligned output and an n_states that is a multiple
+ *      of 16 give the fastest stores). n_iters == 0 is a successful no-op.
  * Errors: RNGX_E_NOINIT; RNGX_E_INVAL (out NULL or misaligned, the byte
  * count overflows size_t, or the cursor would pass value number 2^64 - 1);
  * RNGX_E_HIP. */
@@ -153,17 +153,26 @@ int rngx_hip_notes(uint64_t *released, uint64_t *stray, char *text, size_t cap, 
  *         instruction of a wavefront covers 1 KiB of contiguous output.
  * nontemporal: 1 to use non-temporal (streaming) stores.
  * pace_gbs: 0, or a row schedule for the launch, 1000..20000 (GB/s). With a
- *         schedule the kernel runs on a persistent grid of every block that
- *         fits on the device at once, the blocks walking strips of columns
- *         in turn, and every wavefront writes its iteration k of strip s
- *         no earlier than its own start time + (s * n_iters + k) times the
- *         time the resident wavefronts' share of a row takes at pace_gbs,
- *         read from the device's constant-rate clock. Wavefronts ahead of
- *         the schedule wait; those behind run freely, so the grid moves
- *         down the rows together instead of drifting apart (each wait is
- *         bounded; the schedule never changes a value). Used for calls of
- *         at least 2 iterations on 16-byte aligned rows; other calls run
- *         the unscheduled kernel.
+ *         schedule the kernel runs on a persistent grid of at most the blocks
+ *         that fit on the device at once, the blocks walking strips of
+ *         columns in turn, and every wavefront writes its row number j
+ *         (counted over its strips) no earlier than its own start time + j
+ *         times the time the resident wavefronts' share of a row takes at
+ *         pace_gbs, read from the device's constant-rate clock. Wavefronts
+ *         ahead of the schedule wait; those behind run freely, so the grid
+ *         moves down the rows together instead of drifting apart (each wait
+ *         is bounded; the schedule never changes a value). Used for calls of
+ *         at least 2 iterations. With a schedule, a call whose rows are
+ *         shorter than 4 MiB runs with one chunk and blocks of at most 256,
+ *         its iterations cut into segments that run side by side where the
+ *         rows alone would not fill the device, and without waits if its
+ *         output stays below 192 MiB.
+ * Rows that do not start on 128-byte lines (an odd or ragged n_states, an
+ * output offset) are staged through LDS into whole lines when the output is
+ * larger than 256 MiB or cut into segments, with at most 2 chunks. Staged
+ * rows and segments keep a second buffer of 8 * n_states bytes from the first
+ * such call to the next rngx_init, rngx_set_state or rngx_shutdown; if it
+ * cannot be allocated, the unscheduled kernel runs in its place.
  * Defaults: u64 block 512, 2 chunks, non-temporal stores, schedule 7000
  * GB/s; u32 block 0, the library's choice, which is the same launch
  * (measured on MI355X: 6.8-7.1 TB/s at every size from 2^20 to 2^26 states

@@ -111,6 +111,10 @@ int release_state_locked(Generator &c)
         RNGX_HIP(hipFree(c.state));
         c.state = nullptr;
     }
+    if (c.alt) {
+        RNGX_HIP(hipFree(c.alt));
+        c.alt = nullptr;
+    }
     c.inited = false;
     c.n = 0;
     c.cursor = 0;
@@ -172,6 +176,35 @@ int check_device_locked(const Generator &c)
     return RNGX_OK;
 }
 
+hipError_t run_gen_locked(Generator &c, const rngx_launch &cfg, uint32_t n_iters, void *out,
+                          hipStream_t s, bool u32, bool star)
+{
+    GenPlan plan = plan_gen(cfg, u32, c.n, n_iters, out);
+    if (plan.out_of_place() && !c.alt) {
+        void *p = nullptr;
+        if (hipMalloc(&p, (size_t)c.n * sizeof(uint64_t)) == hipSuccess) {
+            c.alt = static_cast<uint64_t *>(p);
+        } else {
+            // No room for a second copy of the states: the launch that
+            // works in place, as slow as its unaligned rows make it.
+            (void)hipGetLastError();
+            plan.cfg = cfg;
+            plan.scheduled = plan.shift = false;
+            plan.segs = 1;
+            plan.seg_rows = n_iters;
+        }
+    }
+    if (plan.segs > 1 && (c.polys_rows != plan.seg_rows || c.polys_count < plan.segs)) {
+        jump_polys(plan.seg_rows, plan.segs, c.polys.c);
+        c.polys_rows = plan.seg_rows;
+        c.polys_count = plan.segs;
+    }
+    const hipError_t e = launch_gen(plan, c.polys, u32, star, c.state, c.alt, c.n, n_iters, out, s);
+    if (e == hipSuccess && plan.out_of_place())
+        std::swap(c.state, c.alt);
+    return e;
+}
+
 int generate_locked(Generator &c, uint32_t n_iters, void *out, hipStream_t s, bool u32)
 {
     if (!c.inited)
@@ -202,9 +235,8 @@ int generate_locked(Generator &c, uint32_t n_iters, void *out, hipStream_t s, bo
         cfg = rngx_launch{512, 2, 1, 7000};
     }
     take_stray_error("before the rng kernel launch");
-    hipError_t e = launch_gen(cfg, u32,
-                              current_scrambler() == RNGX_SCRAMBLE_STAR, c.state, c.n, n_iters,
-                              out, s);
+    hipError_t e = run_gen_locked(c, cfg, n_iters, out, s, u32,
+                                  current_scrambler() == RNGX_SCRAMBLE_STAR);
     prof::end(tok, s);
     if (e != hipSuccess)
         return hip_fail(e, "rng kernel launch");

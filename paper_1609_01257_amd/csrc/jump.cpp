@@ -13,6 +13,7 @@
 // GPU kernels keep row r in lane r and form M x with one ballot.
 #include <cstring>
 #include <mutex>
+#include <utility>
 
 #include "internal.h"
 
@@ -102,6 +103,40 @@ void power_rows(uint64_t k, uint64_t *rows_out)
         k &= k - 1;
     }
     std::memcpy(rows_out, acc, sizeof acc);
+}
+
+// T satisfies its characteristic polynomial, so T^k = sum over i < 64 of c_i
+// T^i for some bits c. With e the first unit vector, c solves K c = T^k e, K
+// having the columns T^i e: e is cyclic because the step has full period
+// (no proper subspace is invariant), so K is invertible.
+void jump_polys(uint64_t rows, uint32_t count, uint64_t *c)
+{
+    // K^-1 by elimination on the rows of K (row r: bit r of every T^i e).
+    uint64_t k[64] = {0}, inv[64];
+    uint64_t x = 1;
+    for (int i = 0; i < 64; ++i, x = xs_step(x))
+        for (int r = 0; r < 64; ++r)
+            k[r] |= ((x >> r) & 1u) << i;
+    for (int r = 0; r < 64; ++r)
+        inv[r] = (uint64_t)1 << r;
+    for (int i = 0; i < 64; ++i) {
+        int p = i;
+        while (!((k[p] >> i) & 1u))
+            ++p;
+        std::swap(k[p], k[i]);
+        std::swap(inv[p], inv[i]);
+        for (int r = 0; r < 64; ++r)
+            if (r != i && ((k[r] >> i) & 1u)) {
+                k[r] ^= k[i];
+                inv[r] ^= inv[i];
+            }
+    }
+    uint64_t step[64], y = 1;
+    power_rows(rows, step);
+    for (uint32_t j = 0; j < count; ++j) {
+        c[j] = matvec(inv, y);
+        y = matvec(step, y);
+    }
 }
 
 } // namespace rngx

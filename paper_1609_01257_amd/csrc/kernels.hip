@@ -1,19 +1,24 @@
 // Seeding and plain-generation kernels for gfx950 (CDNA4, wave64).
 //
-// init: one state per work-item, state[g] = H(seed, g) (Listing S4).
-// gen:  a persistent loop per lane. The lane loads its states once, then for
-//       every iteration k stores them to row k of the iteration-major output
-//       and advances them one xorshift step (Listing S5), and finally writes
-//       them back. The paper's kernel reads and writes 16 bytes of state per
-//       value per launch; here state traffic is 16 bytes per work-item per
-//       call, and each value costs only its 8 (or 4) output bytes.
+// init:  one state per work-item, state[g] = H(seed, g) (Listing S4).
+// gen:   a persistent loop per lane. The lane loads its states once, then for
+//        every iteration k stores them to row k of the iteration-major output
+//        and advances them one xorshift step (Listing S5), and finally writes
+//        them back. The paper's kernel reads and writes 16 bytes of state per
+//        value per launch; here state traffic is 16 bytes per work-item per
+//        call, and each value costs only its 8 (or 4) output bytes.
+// paced: the same on a persistent grid that keeps to a row schedule, for rows
+//        of any alignment (staged through LDS so that whole lines are stored)
+//        and, when the rows are too short to fill the device, with the
+//        iterations cut into segments that run side by side.
 //
 // Store layout: a wavefront owns 64 * V consecutive work-items (V = 2*P for
 // 64-bit output, 4*P for 32-bit), split into P "chunk columns". In column p,
 // lane l owns the 16 bytes at work-items [base + p*64*E + l*E, +E), E = 16 /
 // sizeof(T). So every store instruction of the wave writes one contiguous
 // 1 KiB line-aligned span (global_store_dwordx4 from all 64 lanes) whenever
-// the row start is 16-byte aligned. No LDS and no cross-lane traffic.
+// the row starts on a 128-byte line. Only staged rows use LDS per value.
+#include <algorithm>
 #include <atomic>
 
 #include "internal.h"
@@ -86,18 +91,21 @@ __device__ __forceinline__ void wait_until(uint64_t due)
     // At most about 2^16 polls of about 100 ns: a wait ends even if the
     // schedule were far ahead of the clock.
     uint32_t polls = 0;
+#pragma nounroll
     while (__builtin_amdgcn_s_memrealtime() < due && ++polls < (1u << 16))
         __builtin_amdgcn_s_sleep(2);
 }
 
-// One complete wavefront: its 64*P*E work-items starting at wbase, all
-// iterations. PACED: iteration k is written no earlier than
-// t0 + ((sched + k * delta256) >> 8) clock ticks.
-template <typename T, int P, bool NT, bool ALIGNED, bool STAR, bool PACED>
+// Output words of one 128-byte line, the unit in which the device's memory
+// takes writes whole.
+template <typename T> constexpr uint32_t kLine = 128 / sizeof(T);
+
+// One complete wavefront, all iterations, in place, unscheduled: its 64*P*E
+// work-items starting at wbase.
+template <typename T, int P, bool NT, bool ALIGNED, bool STAR>
 __device__ __forceinline__ void full_wave(uint64_t *__restrict__ state, uint32_t n,
                                           uint32_t iters, T *__restrict__ out, uint64_t wbase,
-                                          uint32_t lane, uint64_t t0, uint64_t sched,
-                                          uint64_t delta256)
+                                          uint32_t lane)
 {
     typedef Vec16<T> VT;
     constexpr int E = VT::E;
@@ -110,10 +118,6 @@ __device__ __forceinline__ void full_wave(uint64_t *__restrict__ state, uint32_t
             x[p][e] = state[g + e];
     }
     for (uint32_t k = 0; k < iters; ++k) {
-        if (PACED) {
-            wait_until(t0 + (sched >> 8));
-            sched += delta256;
-        }
         T *row = out + (size_t)k * n;
         const bool al = ALIGNED || ((reinterpret_cast<uintptr_t>(row) & 15u) == 0);
 #pragma unroll
@@ -183,7 +187,7 @@ __device__ __forceinline__ void partial_wave(uint64_t *__restrict__ state, uint3
 }
 
 // P chunk columns per lane; NT: non-temporal stores; ALIGNED: every row
-// start is 16-byte aligned (out 16-byte aligned and n*sizeof(T) % 16 == 0).
+// start is 16-byte aligned.
 template <typename T, int P, bool NT, bool ALIGNED, bool STAR>
 __global__ __launch_bounds__(1024) void gen_kernel(uint64_t *__restrict__ state, uint32_t n,
                                                    uint32_t iters, T *__restrict__ out)
@@ -195,42 +199,306 @@ __global__ __launch_bounds__(1024) void gen_kernel(uint64_t *__restrict__ state,
     if (wbase >= n)
         return;
     if (wbase + WAVE_ITEMS <= n)
-        full_wave<T, P, NT, ALIGNED, STAR, false>(state, n, iters, out, wbase, lane, 0, 0, 0);
+        full_wave<T, P, NT, ALIGNED, STAR>(state, n, iters, out, wbase, lane);
     else
         partial_wave<T, P, STAR>(state, n, iters, out, wbase, lane);
 }
 
-// The scheduled launch: a persistent grid of gridDim.x blocks, all resident
-// at once, walks strips of columns; in strip s, block b owns the columns of
-// block s * gridDim.x + b of the unscheduled launch. Every wavefront keeps
-// to one row schedule from its own start t0 (its first clock reading):
-// iteration k of strip s is written no earlier than
-// t0 + (s * iters + k) * delta256 / 256 clock ticks, so the wavefronts write
-// near the same row instead of drifting apart. (Measured on MI355X: one
-// start time shared by the whole grid, the first wavefront's, ran 3-20 %
-// slower at 2^20-2^24 states and the same at 2^26.) Rows are 16-byte
-// aligned (the launcher checks it).
-template <typename T, int P, bool NT, bool STAR>
-__global__ __launch_bounds__(1024) void gen_paced_kernel(uint64_t *__restrict__ state, uint32_t n,
-                                                         uint32_t iters, T *__restrict__ out,
-                                                         uint32_t nstrips, uint64_t delta256)
+// ---- the scheduled launch --------------------------------------------------
+
+// A persistent grid of gridDim.x blocks, all resident at once, walks strips of
+// columns. Every wavefront keeps to one row schedule from its own start t0
+// (its first clock reading): its row number j, counted over all its strips, is
+// written no earlier than t0 + j * delta256 / 256 clock ticks, so the
+// wavefronts write near the same row instead of drifting apart. (Measured on
+// MI355X: one start time shared by the whole grid, the first wavefront's, ran
+// 3-20 % slower at 2^20-2^24 states and the same at 2^26.) The strips are of
+// equal size: a grid as large as fits leaves a last strip of few blocks that
+// takes as long as a full one (2,200,000 x 256 u64: 6.9 TB/s, 4.7 so).
+//
+// Bound by the memory's writes: 2^22 x 256 u64 7.0 TB/s at a schedule of 7,000
+// GB/s, where a large fill runs at 6.7. Registers decide whether every block
+// the occupancy query promises is resident: all variants stay within 64 vector
+// registers (8 wavefronts per SIMD) but the staged one of two 4-byte chunks
+// and those of four, and within 80 scalar ones (with 88, of 8 wavefronts per
+// SIMD only 7 were resident and a launch took twice its time).
+//
+// Staged rows (SHIFT). A row that does not start on a 128-byte line has its
+// wavefronts' spans end inside lines, which then reach the memory in parts
+// (half the rate). Here a wavefront writes the lines that START in its
+// columns: it also keeps the kLine states right of them (one per lane, about
+// 6 % more steps), puts the row's words into LDS in column order and reads
+// them back at the row's line offset, so its stores are whole lines again.
+// LDS moves 32 bytes per 16 stored, a quarter of its rate at 7 TB/s.
+// 10^6 + 3 states x 256: u64 4.1 -> 6.9 TB/s, u32 4.1 -> 6.6.
+//
+// Segments (Polys = JumpPolys). A row of n states occupies n / 128 wavefronts
+// (u64); below some 500 they cannot have enough stores under way. So the
+// iterations are cut into segments, each computed by its own blocks from the
+// states jumped ahead by T^(first row) (build_jump, jump_by); the blocks of
+// the last segment write the new states. 4,096 x 10,000 u64: 1,650 -> 63 us
+// (0.2 -> 5.2 TB/s), 65,536 x 1,000: 173 -> 80 us.
+//
+// In both, wavefronts read states that others advance, so the new states go
+// to another buffer.
+struct PacedArgs {
+    const uint64_t *state_in;
+    uint64_t *state_out; // state_in itself for an in-place launch
+    void *out;
+    uint32_t n, iters;
+    uint32_t seg_rows;   // iterations per segment (iters: one segment)
+    uint32_t col_blocks; // blocks that cover one row
+    uint32_t items;      // segments * col_blocks
+    uint64_t delta256;   // schedule step, clock ticks * 256 (0: none)
+    uint32_t burst;      // rows per schedule step
+};
+
+// T^k as a nibble table in LDS for one block: `poly` holds the 64
+// coefficients of T^k = sum over i of poly_i T^i. Lane j of the first
+// wavefront forms T^k e_j by 64 steps from e_j (about 1 us; no memory);
+// entry v of table q is then T^k (v << 4q).
+__device__ __forceinline__ void build_jump(uint64_t poly, uint64_t *cols, uint64_t *tab)
 {
-    constexpr uint64_t WAVE_ITEMS = 64ull * P * Vec16<T>::E;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t waves_per_block = blockDim.x >> 6;
-    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    for (uint32_t s = 0; s < nstrips; ++s) {
-        const uint64_t wave =
-            ((uint64_t)s * gridDim.x + blockIdx.x) * waves_per_block + (threadIdx.x >> 6);
-        const uint64_t wbase = wave * WAVE_ITEMS;
-        if (wbase >= n)
-            return; // later strips lie further right
-        if (wbase + WAVE_ITEMS > n) {
-            partial_wave<T, P, STAR>(state, n, iters, out, wbase, lane);
-            return; // the last wavefront of the launch
+    __syncthreads(); // the block is done with the previous table
+    if (threadIdx.x < 64) {
+        uint64_t e = (uint64_t)1 << threadIdx.x, y = 0;
+#pragma unroll 8
+        for (int i = 0; i < 64; ++i) {
+            y ^= e & (0 - ((poly >> i) & 1u));
+            e = xs_step(e);
         }
-        full_wave<T, P, NT, true, STAR, true>(state, n, iters, out, wbase, lane, t0,
-                                              (uint64_t)s * iters * delta256, delta256);
+        cols[threadIdx.x] = y;
+    }
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < 256; t += blockDim.x) {
+        uint64_t y = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            y ^= (t >> b) & 1u ? cols[(t >> 4) * 4 + b] : 0;
+        tab[t] = y;
+    }
+    __syncthreads();
+}
+
+// T^k x from such a table: the lanes' lookups for one nibble fall into one
+// 128-byte row of LDS, so they never share a bank.
+__device__ __forceinline__ uint64_t jump_by(const uint64_t *tab, uint64_t x)
+{
+    uint64_t y = 0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+        y ^= tab[16 * q + (uint32_t)((x >> (4 * q)) & 15u)];
+    return y;
+}
+
+// Orders a wavefront's own LDS writes before its reads (and the reverse).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// 16 bytes at any word of LDS.
+__device__ __forceinline__ u64x2 lds_chunk(const uint64_t *p)
+{
+    typedef u64x2 u64x2_w __attribute__((aligned(8)));
+    return *reinterpret_cast<const u64x2_w *>(p);
+}
+__device__ __forceinline__ u32x4 lds_chunk(const uint32_t *p)
+{
+    typedef u32x4 u32x4_w __attribute__((aligned(4)));
+    return *reinterpret_cast<const u32x4_w *>(p);
+}
+
+// Keeps the value's computation before this point.
+__device__ __forceinline__ void pin(uint64_t &x) { asm volatile("" : "+v"(x)); }
+
+// Rows of one wavefront's columns, from its states x (and, for staged rows,
+// xh: the kLine states right of its columns, one per lane).
+template <typename T, int P, bool NT, bool STAR, bool SHIFT, bool WHOLE>
+__device__ __forceinline__ void paced_rows(uint64_t (&x)[P][Vec16<T>::E], uint64_t xh, T *row,
+                                           uint32_t rows, uint64_t n, uint64_t wbase,
+                                           uint32_t lane, T *stage, uint64_t t0, uint64_t &sched,
+                                           uint64_t delta256, uint32_t burst)
+{
+    typedef Vec16<T> VT;
+    typedef typename VT::type V16;
+    constexpr int E = VT::E;
+    constexpr uint32_t W = 64u * P * E, L = kLine<T>;
+    // Columns from wbase to the end of the row (all that matter here).
+    const uint32_t cols = (uint32_t)(n - wbase < W + L ? n - wbase : W + L);
+    uint32_t left = 1;
+#pragma nounroll
+    for (uint32_t k = 0; k < rows; ++k) {
+        if (delta256 && --left == 0) {
+            wait_until(t0 + (sched >> 8));
+            sched += delta256;
+            left = burst;
+        }
+        if (SHIFT) {
+            // The wavefront writes the lines that start in its columns.
+            const uint32_t d =
+                (0u - (uint32_t)(reinterpret_cast<uintptr_t>(row) / sizeof(T))) & (L - 1);
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                *reinterpret_cast<V16 *>(stage + p * 64 * E + lane * E) =
+                    VT::template pack<STAR>(x[p]);
+            if (lane < L)
+                stage[W + lane] = emit<T, STAR>(xh);
+            wave_lds_fence();
+            V16 v[P];
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                v[p] = lds_chunk(stage + d + p * 64 * E + lane * E);
+            // The words of the row's first and last, partial lines and
+            // chunks: its first d, and those past its last whole chunk.
+            const uint32_t lim = WHOLE || d >= cols ? 0 : cols - d;
+            const T head = stage[lane];
+            T tail = 0;
+            if (!WHOLE)
+                tail = stage[d + (lim & ~(E - 1u)) + (lane & (E - 1u))];
+            wave_lds_fence();
+            // The next states are formed while the LDS answers.
+            __builtin_amdgcn_sched_barrier(0);
+            xh = xs_step(xh);
+            pin(xh);
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    x[p][e] = xs_step(x[p][e]);
+                    pin(x[p][e]);
+                }
+            T *const dst = row + wbase + d;
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                if (WHOLE || p * 64 + lane < lim / E)
+                    store16<NT>(reinterpret_cast<V16 *>(dst + p * 64 * E + lane * E), v[p]);
+            if (wbase == 0 && lane < d && lane < n)
+                row[lane] = head;
+            if (!WHOLE && lane < lim % E && lim < W)
+                dst[(lim & ~(E - 1u)) + lane] = tail;
+        } else {
+            // Whole lines: every row is a whole number of them.
+            T *const dst = row + wbase;
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                if (WHOLE || (p * 64 + lane) * E < cols)
+                    store16<NT>(reinterpret_cast<V16 *>(dst + p * 64 * E + lane * E),
+                                VT::template pack<STAR>(x[p]));
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    x[p][e] = xs_step(x[p][e]);
+            }
+        }
+        row += n;
+    }
+}
+
+// The states of a wavefront's columns, 16 bytes at a time where all of them
+// exist (whole).
+template <int P, int E>
+__device__ __forceinline__ void load_states(uint64_t (&x)[P][E], const uint64_t *state, uint64_t n,
+                                            uint64_t wbase, uint32_t lane, bool whole)
+{
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const uint64_t g = wbase + (uint64_t)p * 64 * E + (uint64_t)lane * E;
+        if (whole) {
+#pragma unroll
+            for (int e = 0; e < E; e += 2) {
+                const u64x2 v = *reinterpret_cast<const u64x2 *>(state + g + e);
+                x[p][e] = v.x;
+                x[p][e + 1] = v.y;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                x[p][e] = g + e < n ? state[g + e] : 0;
+        }
+    }
+}
+template <int P, int E>
+__device__ __forceinline__ void store_states(const uint64_t (&x)[P][E], uint64_t *state,
+                                             uint64_t n, uint64_t wbase, uint32_t lane, bool whole)
+{
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const uint64_t g = wbase + (uint64_t)p * 64 * E + (uint64_t)lane * E;
+        if (whole) {
+#pragma unroll
+            for (int e = 0; e < E; e += 2)
+                *reinterpret_cast<u64x2 *>(state + g + e) = u64x2{x[p][e], x[p][e + 1]};
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (g + e < n)
+                    state[g + e] = x[p][e];
+        }
+    }
+}
+
+// A launch without segments takes no polynomials.
+struct NoPolys {
+};
+__device__ __forceinline__ uint64_t poly_of(const NoPolys &, uint32_t) { return 0; }
+__device__ __forceinline__ uint64_t poly_of(const JumpPolys &p, uint32_t seg) { return p.c[seg]; }
+
+template <typename T, int P, bool NT, bool STAR, bool SHIFT, typename Polys>
+__global__ __launch_bounds__(1024) void
+gen_paced_kernel(const PacedArgs a, const Polys polys)
+{
+    constexpr int E = Vec16<T>::E;
+    constexpr uint32_t W = 64u * P * E; // work-items per wavefront
+    constexpr uint32_t L = kLine<T>;
+    constexpr bool SEG = sizeof(Polys) > sizeof(NoPolys);
+    __shared__ uint64_t jump_cols[SEG ? 64 : 1], jump_tab[SEG ? 256 : 1];
+    extern __shared__ __align__(16) unsigned char lds_dyn[];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    T *stage = reinterpret_cast<T *>(lds_dyn) + (size_t)wid * (W + L);
+    T *const out = static_cast<T *>(a.out);
+    const uint64_t n = a.n;
+    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    uint64_t sched = 0;
+    uint32_t have = 0; // the segment jump_tab belongs to (0: none)
+    for (uint32_t item = blockIdx.x; item < a.items; item += gridDim.x) {
+        const uint32_t seg = SEG ? item / a.col_blocks : 0;
+        const uint64_t wbase =
+            ((uint64_t)(SEG ? item - seg * a.col_blocks : item) * (blockDim.x >> 6) + wid) * W;
+        if (!SEG && wbase >= n)
+            return; // later strips lie further right
+        const bool mine = wbase + W <= n;
+        uint64_t x[P][E], xh = 0;
+        load_states(x, a.state_in, n, wbase, lane, mine);
+        if (SHIFT && lane < L && wbase + W + lane < n)
+            xh = a.state_in[wbase + W + lane];
+        if (SEG && seg) { // uniform over the block
+            if (seg != have)
+                build_jump(poly_of(polys, seg), jump_cols, jump_tab);
+            have = seg;
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    x[p][e] = jump_by(jump_tab, x[p][e]);
+            if (SHIFT)
+                xh = jump_by(jump_tab, xh);
+        }
+        if (SEG && wbase >= n)
+            continue; // no columns here (the wavefront still helped with the table)
+        const uint32_t k0 = seg * a.seg_rows;
+        const uint32_t rows = a.iters - k0 < a.seg_rows ? a.iters - k0 : a.seg_rows;
+        T *row = out + (uint64_t)k0 * n;
+        if (wbase + W + (SHIFT ? L : 0) <= n)
+            paced_rows<T, P, NT, STAR, SHIFT, true>(x, xh, row, rows, n, wbase, lane, stage, t0,
+                                                    sched, a.delta256, a.burst);
+        else
+            paced_rows<T, P, NT, STAR, SHIFT, false>(x, xh, row, rows, n, wbase, lane, stage, t0,
+                                                     sched, a.delta256, a.burst);
+        if (k0 + rows == a.iters)
+            store_states(x, a.state_out, n, wbase, lane, mine);
     }
 }
 
@@ -247,14 +515,18 @@ hipError_t launch_gen_t(uint32_t block, uint64_t *state, uint32_t n, uint32_t it
 }
 
 // The scheduled launch: grid = every block that fits on the device at once
-// (at most the blocks the columns need); the schedule's step is the time
+// (at most the blocks the work needs); the schedule's step is the time
 // the grid's share of a row (blocks x block x 16 x P bytes) takes at
 // pace_gbs, in ticks of the device's constant-rate clock, times 256.
-template <typename T, int P, bool NT, bool STAR>
-hipError_t launch_paced_t(uint32_t block, uint32_t pace_gbs, uint64_t *state, uint32_t n,
-                          uint32_t iters, T *out, hipStream_t s)
+template <typename T, int P, bool NT, bool STAR, bool SHIFT, typename Polys>
+hipError_t launch_paced_t(const GenPlan &plan, const Polys &polys, uint64_t *state,
+                          uint64_t *state_out, uint32_t n, uint32_t iters, void *out,
+                          hipStream_t s)
 {
-    constexpr uint64_t WAVE_ITEMS = 64ull * P * Vec16<T>::E;
+    const uint32_t block = plan.cfg.block, pace_gbs = plan.cfg.pace_gbs;
+    constexpr uint32_t W = 64u * P * Vec16<T>::E;
+    const uint32_t wpb = block / 64;
+    const size_t lds = SHIFT ? (size_t)wpb * (W + kLine<T>) * sizeof(T) : 0;
     // Device attributes and this kernel's occupancy at `block`, cached per
     // device (devices beyond the table query every launch).
     constexpr int kDevs = 16;
@@ -265,7 +537,7 @@ hipError_t launch_paced_t(uint32_t block, uint32_t pace_gbs, uint64_t *state, ui
     if (e != hipSuccess)
         return e;
     const bool cacheable = dev >= 0 && dev < kDevs;
-    const int bi = (int)(block / 64) - 1; // block 64..1024
+    const int bi = (int)wpb - 1; // block 64..1024
     int cus = cacheable ? cached_cus[dev].load(std::memory_order_relaxed) : 0;
     int clock_khz = cacheable ? cached_khz[dev].load(std::memory_order_relaxed) : 0;
     int occ = cacheable ? cached_occ[dev][bi].load(std::memory_order_relaxed) : 0;
@@ -275,7 +547,7 @@ hipError_t launch_paced_t(uint32_t block, uint32_t pace_gbs, uint64_t *state, ui
             e = hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, dev);
         if (e == hipSuccess)
             e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &occ, gen_paced_kernel<T, P, NT, STAR>, (int)block, 0);
+                &occ, gen_paced_kernel<T, P, NT, STAR, SHIFT, Polys>, (int)block, lds);
         if (e != hipSuccess)
             return e;
         cus = cus > 0 ? cus : 1;
@@ -287,47 +559,81 @@ hipError_t launch_paced_t(uint32_t block, uint32_t pace_gbs, uint64_t *state, ui
             cached_occ[dev][bi].store(occ, std::memory_order_relaxed);
         }
     }
-    const uint64_t waves = (n + WAVE_ITEMS - 1) / WAVE_ITEMS;
-    const uint64_t need = (waves * 64 + block - 1) / block;
+    const uint64_t waves = ((uint64_t)n + W - 1) / W;
+    const uint64_t col_blocks = (waves + wpb - 1) / wpb;
+    const uint64_t items = col_blocks * plan.segs;
     uint64_t grid = (uint64_t)occ * (uint64_t)cus;
-    if (grid > need)
-        grid = need;
-    const uint64_t nstrips = (need + grid - 1) / grid;
+    // Strips of equal size.
+    const uint64_t strips = (items + grid - 1) / grid;
+    grid = (items + strips - 1) / strips;
     const double row_bytes = (double)grid * block * 16.0 * P;
-    const double ticks = row_bytes / (pace_gbs * 1e9) * clock_khz * 1e3;
-    const uint64_t delta256 = (uint64_t)(ticks * 256.0);
-    gen_paced_kernel<T, P, NT, STAR><<<dim3((uint32_t)grid), dim3(block), 0, s>>>(
-        state, n, iters, out, (uint32_t)nstrips, delta256);
+    const double ticks = pace_gbs ? row_bytes / (pace_gbs * 1e9) * clock_khz * 1e3 : 0.0;
+    PacedArgs a;
+    a.state_in = state;
+    a.state_out = state_out;
+    a.out = out;
+    a.n = n;
+    a.iters = iters;
+    a.seg_rows = plan.seg_rows;
+    a.col_blocks = (uint32_t)col_blocks;
+    a.items = (uint32_t)items;
+    // Rows between clock readings: about a microsecond of the schedule (a
+    // reading costs a wavefront about 0.1 us).
+    const double rows_per_us = ticks > 0 ? clock_khz * 1e-3 / ticks : 0.0;
+    a.burst = rows_per_us > 8.0 ? 8u : rows_per_us > 1.0 ? (uint32_t)rows_per_us : 1u;
+    a.delta256 = (uint64_t)(ticks * 256.0 * a.burst);
+    gen_paced_kernel<T, P, NT, STAR, SHIFT, Polys>
+        <<<dim3((uint32_t)grid), dim3(block), lds, s>>>(a, polys);
     return hipGetLastError();
 }
 
-template <typename T, int P, bool STAR>
-hipError_t launch_gen_p(const rngx_launch &cfg, bool al, uint64_t *state, uint32_t n,
-                        uint32_t iters, T *out, hipStream_t s)
+template <typename T, int P, bool STAR, bool SHIFT, typename Polys>
+hipError_t launch_paced_nt(const GenPlan &plan, const Polys &polys, uint64_t *state, uint64_t *so,
+                           uint32_t n, uint32_t iters, T *out, hipStream_t s)
 {
-    if (cfg.pace_gbs && al && iters >= 2)
-        return cfg.nontemporal
-                   ? launch_paced_t<T, P, true, STAR>(cfg.block, cfg.pace_gbs, state, n, iters,
-                                                      out, s)
-                   : launch_paced_t<T, P, false, STAR>(cfg.block, cfg.pace_gbs, state, n, iters,
-                                                       out, s);
-    if (cfg.nontemporal)
-        return al ? launch_gen_t<T, P, true, true, STAR>(cfg.block, state, n, iters, out, s)
-                  : launch_gen_t<T, P, true, false, STAR>(cfg.block, state, n, iters, out, s);
-    return al ? launch_gen_t<T, P, false, true, STAR>(cfg.block, state, n, iters, out, s)
-              : launch_gen_t<T, P, false, false, STAR>(cfg.block, state, n, iters, out, s);
+    return plan.cfg.nontemporal
+               ? launch_paced_t<T, P, true, STAR, SHIFT>(plan, polys, state, so, n, iters, out, s)
+               : launch_paced_t<T, P, false, STAR, SHIFT>(plan, polys, state, so, n, iters, out,
+                                                          s);
+}
+
+template <typename T, int P, bool STAR>
+hipError_t launch_gen_p(const GenPlan &plan, const JumpPolys &polys, uint64_t *state,
+                        uint64_t *alt, uint32_t n, uint32_t iters, T *out, hipStream_t s)
+{
+    if (plan.scheduled) {
+        uint64_t *const so = plan.out_of_place() ? alt : state;
+        if (plan.segs > 1) // one chunk per lane (plan_gen)
+            return plan.shift
+                       ? launch_paced_nt<T, 1, STAR, true>(plan, polys, state, so, n, iters, out, s)
+                       : launch_paced_nt<T, 1, STAR, false>(plan, polys, state, so, n, iters, out,
+                                                            s);
+        // Staged rows: at most two chunks (four would stage more than 64 KiB
+        // a block).
+        constexpr int Q = P < 2 ? P : 2;
+        const NoPolys none;
+        return plan.shift
+                   ? launch_paced_nt<T, Q, STAR, true>(plan, none, state, so, n, iters, out, s)
+                   : launch_paced_nt<T, P, STAR, false>(plan, none, state, so, n, iters, out, s);
+    }
+    const bool nt = plan.cfg.nontemporal != 0;
+    const uint32_t block = plan.cfg.block;
+    if (nt)
+        return plan.aligned16 ? launch_gen_t<T, P, true, true, STAR>(block, state, n, iters, out, s)
+                              : launch_gen_t<T, P, true, false, STAR>(block, state, n, iters, out,
+                                                                      s);
+    return plan.aligned16 ? launch_gen_t<T, P, false, true, STAR>(block, state, n, iters, out, s)
+                          : launch_gen_t<T, P, false, false, STAR>(block, state, n, iters, out, s);
 }
 
 template <typename T, bool STAR>
-hipError_t launch_gen_typed(const rngx_launch &cfg, uint64_t *state, uint32_t n, uint32_t iters,
-                            T *out, hipStream_t s)
+hipError_t launch_gen_typed(const GenPlan &plan, const JumpPolys &polys, uint64_t *state,
+                            uint64_t *alt, uint32_t n, uint32_t iters, T *out, hipStream_t s)
 {
-    const bool al = (reinterpret_cast<uintptr_t>(out) & 15u) == 0 &&
-                    ((uint64_t)n * sizeof(T)) % 16u == 0;
-    switch (cfg.chunks) {
-    case 1: return launch_gen_p<T, 1, STAR>(cfg, al, state, n, iters, out, s);
-    case 2: return launch_gen_p<T, 2, STAR>(cfg, al, state, n, iters, out, s);
-    default: return launch_gen_p<T, 4, STAR>(cfg, al, state, n, iters, out, s);
+    switch (plan.cfg.chunks) {
+    case 1: return launch_gen_p<T, 1, STAR>(plan, polys, state, alt, n, iters, out, s);
+    case 2: return launch_gen_p<T, 2, STAR>(plan, polys, state, alt, n, iters, out, s);
+    default: return launch_gen_p<T, 4, STAR>(plan, polys, state, alt, n, iters, out, s);
     }
 }
 
@@ -350,16 +656,68 @@ hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_gen(const rngx_launch &cfg, bool u32, bool star, uint64_t *state, uint32_t n,
-                      uint32_t iters, void *out, hipStream_t s)
+// What the Infinity Cache holds.
+static constexpr uint64_t kCacheBytes = 256ull << 20;
+
+GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, const void *out)
+{
+    const uint64_t row = (uint64_t)n * (u32 ? 4 : 8), bytes = row * iters;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(out) | (iters > 1 ? row : 0);
+    const bool lines = at % 128 == 0;
+    GenPlan p;
+    p.cfg = cfg;
+    p.seg_rows = iters;
+    p.aligned16 = at % 16 == 0;
+    // Narrow rows, below 4 MiB: as configured they would leave wavefronts or
+    // whole compute units without work, so every lane takes one chunk and
+    // every block is small. Fewer than 512 wavefronts (a wavefront writes an
+    // aligned row in about 55 ns, so they fall short of the memory's rate)
+    // or 4096 (staged rows, about 220 ns each; stored word by word, 300 and
+    // more) and at least 64 iterations (24 off the lines; a segment's jump
+    // costs about 2.5 us): the iterations are cut into segments of at least 8. 4,096 x 10,000 u64: 63 us against 1,650 in one
+    // segment of 512 x 2; 65,536 x 64, one segment: 10.1 us against 11.7 in
+    // two and 16.1 with blocks of 512 x 2.
+    const uint64_t waves = (row + 1023) / 1024;
+    const bool narrow = cfg.pace_gbs && iters >= 2 && waves < 4096;
+    if (narrow && iters >= (lines ? 64u : 24u)) {
+        const uint64_t target = lines ? (waves < 512 ? 1024 : 1) : 4096;
+        const uint64_t segs =
+            std::min<uint64_t>({(target + waves / 2) / waves, iters / 8, kMaxSegs});
+        if (segs > 1) {
+            p.seg_rows = (uint32_t)((iters + segs - 1) / segs);
+            p.segs = (iters + p.seg_rows - 1) / p.seg_rows;
+        }
+    }
+    // Rows off the 128-byte lines are staged where the memory takes the
+    // values: stored where it lies, such a row writes its lines in parts
+    // (10^6 + 3 states x 256 u64: 6.89 TB/s staged, 4.13 not; 10^6 + 2, 16-byte
+    // aligned: 6.9 and 4.3). Below 256 MiB the Infinity Cache puts the parts
+    // together and staging only costs (2^22 + 1 x 8: 54.7 us staged, 51.6 not).
+    p.shift = !lines && iters >= 2 && (bytes > kCacheBytes || p.segs > 1);
+    p.scheduled = p.shift || (cfg.pace_gbs && iters >= 2 && p.aligned16);
+    if (narrow && p.scheduled) {
+        p.cfg.chunks = 1;
+        p.cfg.block = std::min(cfg.block, 256u);
+        // Outputs well inside that cache run ahead of HBM's rate, so a
+        // schedule only holds them back (131,072 x 100 u64: 5.25 TB/s free,
+        // below 5.1 scheduled; 65,536 x 1,000: 5.5 free, 6.5 scheduled).
+        if (bytes <= kCacheBytes * 3 / 4)
+            p.cfg.pace_gbs = 0;
+    }
+    return p;
+}
+
+hipError_t launch_gen(const GenPlan &plan, const JumpPolys &polys, bool u32, bool star,
+                      uint64_t *state, uint64_t *alt, uint32_t n, uint32_t iters, void *out,
+                      hipStream_t s)
 {
     uint32_t *o32 = static_cast<uint32_t *>(out);
     uint64_t *o64 = static_cast<uint64_t *>(out);
     if (u32)
-        return star ? launch_gen_typed<uint32_t, true>(cfg, state, n, iters, o32, s)
-                    : launch_gen_typed<uint32_t, false>(cfg, state, n, iters, o32, s);
-    return star ? launch_gen_typed<uint64_t, true>(cfg, state, n, iters, o64, s)
-                : launch_gen_typed<uint64_t, false>(cfg, state, n, iters, o64, s);
+        return star ? launch_gen_typed<uint32_t, true>(plan, polys, state, alt, n, iters, o32, s)
+                    : launch_gen_typed<uint32_t, false>(plan, polys, state, alt, n, iters, o32, s);
+    return star ? launch_gen_typed<uint64_t, true>(plan, polys, state, alt, n, iters, o64, s)
+                : launch_gen_typed<uint64_t, false>(plan, polys, state, alt, n, iters, o64, s);
 }
 
 } // namespace rngx

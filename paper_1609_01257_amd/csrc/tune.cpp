@@ -386,7 +386,7 @@ extern "C" int rngx_autotune_plain(uint32_t n_iters, int u32, void *out, uint32_
             return rc2;
         RNGX_HIP(hipEventRecord(sc.e0, s));
         for (uint32_t r = 0; r < n; ++r)
-            RNGX_HIP(launch_gen(cfg, u32 != 0, star, g.state, g.n, n_iters, out, s));
+            RNGX_HIP(run_gen_locked(g, cfg, n_iters, out, s, u32 != 0, star));
         RNGX_HIP(hipEventRecord(sc.e1, s));
         RNGX_HIP(hipEventSynchronize(sc.e1));
         float t = 0.f;
@@ -399,7 +399,7 @@ extern "C" int rngx_autotune_plain(uint32_t n_iters, int u32, void *out, uint32_
         if (rc2)
             return rc2;
         take_stray_error("before an autotuned rng kernel launch");
-        RNGX_HIP(launch_gen(cfg, u32 != 0, star, g.state, g.n, n_iters, out, s));
+        RNGX_HIP(run_gen_locked(g, cfg, n_iters, out, s, u32 != 0, star));
         uint64_t sum = 0;
         rc2 = rngx_checksum(static_cast<const uint64_t *>(out), words, s, &sum);
         if (rc2)
@@ -439,8 +439,9 @@ extern "C" int rngx_autotune_plain(uint32_t n_iters, int u32, void *out, uint32_
     for (int i = 0; i < kBases; ++i)
         if ((rc = try_cfg(base[i], &ms)))
             return rc;
-    // Row schedules (they apply to aligned rows and calls of at least 2
-    // iterations; elsewhere the launch runs unscheduled). Which base and
+    // Row schedules (they apply to calls of at least 2 iterations whose rows
+    // are 16-byte aligned or staged; elsewhere the launch runs unscheduled,
+    // and rows below 4 MiB run in a shape of their own). Which base and
     // which rate suit a schedule is not predicted by the unscheduled times
     // (measured), so: every base at 6000, 6750 and 7500 GB/s, then the two
     // bases fastest with a schedule at 5500..8000 in steps of 250.
@@ -509,7 +510,7 @@ extern "C" int rngx_autotune_plain(uint32_t n_iters, int u32, void *out, uint32_
     // generator is left exactly as it was (state and cursor).
     if ((rc = restore()))
         return rc;
-    RNGX_HIP(launch_gen(result->best, u32 != 0, star, g.state, g.n, n_iters, out, s));
+    RNGX_HIP(run_gen_locked(g, result->best, n_iters, out, s, u32 != 0, star));
     if ((rc = restore()))
         return rc;
     RNGX_HIP(hipEventRecord(g.state_ready, s));

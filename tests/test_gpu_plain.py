@@ -473,3 +473,72 @@ def test_tune_cache_roundtrip(tmp_path):
         rngx.set_launch(False, **old64)
         rngx.set_launch(True, **old32)
         rngx.set_batch_cfg(**oldb)
+
+
+# Short rows: the iterations are cut into segments of at least 8 rows, each
+# from states jumped ahead. Columns around a wavefront's 128 (u64) or 256
+# (u32), a line's 16 or 32, blocks with idle wavefronts; iteration counts
+# whose last segment is short.
+@pytest.mark.parametrize("u32", [False, True])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 127, 128, 129, 143, 144, 255, 256, 257, 288, 1024,
+                               1025, 4096, 16387])
+def test_segmented_short_rows(oracle, u32, n):
+    gen, want = (rngx.generate_u32, oracle.generate_u32) if u32 else (rngx.generate,
+                                                                     oracle.generate)
+    for iters, offset in [(24, 1), (64, 0), (65, 0), (257, 3), (2100, 0)]:
+        rngx.init(11, n)
+        dt = torch.int32 if u32 else torch.int64
+        first = torch.zeros(2 * n, dtype=dt, device="cuda")
+        buf = torch.zeros(iters * n + offset + 1, dtype=dt, device="cuda")
+        gen(2, first)
+        gen(iters, buf[offset:offset + iters * n])
+        torch.cuda.synchronize()
+        host = (_u32 if u32 else _u64)(buf)
+        assert (host[:offset] == 0).all() and host[offset + iters * n] == 0
+        exp = want(11, n, iters, cursor=2)
+        assert np.array_equal(host[offset:-1].reshape(iters, n), exp), (iters, offset)
+        # The states were advanced past every segment, in the other buffer.
+        st, _, c = rngx.get_state()
+        assert c == iters + 2
+        assert np.array_equal(st, oracle.generate(11, n, 1, cursor=c).ravel())
+
+
+# Rows off the 128-byte lines and outputs above 256 MiB: staged rows. The last
+# wavefront has a whole line's states right of it, some, or none.
+@pytest.mark.parametrize("u32,n,offset", [(False, (1 << 22) + 1, 0), (False, (1 << 22) - 14, 1),
+                                          (False, (1 << 22) + 240, 5), (True, (1 << 23) + 33, 0),
+                                          (True, (1 << 23) - 31, 7)])
+def test_staged_rows(oracle, u32, n, offset):
+    iters = 9
+    assert np.array_equal(run(6, n, iters, u32=u32, offset=offset, pre=1),
+                          (oracle.generate_u32 if u32 else oracle.generate)(6, n, iters, cursor=1))
+    st, _, c = rngx.get_state()
+    assert c == iters + 1 and np.array_equal(st, oracle.generate(6, n, 1, cursor=c).ravel())
+
+
+def test_scrambled_segments_and_staged_rows(oracle, star):
+    for u32, n, iters in [(False, 4099, 100), (True, 4099, 100), (True, 8192, 100),
+                          (True, (1 << 23) + 1, 9)]:
+        got = run(3, n, iters, u32=u32)
+        exp = (oracle.generate_star_u32 if u32 else oracle.generate_star)(3, n, iters)
+        assert np.array_equal(got, exp), (u32, n, iters)
+
+
+def test_paths_with_and_without_a_second_state_buffer_alternate(oracle):
+    # In-place and out-of-place calls in turn, on two streams.
+    seed, n = 5, 20003
+    rngx.init(seed, n)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs, k = [], 0
+    for i, iters in enumerate([1, 100, 3, 100, 24, 1, 1000, 2]):
+        o = torch.empty(iters * n, dtype=torch.int64, device="cuda")
+        s = streams[i % 2]
+        s.wait_stream(torch.cuda.current_stream())
+        o.record_stream(s)
+        rngx.generate(iters, o, stream=s)
+        outs.append((k, iters, o))
+        k += iters
+    torch.cuda.synchronize()
+    exp = oracle.generate(seed, n, k)
+    for at, iters, o in outs:
+        assert np.array_equal(_u64(o).reshape(iters, n), exp[at:at + iters]), at
