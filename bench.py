@@ -29,8 +29,8 @@ GIB = 1 << 30
 # pace_gbs); u32 block 0 = chosen by size.
 LIB_DEFAULT_U64 = (512, 2, 1, 7000)
 LIB_DEFAULT_U32 = (0, 0, 0, 0)
-# The request server's launch configuration for batches above 2^23 values
-# (the grouped order), used by the in-pool batched comparator.
+# The request server's launch configuration (the values that leave the order
+# to the library), used by the in-pool batched comparator.
 SERVER_LARGE_BATCH_CFG = dict(values_per_lane=16, waves_per_block=4, blocks=0, use_graph=False,
                               row_values=16, run_items=0, per_item=False, group=32,
                               group_steps=8, pace_gbs=6250)

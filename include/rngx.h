@@ -318,7 +318,9 @@ int rngx_generate_batch(const rngx_req *reqs, uint32_t m, uint64_t *out, uint64_
  * (262,272 bytes, one per device, held until the process ends) instead of
  * a buffer allocated for the batch; the jump tables are static device arrays
  * too. The launch is direct (never a captured graph) in the batch
- * configuration's launch shape; no profiler events are recorded.
+ * configuration's launch shape (with the default's values, one wave per item
+ * up to 2^26 values and the grouped order above: the sweep order needs
+ * memory); no profiler events are recorded.
  * reqs, m, out, out_cap, stream: as rngx_generate_batch; at most
  * RNGX_NOALLOC_MAX_REQS requests. The table is copied from pageable host
  * memory, which HIP does synchronously, so the call may block until the
@@ -369,10 +371,21 @@ int rngx_generate_batch_noalloc(const rngx_req *reqs, uint32_t m, uint64_t *out,
  *   time the grid's items of one step take at pace_gbs, on the device's
  *   constant-rate clock (bounded waits, as for rngx_launch.pace_gbs). 0
  *   without a group.
- * Default: the grouped order with values_per_lane 16, 4 waves per block,
- * a graph, 16-value rows, groups of 32, 8 steps and 6250 GB/s (the
- * autotuner's pick on a 4,096-stream table on MI355X, 6.2 TB/s there
- * against 5.9 for the persistent grid with S = 256).
+ * Default: values_per_lane 16, 4 waves per block, a graph, 16-value rows,
+ * groups of 32, 8 steps and 6250 GB/s. These values (whatever use_graph,
+ * blocks and run_items) leave the order to the library, which launches
+ * directly, without a graph (a stream that is being captured excepted: there
+ * they run as given):
+ *   up to 2^26 values, one wave per 1,024-value item; a table of up to 48
+ *   requests travels in the kernel's arguments, a longer one is uploaded by a
+ *   kernel, through one of 4 staging buffers, so that a call does not wait
+ *   for the one before it;
+ *   above, the sweep order: all wavefronts of the grid take consecutive
+ *   512-value tiles, then all move on together, at 7000 GB/s, from starting
+ *   states that a first kernel prepares (16 bytes of device memory per 8,192
+ *   values, kept with the staging buffer, given back by rngx_shutdown). 6.9
+ *   TB/s on a 4,096-stream table on MI355X, against 6.2 for the grouped order
+ *   and 5.9 for the persistent grid with S = 256.
  * The output never depends on the configuration. */
 typedef struct rngx_batch_cfg {
     uint32_t values_per_lane;
@@ -414,7 +427,8 @@ typedef struct rngx_tune_result {
  * 8, 16 or 32 waves per compute unit, those whose LDS fits; 16-value rows)
  * and of the grouped order (values_per_lane 16, 16-value rows, 4
  * wavefronts per block x groups of 16 or 32 wavefronts x 8 or 16 steps x
- * pace_gbs 5750, 6000, 6125, 6250, 6375, 6500 or 6750), each as back-to-back
+ * pace_gbs 5750, 6000, 6125, 6250, 6375, 6500 or 6750; the default's values
+ * among them stand for the library's own order), each as back-to-back
  * launches, then the four fastest again with three times the launches,
  * on this request table with HIP events, check
  * that every candidate's output has the same checksum, keep the fastest as
@@ -509,11 +523,10 @@ int rngx_jump_ahead(uint64_t state, uint64_t k, uint64_t *out);
  * memory and a launch slot are free.
  * pool: caller-owned device memory of pool_bytes bytes, 256-byte aligned,
  *       kept alive until rngx_serve_stop; results are written into it.
- * Batches are launched directly (no graph) with a schedule chosen by their
- * size, independent of the batch configuration: up to 2^23 values, one wave
- * per 1,024-value item (tables of up to 16 requests in the kernel's
- * arguments); larger, the persistent grid with 256 values per lane, at most
- * 8 waves per compute unit, fitted to the batch.
+ * Batches are launched directly (no graph) in the order that the batch API's
+ * default leaves to the library, whatever the batch configuration: up to 2^26
+ * values, one wave per 1,024-value item (tables of up to 48 requests in the
+ * kernel's arguments); larger, the sweep order.
  * Errors: RNGX_E_BUSY if already running; RNGX_E_INVAL (n_states == 0, NULL
  * or misaligned pool, pool_bytes < 256, n_streams outside 1..16,
  * max_batch == 0); RNGX_E_NOMEM; RNGX_E_HIP. */

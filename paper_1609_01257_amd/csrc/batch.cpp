@@ -3,12 +3,12 @@
 //
 // A BatchSlot owns one page-locked staging buffer and one device table
 // (a BatchDesc followed by the packed BatchReq array). A batch is staged on
-// the host, then one HIP graph copies the table to the device and launches
-// the persistent kernel; the graph is captured once per (capacity, launch
-// configuration) and replayed for every later batch, because the kernel
-// reads everything that changes from the device table. Before a slot's
-// staging buffer is rewritten, the slot's previous batch must have finished
-// (its `done` event).
+// the host; its table then goes to the device and the kernel is launched. In
+// a configuration that asks for a HIP graph, one graph does both: captured
+// once per (capacity, launch configuration) and replayed for every later
+// batch, because the kernel reads everything that changes from the device
+// table. Before a slot's staging buffer is rewritten, the slot's previous
+// batch must have finished (its `done` event).
 #include <algorithm>
 #include <chrono>
 #include <cstring>
@@ -46,11 +46,12 @@ int batch_group_index(uint32_t g)
 }
 
 // The constant tables every batch launch reads, in static device memory: one
-// copy per device, which lives as long as the process (1,136 KiB). They are
+// copy per device, which lives as long as the process (1,456 KiB). They are
 // filled on a device's first batched call of any kind, so later calls, also
 // the allocation-free entry point, only enqueue work.
-__device__ __align__(256) uint64_t g_pow2[64 * 64];                  // T^(2^b), 64 rows each
+__device__ __align__(256) uint64_t g_jump[kJumpTable];               // T^(a 16^i), 64 rows each
 __device__ __align__(256) uint64_t g_spread[kNumS * kSpreadTable];   // lane-spread tables per S
+__device__ __align__(256) uint64_t g_sweep[kSweepTables];            // the sweep order's tables
 __device__ __align__(256) uint64_t g_carry_nib[kNumS * kCarryTable]; // T^(63 S) nibble tables per S
 // T^(g 64 S - S) nibble tables per S and group size g (the grouped order).
 __device__ __align__(256) uint64_t g_group_nib[kNumS * kNumGroups * kCarryTable];
@@ -63,24 +64,32 @@ namespace {
 struct DevTables {
     int n_cus = 0;
     bool loaded = false;
-    const uint64_t *d_pow2 = nullptr;
+    const uint64_t *d_jump = nullptr;
     const uint64_t *d_spread = nullptr;
     const uint64_t *d_carry_nib = nullptr;
     const uint64_t *d_group_nib = nullptr;
+    const uint64_t *d_sweep = nullptr;
     int clock_khz = 0;               // constant-rate clock (s_memrealtime)
     uint64_t *d_acc = nullptr;       // checksum accumulator
     uint64_t *h_acc = nullptr;       // page-locked copy of it
 };
 constexpr int kMaxDevices = 64;
 
+// Where the library's order changes (batch_order), in values: 512 MiB.
+constexpr uint64_t kItemOrderValues = 1ull << 26;
+
+constexpr uint32_t kApiSlots = 4;
+
 struct BatchGlobals {
     std::mutex mu;
     DevTables dev[kMaxDevices];
-    // The grouped order: the autotuner's pick on the 4,096-stream table and
-    // the server's order for large batches (6.2 TB/s there against 5.9 for
-    // the persistent grid with S = 256).
+    // These values leave the order to the library (batch_order).
     rngx_batch_cfg cfg{16, 4, 0, 1, 16, 0, 0, 32, 8, 6250};
-    BatchSlot api_slot;
+    // Configurations that run as given use the first slot; the library's own
+    // order takes an idle one (free_api_slot), so that a call stages its table
+    // while the batches before it still run.
+    BatchSlot api_slot[kApiSlots];
+    uint32_t next_slot = 0;
     // Device address of `scratch` per device (rngx_generate_batch_noalloc),
     // taken once on the device's first such call.
     unsigned char *scratch_ptr[kMaxDevices] = {};
@@ -119,7 +128,9 @@ void free_acc(DevTables &t)
 // Host images of the lane-spread and carry tables for every allowed S, in
 // static host memory (built under tables_mu, once per device): filling the
 // device tables allocates nothing.
+uint64_t g_jump_host[kJumpTable];
 uint64_t g_spread_host[kNumS * kSpreadTable];
+uint64_t g_sweep_host[kSweepTables];
 uint64_t g_carry_host[kNumS * kCarryTable];
 uint64_t g_group_host[kNumS * kNumGroups * kCarryTable];
 
@@ -142,8 +153,39 @@ void nibble_table(uint64_t k, uint64_t *t)
         }
 }
 
-void build_host_tables(uint64_t *spread, uint64_t *nib, uint64_t *group)
+// Lane spread for steps of S values: entry ((16 q + v) * 64 + m) is
+// T^(m S) (v << 4q), so a lane m places above a wave-uniform state z with the
+// XOR of one entry per nibble of z.
+void spread_table(uint64_t S, uint64_t *sp)
 {
+    for (uint32_t m = 0; m < 64; ++m) {
+        uint64_t nib[256];
+        nibble_table(m * S, nib);
+        for (int i = 0; i < 256; ++i)
+            sp[i * 64 + m] = nib[i];
+    }
+}
+
+void build_host_tables(uint64_t *jump, uint64_t *spread, uint64_t *sweep, uint64_t *nib,
+                       uint64_t *group)
+{
+    for (uint64_t a = 0; a < 16; ++a)
+        power_rows(512 * a, sweep + kSweepTable + 64 * a);
+    spread_table(kAnchorValues, sweep + kSweepTable + 16 * 64);
+    for (uint32_t m = 0; m < 64; ++m) {
+        uint64_t rows[64];
+        power_rows(8 * m, rows);
+        for (int q = 0; q < 22; ++q)
+            for (uint64_t v = 0; v < 8; ++v) {
+                uint64_t e = 0;
+                for (int r = 0; r < 64; ++r)
+                    e |= (uint64_t)(__builtin_popcountll(rows[r] & (v << (3 * q))) & 1) << r;
+                sweep[(8 * q + v) * 64 + m] = e;
+            }
+    }
+    for (uint32_t i = 0; i < 16; ++i)
+        for (uint64_t a = 0; a < 16; ++a)
+            power_rows(a << (4 * i), jump + (16 * i + a) * 64);
     std::memset(spread, 0, sizeof(uint64_t) * kNumS * kSpreadTable);
     std::memset(nib, 0, sizeof(uint64_t) * kNumS * kCarryTable);
     // Grouped order: a lane that just emitted its S values of a tile moves
@@ -154,25 +196,7 @@ void build_host_tables(uint64_t *spread, uint64_t *nib, uint64_t *group)
                          group + ((size_t)i * kNumGroups + gi) * kCarryTable);
     for (int i = 0; i < kNumS; ++i) {
         const uint64_t S = kValuesPerLane[i];
-        // Lane spread: entry ((16 q + v) * 64 + m) is T^(m S) (v << 4q),
-        // so a lane m places above a wave-uniform state z with the XOR of
-        // one entry per nibble of z.
-        uint64_t *sp = spread + (size_t)kSpreadTable * i;
-        for (uint32_t m = 0; m < 64; ++m) {
-            uint64_t rows[64], col[64] = {0};
-            power_rows(m * S, rows);
-            for (int r = 0; r < 64; ++r)
-                for (int j = 0; j < 64; ++j)
-                    col[j] |= ((rows[r] >> j) & 1u) << r;
-            for (int q = 0; q < 16; ++q)
-                for (int v = 0; v < 16; ++v) {
-                    uint64_t e = 0;
-                    for (int b = 0; b < 4; ++b)
-                        if ((v >> b) & 1)
-                            e ^= col[4 * q + b];
-                    sp[(16 * q + v) * 64 + m] = e;
-                }
-        }
+        spread_table(S, spread + (size_t)kSpreadTable * i);
         // A lane that just emitted its S values of a tile is C - S = 63 S
         // values short of its start in the next tile. M = T^(63 S) is
         // stored as 16 tables of 16 entries: entry v of table q is
@@ -202,6 +226,8 @@ void free_slot(BatchSlot &s)
         RNGX_NOTE(hipHostFree(s.staging));
     if (s.devtab)
         RNGX_NOTE(hipFree(s.devtab));
+    if (s.anchors)
+        RNGX_NOTE(hipFree(s.anchors));
     if (s.done)
         RNGX_NOTE(hipEventDestroy(s.done));
     if (s.cap_stream)
@@ -217,9 +243,9 @@ std::mutex &tables_mu()
 
 } // namespace
 
-int batch_tables_locked(const uint64_t **pow2, const uint64_t **spread_all, int *n_cus,
+int batch_tables_locked(const uint64_t **jump, const uint64_t **spread_all, int *n_cus,
                         const uint64_t **carry_nib_all, const uint64_t **group_nib_all,
-                        int *clock_khz)
+                        int *clock_khz, const uint64_t **sweep)
 {
     // Own lock: the server thread reaches here without the batch API lock.
     std::lock_guard<std::mutex> lk(tables_mu());
@@ -233,10 +259,10 @@ int batch_tables_locked(const uint64_t **pow2, const uint64_t **spread_all, int 
     if (!t.loaded) {
         // Device addresses of this device's copies of the static tables
         // (the arrays' names are host-side stand-ins), then their contents.
-        build_host_tables(g_spread_host, g_carry_host, g_group_host);
-        void *p2 = nullptr, *ps = nullptr, *pc = nullptr, *pg = nullptr;
+        build_host_tables(g_jump_host, g_spread_host, g_sweep_host, g_carry_host, g_group_host);
+        void *p2 = nullptr, *ps = nullptr, *pc = nullptr, *pg = nullptr, *pw = nullptr;
         int cus = 0, khz = 0;
-        hipError_t e = hipGetSymbolAddress(&p2, HIP_SYMBOL(g_pow2));
+        hipError_t e = hipGetSymbolAddress(&p2, HIP_SYMBOL(g_jump));
         if (e == hipSuccess)
             e = hipGetSymbolAddress(&ps, HIP_SYMBOL(g_spread));
         if (e == hipSuccess)
@@ -244,7 +270,11 @@ int batch_tables_locked(const uint64_t **pow2, const uint64_t **spread_all, int 
         if (e == hipSuccess)
             e = hipGetSymbolAddress(&pg, HIP_SYMBOL(g_group_nib));
         if (e == hipSuccess)
-            e = hipMemcpy(p2, jump_tables(), sizeof g_pow2, hipMemcpyHostToDevice);
+            e = hipGetSymbolAddress(&pw, HIP_SYMBOL(g_sweep));
+        if (e == hipSuccess)
+            e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess)
+            e = hipMemcpy(p2, g_jump_host, sizeof g_jump, hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = hipMemcpy(ps, g_spread_host, sizeof g_spread, hipMemcpyHostToDevice);
         if (e == hipSuccess)
@@ -252,21 +282,22 @@ int batch_tables_locked(const uint64_t **pow2, const uint64_t **spread_all, int 
         if (e == hipSuccess)
             e = hipMemcpy(pg, g_group_host, sizeof g_group_nib, hipMemcpyHostToDevice);
         if (e == hipSuccess)
-            e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+            e = hipMemcpy(pw, g_sweep_host, sizeof g_sweep, hipMemcpyHostToDevice);
         if (e == hipSuccess)
             e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev);
         if (e != hipSuccess)
             return hip_fail(e, "batch: device tables");
-        t.d_pow2 = static_cast<const uint64_t *>(p2);
+        t.d_jump = static_cast<const uint64_t *>(p2);
         t.d_spread = static_cast<const uint64_t *>(ps);
         t.d_carry_nib = static_cast<const uint64_t *>(pc);
         t.d_group_nib = static_cast<const uint64_t *>(pg);
+        t.d_sweep = static_cast<const uint64_t *>(pw);
         t.clock_khz = khz > 0 ? khz : 100000;
         t.n_cus = cus;
         t.loaded = true;
     }
-    if (pow2)
-        *pow2 = t.d_pow2;
+    if (jump)
+        *jump = t.d_jump;
     if (spread_all)
         *spread_all = t.d_spread;
     if (carry_nib_all)
@@ -275,15 +306,45 @@ int batch_tables_locked(const uint64_t **pow2, const uint64_t **spread_all, int 
         *group_nib_all = t.d_group_nib;
     if (clock_khz)
         *clock_khz = t.clock_khz;
+    if (sweep)
+        *sweep = t.d_sweep;
     if (n_cus)
         *n_cus = t.n_cus;
     return RNGX_OK;
 }
 
+// The default configuration's values, whatever its graph flag and the fields
+// the grouped order ignores.
+static bool library_order(const rngx_batch_cfg &c)
+{
+    return c.values_per_lane == 16 && c.waves_per_block == 4 && c.row_values == 16 &&
+           !c.per_item && c.group == 32 && c.group_steps == 8 && c.pace_gbs == 6250;
+}
+
+// One wave per 1,024-value item up to 512 MiB, the sweep order above: a
+// smaller batch has too few steps for its first kernel, its tables and its
+// schedule's start to pay (us per call, item order / sweep: 62 MB in 256
+// requests 24 / 34, 215 MB in 64 43 / 50, 380 MB in 1,024 76 / 82, 797 MB in
+// 256 156 / 139, 2.4 GB in 512 415 / 368; the grouped order 66 / 68 / 114 /
+// 168 / 425 in this sequence). Requests shorter than an anchor's 8,192 values
+// cost both the same (850 MB in 100,000: 675 / 650, in both mostly staging).
+rngx_batch_cfg batch_order(const rngx_batch_cfg &c, uint64_t values, bool anchors)
+{
+    if (!library_order(c))
+        return c;
+    if (values <= kItemOrderValues)
+        return rngx_batch_cfg{16, 4, 0, kUploadKernel, 16, 1, 1, 0, 0, 0};
+    if (!anchors)
+        return c;
+    return rngx_batch_cfg{8, 4, 0, kUploadKernel, 8, 0, 0, kSweepOrder, 1, 7000};
+}
+
 int resolve_batch_cfg(const rngx_batch_cfg &c, int n_cus, rngx_batch_cfg *out)
 {
     rngx_batch_cfg r = c;
-    if (r.group) {
+    if (r.group == kSweepOrder) {
+        r.blocks = (uint32_t)std::max(1, n_cus); // one block per compute unit
+    } else if (r.group) {
         // Every block that fits at once, rounded down to whole groups.
         int occ = 0;
         const hipError_t e = batch_group_occupancy(r, &occ);
@@ -299,15 +360,20 @@ int resolve_batch_cfg(const rngx_batch_cfg &c, int n_cus, rngx_batch_cfg *out)
     return RNGX_OK;
 }
 
-void fill_batch_tables(BatchTables &t, const rngx_batch_cfg &cfg, const uint64_t *pow2,
+void fill_batch_tables(BatchTables &t, const rngx_batch_cfg &cfg, const uint64_t *jump,
                        const uint64_t *spread_all, const uint64_t *nib_all,
-                       const uint64_t *group_all, int clock_khz)
+                       const uint64_t *group_all, const uint64_t *sweep, int clock_khz)
 {
     const int si = batch_s_index(cfg.values_per_lane);
-    t.pow2 = pow2;
+    t.jump = jump;
     t.spread = spread_all + (size_t)kSpreadTable * si;
     t.carry_nib = nib_all + (size_t)kCarryTable * si;
-    t.group_nib = cfg.group ? group_all + ((size_t)si * kNumGroups +
+    t.sweep = sweep;
+    t.anchor_spread = sweep + kSweepTable + 16 * 64;
+    t.anchors = nullptr;
+    t.v_end = 0;
+    t.group_nib = cfg.group && cfg.group != kSweepOrder
+                            ? group_all + ((size_t)si * kNumGroups +
                                            batch_group_index(cfg.group)) * kCarryTable
                             : nullptr;
     t.clock_khz = (uint32_t)clock_khz;
@@ -342,10 +408,19 @@ int batch_stage_items(BatchSlot &slot, const StageReq *items, uint32_t k,
         slot.staging = slot.devtab = nullptr;
         slot.capacity = 0;
         const size_t bytes = kReqOffset + (size_t)cap * sizeof(BatchReq);
-        hipError_t e = hipHostMalloc(&slot.staging, bytes, hipHostMallocDefault);
+        // Coherent: the upload kernel reads it anew each time, never from a
+        // device cache that holds the slot's previous table.
+        hipError_t e =
+            hipHostMalloc(&slot.staging, bytes, hipHostMallocMapped | hipHostMallocCoherent);
         if (e != hipSuccess) {
             slot.staging = nullptr;
             return hip_fail(e, "hipHostMalloc (batch staging)");
+        }
+        e = hipHostGetDevicePointer(&slot.mapped, slot.staging, 0);
+        if (e != hipSuccess) {
+            RNGX_NOTE(hipHostFree(slot.staging));
+            slot.staging = slot.mapped = nullptr;
+            return hip_fail(e, "hipHostGetDevicePointer (batch staging)");
         }
         e = hipMalloc(&slot.devtab, bytes);
         if (e != hipSuccess) {
@@ -377,6 +452,7 @@ int batch_stage_items(BatchSlot &slot, const StageReq *items, uint32_t k,
     desc->m = k;
     slot.m_staged = k;
     slot.n_items = n_items;
+    slot.v_end = k ? items[k - 1].vbase + items[k - 1].length : 0;
     return RNGX_OK;
 }
 
@@ -420,11 +496,13 @@ static uint64_t line_skew(const uint64_t *out)
 }
 
 int batch_stage(BatchSlot &slot, const rngx_req *reqs, uint32_t m, uint64_t *out,
-                uint64_t out_cap, uint32_t values_per_lane, uint64_t *total_out)
+                uint64_t out_cap, const rngx_batch_cfg &cfg, bool as_given, rngx_batch_cfg *run,
+                uint64_t *total_out)
 {
     int rc = batch_validate(reqs, m, out, out_cap, total_out);
     if (rc || *total_out == 0)
         return rc;
+    *run = as_given ? cfg : batch_order(cfg, *total_out, true);
     // Packed layout: the virtual index of a value is its output index plus
     // the skew of `out` in its 128-byte line, so tile rows fall on whole
     // lines of the output.
@@ -446,16 +524,38 @@ int batch_stage(BatchSlot &slot, const rngx_req *reqs, uint32_t m, uint64_t *out
         }
         base += len;
     }
-    return batch_stage_items(slot, items.data(), (uint32_t)items.size(), values_per_lane,
-                             nullptr);
+    return batch_stage_items(slot, items.data(), (uint32_t)items.size(),
+                             run->values_per_lane, nullptr);
+}
+
+// The slot's anchors, grown to the staged batch; null (the sweep order then
+// searches and jumps for every tile) when there is no memory for them.
+static SweepAnchor *slot_anchors(BatchSlot &slot)
+{
+    const uint64_t need = (slot.v_end + kAnchorValues - 1) / kAnchorValues;
+    if (need > slot.n_anchors) {
+        if (slot.anchors)
+            RNGX_NOTE(hipFree(slot.anchors));
+        slot.anchors = nullptr;
+        slot.n_anchors = 0;
+        void *p = nullptr;
+        if (hipMalloc(&p, need * sizeof(SweepAnchor)) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        slot.anchors = static_cast<SweepAnchor *>(p);
+        slot.n_anchors = need;
+    }
+    return slot.anchors;
 }
 
 int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipStream_t stream,
                  bool fit_grid, const char *prof_name)
 {
-    const uint64_t *pow2 = nullptr, *spread_all = nullptr, *nib_all = nullptr, *group_all = nullptr;
+    const uint64_t *jump = nullptr, *spread_all = nullptr, *nib_all = nullptr, *group_all = nullptr,
+                   *sweep = nullptr;
     int n_cus = 0, clock_khz = 0;
-    int rc = batch_tables_locked(&pow2, &spread_all, &n_cus, &nib_all, &group_all, &clock_khz);
+    int rc = batch_tables_locked(&jump, &spread_all, &n_cus, &nib_all, &group_all, &clock_khz, &sweep);
     if (rc)
         return rc;
     rngx_batch_cfg cfg;
@@ -475,10 +575,13 @@ int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipSt
             cfg.blocks = (uint32_t)std::max<uint64_t>(1, need);
     }
     BatchTables tabs;
-    fill_batch_tables(tabs, cfg, pow2, spread_all, nib_all, group_all, clock_khz);
+    fill_batch_tables(tabs, cfg, jump, spread_all, nib_all, group_all, sweep, clock_khz);
+    if (cfg.group == kSweepOrder)
+        tabs.anchors = slot_anchors(slot);
+    tabs.v_end = slot.v_end;
     const BatchDesc *ddesc = static_cast<const BatchDesc *>(slot.devtab);
     const int tok = prof::begin(prof_name, stream);
-    if (cfg.use_graph) {
+    if (cfg.use_graph == 1) {
         const bool same = slot.exec && slot.exec_cfg.values_per_lane == cfg.values_per_lane &&
                           slot.exec_cfg.waves_per_block == cfg.waves_per_block &&
                           slot.exec_cfg.blocks == cfg.blocks &&
@@ -537,8 +640,12 @@ int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipSt
             return hip_fail(e, "batch kernel launch");
     } else {
         const size_t bytes = kReqOffset + (size_t)slot.m_staged * sizeof(BatchReq);
-        RNGX_HIP(hipMemcpyAsync(slot.devtab, slot.staging, bytes, hipMemcpyHostToDevice, stream));
         take_stray_error("before the batch kernel launch");
+        if (cfg.use_graph == kUploadKernel)
+            RNGX_HIP(launch_batch_upload(slot.mapped, slot.devtab, bytes, stream));
+        else
+            RNGX_HIP(hipMemcpyAsync(slot.devtab, slot.staging, bytes, hipMemcpyHostToDevice,
+                                    stream));
         hipError_t e = launch_batch(cfg, ddesc, tabs, star, stream);
         if (e != hipSuccess)
             return hip_fail(e, "batch kernel launch");
@@ -554,7 +661,8 @@ void release_batch()
 {
     BatchGlobals &g = G();
     std::lock_guard<std::mutex> lk(g.mu);
-    free_slot(g.api_slot);
+    for (BatchSlot &slot : g.api_slot)
+        free_slot(slot);
     std::lock_guard<std::mutex> lt(tables_mu());
     int cur = -1;
     RNGX_NOTE(hipGetDevice(&cur));
@@ -581,6 +689,25 @@ int noalloc_scratch_locked(BatchGlobals &g, int dev, unsigned char **ptr)
     }
     *ptr = g.scratch_ptr[dev];
     return RNGX_OK;
+}
+
+// A slot whose last batch has finished, with room for m requests if there is
+// one (a program that waits for each batch stays on one slot); the slots in
+// turn when all are busy.
+BatchSlot *free_api_slot(BatchGlobals &g, uint32_t m)
+{
+    BatchSlot *idle = nullptr;
+    for (BatchSlot &slot : g.api_slot) {
+        if (slot.done && hipEventQuery(slot.done) != hipSuccess) {
+            (void)hipGetLastError(); // not ready
+            continue;
+        }
+        if (slot.capacity >= m)
+            return &slot;
+        if (!idle || slot.capacity > idle->capacity)
+            idle = &slot;
+    }
+    return idle ? idle : &g.api_slot[g.next_slot++ % kApiSlots];
 }
 
 rngx_batch_cfg current_batch_cfg()
@@ -633,14 +760,23 @@ extern "C" int rngx_generate_batch(const rngx_req *reqs, uint32_t m, uint64_t *o
     BatchGlobals &g = G();
     std::lock_guard<std::mutex> lk(g.mu);
     clear_error();
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    // A stream that is being captured takes the configuration as it stands, a
+    // graph launch: the library's own launches would enter the capture with a
+    // table that later calls rewrite.
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s && hipStreamIsCapturing(s, &st) != hipSuccess)
+        (void)hipGetLastError();
+    const bool as_given = st != hipStreamCaptureStatusNone || !library_order(g.cfg);
+    BatchSlot *slot = as_given ? &g.api_slot[0] : free_api_slot(g, m);
     uint64_t total = 0;
-    int rc = batch_stage(g.api_slot, reqs, m, out, out_cap, g.cfg.values_per_lane, &total);
+    rngx_batch_cfg run;
+    int rc = batch_stage(*slot, reqs, m, out, out_cap, g.cfg, as_given, &run, &total);
     if (rc)
         return rc;
     if (total == 0)
         return RNGX_OK;
-    return batch_launch(g.api_slot, g.cfg, current_scrambler() == RNGX_SCRAMBLE_STAR,
-                        static_cast<hipStream_t>(stream));
+    return batch_launch(*slot, run, current_scrambler() == RNGX_SCRAMBLE_STAR, s);
 }
 
 extern "C" int rngx_generate_batch_noalloc(const rngx_req *reqs, uint32_t m, uint64_t *out,
@@ -668,13 +804,14 @@ extern "C" int rngx_generate_batch_noalloc(const rngx_req *reqs, uint32_t m, uin
         return rc;
     // The jump tables are static device arrays too; the device's first
     // batched call of any kind fills them.
-    const uint64_t *pow2 = nullptr, *spread_all = nullptr, *nib_all = nullptr, *group_all = nullptr;
+    const uint64_t *jump = nullptr, *spread_all = nullptr, *nib_all = nullptr, *group_all = nullptr,
+                   *sweep = nullptr;
     int n_cus = 0, clock_khz = 0;
-    rc = batch_tables_locked(&pow2, &spread_all, &n_cus, &nib_all, &group_all, &clock_khz);
+    rc = batch_tables_locked(&jump, &spread_all, &n_cus, &nib_all, &group_all, &clock_khz, &sweep);
     if (rc)
         return rc;
     rngx_batch_cfg cfg;
-    if ((rc = resolve_batch_cfg(g.cfg, n_cus, &cfg)))
+    if ((rc = resolve_batch_cfg(batch_order(g.cfg, total, false), n_cus, &cfg)))
         return rc;
     const uint64_t C = 64ull * cfg.values_per_lane;
 
@@ -710,7 +847,8 @@ extern "C" int rngx_generate_batch_noalloc(const rngx_req *reqs, uint32_t m, uin
         cfg.blocks = (uint32_t)std::max<uint64_t>(1, need);
     }
     BatchTables tabs;
-    fill_batch_tables(tabs, cfg, pow2, spread_all, nib_all, group_all, clock_khz);
+    fill_batch_tables(tabs, cfg, jump, spread_all, nib_all, group_all, sweep, clock_khz);
+    tabs.v_end = skew + total;
     const bool star = current_scrambler() == RNGX_SCRAMBLE_STAR;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (cfg.per_item && k <= kSmallReqs) {
@@ -802,6 +940,7 @@ extern "C" int rngx_autotune_batch(const rngx_req *reqs, uint32_t m, uint64_t *o
         }
     } guard{e0, e1};
 
+    BatchSlot &slot = g.api_slot[0];
     uint64_t ref_sum = 0, total = 0;
     bool have_ref = false;
     double best = 1e300;
@@ -813,12 +952,13 @@ extern "C" int rngx_autotune_batch(const rngx_req *reqs, uint32_t m, uint64_t *o
     // candidate: it is a configuration of its own (rngx_set_batch_cfg) and
     // the server's schedule for small batches.
     auto try_cfg = [&](const rngx_batch_cfg &c) -> int {
-        int rc2 = batch_stage(g.api_slot, reqs, m, out, out_cap, c.values_per_lane, &total);
+        rngx_batch_cfg run;
+        int rc2 = batch_stage(slot, reqs, m, out, out_cap, c, false, &run, &total);
         if (rc2)
             return rc2;
         if (total == 0)
             return set_error(RNGX_E_INVAL, "rngx_autotune_batch: no values requested");
-        rc2 = batch_launch(g.api_slot, c, star, s); // warm-up (and graph capture)
+        rc2 = batch_launch(slot, run, star, s); // warm-up (and graph capture)
         if (rc2)
             return rc2;
         uint64_t sum = 0;
@@ -837,7 +977,7 @@ extern "C" int rngx_autotune_batch(const rngx_req *reqs, uint32_t m, uint64_t *o
         }
         RNGX_HIP(hipEventRecord(e0, s));
         for (uint32_t r = 0; r < reps; ++r) {
-            rc2 = batch_launch(g.api_slot, c, star, s);
+            rc2 = batch_launch(slot, run, star, s);
             if (rc2)
                 return rc2;
         }
@@ -930,13 +1070,14 @@ extern "C" int rngx_autotune_batch(const rngx_req *reqs, uint32_t m, uint64_t *o
         if (fastest[k] < 0)
             continue;
         const rngx_batch_cfg c = result->tried[fastest[k]].cfg;
-        if ((rc = batch_stage(g.api_slot, reqs, m, out, out_cap, c.values_per_lane, &total)))
+        rngx_batch_cfg run;
+        if ((rc = batch_stage(slot, reqs, m, out, out_cap, c, false, &run, &total)))
             return rc;
-        if ((rc = batch_launch(g.api_slot, c, star, s))) // warm-up (and graph capture)
+        if ((rc = batch_launch(slot, run, star, s))) // warm-up (and graph capture)
             return rc;
         RNGX_HIP(hipEventRecord(e0, s));
         for (uint32_t r = 0; r < 3 * reps; ++r)
-            if ((rc = batch_launch(g.api_slot, c, star, s)))
+            if ((rc = batch_launch(slot, run, star, s)))
                 return rc;
         RNGX_HIP(hipEventRecord(e1, s));
         RNGX_HIP(hipEventSynchronize(e1));

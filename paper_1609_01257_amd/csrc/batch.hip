@@ -14,9 +14,10 @@
 //
 // Per item, lane l produces the S values of the tile's l-th sub-range. Its
 // starting state comes from GF(2) jump-ahead. The wave first jumps from the
-// stream's initial state to the tile's first position with the T^(2^b)
-// tables, all lanes at once: lane r holds row r of a jump matrix M and M x
-// is one AND, two popcounts and a ballot (x is uniform across the wave).
+// stream's initial state to the tile's first position with one matrix
+// T^(a 16^i) per hexadecimal digit of the distance, all lanes at once: lane r
+// holds row r of a jump matrix M and M x is one AND, two popcounts and a
+// ballot (x is uniform across the wave).
 // Each lane m then places itself m S values further with a lane-spread
 // table: T^(m S) z is the XOR of 16 entries, one per nibble of the uniform
 // z, and the 64 lanes read 64 consecutive entries (one coalesced load per
@@ -25,7 +26,11 @@
 // with 16-byte stores, 8 lanes per line, so every store instruction covers
 // whole lines. LDS and cross-lane operations appear only for this
 // bookkeeping.
+//
+// The sweep order (batch_sweep_kernel) takes tiles of the whole batch instead
+// of items, in one window that moves through the output on a schedule.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cstring>
 #include <vector>
@@ -63,15 +68,24 @@ __device__ __forceinline__ uint64_t wave_matvec(uint64_t row, uint64_t x)
     return __ballot((pc & 1u) != 0u);
 }
 
-// T^k x for a wave-uniform k and x, with pow2 = 64 matrices of 64 rows.
-// (Loading several factors' rows ahead of use measured slower.)
-__device__ __forceinline__ uint64_t wave_jump(const uint64_t *__restrict__ pow2, uint32_t lane,
+// T^k x for a wave-uniform k and x, with jump = the matrices T^(a 16^i) of
+// every hexadecimal digit a of k at position i (64 rows each; a = 0 is the
+// identity). What bounds it is the latency of the row loads, which do not
+// depend on x, so eight digits' rows are loaded at once: most jumps wait for
+// memory once, where one factor T^(2^b) after the other waited for each set
+// bit of k (about 12 in a 2^24-value request).
+__device__ __forceinline__ uint64_t wave_jump(const uint64_t *__restrict__ jump, uint32_t lane,
                                               uint64_t x, uint64_t k)
 {
-    while (k) {
-        const int b = __builtin_ctzll(k);
-        x = wave_matvec(pow2[64 * b + lane], x);
-        k &= k - 1;
+#pragma nounroll
+    for (; k; k >>= 32, jump += 8 * 16 * 64) {
+        uint64_t row[8];
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i)
+            row[i] = jump[(16 * i + (uint32_t)((k >> (4 * i)) & 15u)) * 64 + lane];
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i)
+            x = wave_matvec(row[i], x);
     }
     return x;
 }
@@ -193,7 +207,7 @@ template <int S, int R, bool STAR, bool NT = false>
 __device__ __forceinline__ bool process_item(const ItemReq &r, uint64_t item, bool carry,
                                              uint64_t &x, uint64_t *lds,
                                              const uint64_t *carry_tab,
-                                             const uint64_t *__restrict__ pow2,
+                                             const uint64_t *__restrict__ jump,
                                              const uint64_t *__restrict__ spread,
                                              g_cu64 *__restrict__ states, uint32_t lane)
 {
@@ -218,7 +232,7 @@ __device__ __forceinline__ bool process_item(const ItemReq &r, uint64_t item, bo
         mix.mix_high = r.mix_high;
         mix.zero_fix = r.zero_fix;
         const uint64_t x0 = states ? states[r.gid] : init_state(mix, r.gid);
-        const uint64_t xq0 = wave_jump(pow2, lane, x0, r.offset + (q0 - B));
+        const uint64_t xq0 = wave_jump(jump, lane, x0, r.offset + (q0 - B));
         // Lanes from b on start at T0 + l S = (T0 + b S) + (l - b) S: with
         // z the state at T0 + b S, lane l takes T^((l - b) S) z from the
         // spread table. If the request starts inside lane l0's range, that
@@ -232,7 +246,7 @@ __device__ __forceinline__ bool process_item(const ItemReq &r, uint64_t item, bo
             if (rem != 0) {
                 l0 = b++;
                 if (b < 64)
-                    z = wave_jump(pow2, lane, xq0, (uint64_t)S - rem);
+                    z = wave_jump(jump, lane, xq0, (uint64_t)S - rem);
             }
         }
         x = 0;
@@ -320,7 +334,7 @@ __device__ __forceinline__ bool process_item(const ItemReq &r, uint64_t item, bo
 
 template <int S, int R, bool STAR>
 __global__ __launch_bounds__(256) void batch_kernel(const BatchDesc *__restrict__ desc,
-                                                    const uint64_t *__restrict__ pow2,
+                                                    const uint64_t *__restrict__ jump,
                                                     const uint64_t *__restrict__ spread,
                                                     const uint64_t *__restrict__ carry_nib,
                                                     uint32_t run_items, uint32_t per_item)
@@ -391,7 +405,7 @@ __global__ __launch_bounds__(256) void batch_kernel(const BatchDesc *__restrict_
             req_end = uniform64(lo + 1 < m ? (uint64_t)reqs[lo + 1].item_begin : n_items);
         }
         const ItemReq r = load_req(reqs, lo);
-        const bool full = process_item<S, R, STAR>(r, item, carry, x, lds, carry_tab, pow2,
+        const bool full = process_item<S, R, STAR>(r, item, carry, x, lds, carry_tab, jump,
                                                    spread, states, lane);
         // Lane l now holds the state at T0 + l*S + S when the tile was full.
         // Every quantity of this loop is the same in all lanes; saying so
@@ -471,7 +485,7 @@ __device__ __forceinline__ void wait_clock(uint64_t due)
 // time + k * delta256 / 256 clock ticks.
 template <int S, int R, bool STAR>
 __global__ __launch_bounds__(256) void batch_group_kernel(const BatchDesc *__restrict__ desc,
-                                                          const uint64_t *__restrict__ pow2,
+                                                          const uint64_t *__restrict__ jump,
                                                           const uint64_t *__restrict__ spread,
                                                           const uint64_t *__restrict__ group_nib,
                                                           uint32_t group, uint32_t steps,
@@ -526,7 +540,7 @@ __global__ __launch_bounds__(256) void batch_group_kernel(const BatchDesc *__res
                 continue;
             }
             if (!carry) {
-                lo = __builtin_amdgcn_readfirstlane(bisect_request(reqs, m, item));
+                lo = find_request(reqs, m, item, lane);
                 req_end = uniform64(lo + 1 < m ? (uint64_t)reqs[lo + 1].item_begin : n_items);
             }
             const ItemReq r = load_req(reqs, lo);
@@ -534,7 +548,7 @@ __global__ __launch_bounds__(256) void batch_group_kernel(const BatchDesc *__res
             cur_E = uniform64(r.vbase + r.length);
             cur_obase = uniform64(reinterpret_cast<uintptr_t>(r.dst) - r.vbase * sizeof(uint64_t));
             const bool full = process_item<S, R, STAR, true>(r, item, carry, x, lds, stride_tab,
-                                                             pow2, spread, states, lane);
+                                                             jump, spread, states, lane);
             // Lane l holds the state at T0 + l*S + S when the tile was full;
             // the wave's next item is `group` tiles on if it is still in
             // this request.
@@ -544,11 +558,252 @@ __global__ __launch_bounds__(256) void batch_group_kernel(const BatchDesc *__res
     }
 }
 
+// The sweep order: what the library runs for a large batch when the
+// configuration leaves the order to it (batch_order). All wavefronts of the
+// grid take consecutive 4 KiB tiles (512 values, 8 per lane) of the virtual
+// index space, then all move on by the grid's width, on a clock schedule: the
+// grid writes one dense window that moves through the output as a fill does.
+// (Store-only, 4 KiB pieces in this order hold any schedule up to 7.2 TB/s; 8
+// KiB pieces fall off above 6.5, groups of 32 wavefronts in regions of their
+// own above 6.3.)
+//
+// Keeping to the schedule leaves no room for a vector load: its wait is also
+// a wait for the wavefront's earlier stores, several microseconds at this
+// rate, against 2.4 for a step. So what a tile needs is found beforehand: a
+// first kernel gives every group of 16 tiles that lies inside one request an
+// anchor, the state at its first position and its output address. Per tile
+// the sweep reads one anchor (a scalar load, one step ahead), moves the state
+// to the tile with one matrix-vector product, spreads it over the lanes with
+// one look-up per 3 bits in a table of 22 x 8 x 64 entries (88 KiB) that stays
+// in LDS, and passes 8 values per lane through LDS to whole-line stores, in
+// chunks whose places are permuted so that neither side meets in a bank. 16
+// wavefronts per compute unit share the table: one block.
+//
+// Tiles of a group that requests share are found by search and jump, as the
+// other orders do.
+//
+// Measured, 4,096 streams of 2^10 ... 2^24 values, 56 GB: 6.92 TB/s at a
+// schedule of 7,000 GB/s (6.19 in the grouped order; 5.4 at 7,250, past what
+// it holds); 256 streams of 2^24: 6.93, and 7.12 at 7,250. Everything but the
+// stores runs at 15 TB/s. Jumping for every tile, without anchors: 5.5 at
+// 6,500. Letting a late wavefront move its schedule on instead of catching
+// up: 5.1.
+constexpr uint32_t kSweepWaves = 16;
+constexpr uint32_t kSweepS = 8;
+constexpr uint32_t kSweepC = 64 * kSweepS;
+constexpr uint32_t kAnchorTiles = 16;
+static_assert(kSweepC * kAnchorTiles == kAnchorValues, "anchor spacing");
+typedef __attribute__((address_space(4))) const SweepAnchor g_anchor;
+
+// The last request whose first virtual index is at most P (request 0 if none).
+__device__ __forceinline__ uint32_t find_vbase(g_req *__restrict__ reqs, uint32_t m, uint64_t P,
+                                               uint32_t lane)
+{
+    uint32_t lo = 0, n = m;
+    while (n > 1) {
+        const uint32_t step = (n + 63) / 64;
+        const uint32_t off = lane * step;
+        const bool le = lane == 0 || (off < n && reqs[lo + off].vbase <= P);
+        const uint32_t k = 63 - __builtin_clzll(__ballot(le));
+        lo += k * step;
+        n = (n - k * step) < step ? (n - k * step) : step;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// State at value number offset + d of request r's stream (d < 0 for positions
+// before the request), modulo the order 2^64 - 1 of the step.
+__device__ __forceinline__ uint64_t request_state(const ItemReq &r, int64_t d,
+                                                  g_cu64 *__restrict__ states,
+                                                  const uint64_t *__restrict__ jump, uint32_t lane)
+{
+    SeedMix mix;
+    mix.mix_low = r.mix_low;
+    mix.mix_high = r.mix_high;
+    mix.zero_fix = r.zero_fix;
+    const uint64_t x0 = uniform64(states ? states[r.gid] : init_state(mix, r.gid));
+    const uint64_t k = r.offset + (uint64_t)d - (d < 0 && r.offset < (uint64_t)-d ? 1u : 0u);
+    return wave_jump(jump, lane, x0, k);
+}
+
+// One anchor per lane, per_wave (at most 64) consecutive groups per wavefront:
+// the groups of one request are spread from the first of them, as lanes are
+// from a tile's start, one request after the other.
+__global__ __launch_bounds__(256) void batch_anchor_kernel(const BatchDesc *__restrict__ desc,
+                                                           const uint64_t *__restrict__ jump,
+                                                           const uint64_t *__restrict__ spread,
+                                                           SweepAnchor *__restrict__ anchors,
+                                                           uint64_t n_groups, uint32_t per_wave)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint64_t wave = (uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const uint64_t g0 = uniform64(wave * per_wave);
+    if (g0 >= n_groups)
+        return;
+    const uint32_t m = desc->m;
+    g_req *__restrict__ reqs = (g_req *)desc->reqs;
+    g_cu64 *__restrict__ states = (g_cu64 *)desc->states;
+    const uint64_t P = (g0 + lane) * kAnchorValues;
+    const uint32_t j0 = find_vbase(reqs, m, g0 * kAnchorValues, lane);
+    const uint32_t j1 = find_vbase(reqs, m, (g0 + per_wave - 1) * kAnchorValues, lane);
+    uint32_t j = j0, hi = j1 + 1;
+    while (__ballot(hi - j > 1)) { // per lane: the last request from j on with vbase <= P
+        const uint32_t mid = (j + hi) >> 1;
+        if (hi - j > 1) {
+            if (reqs[mid].vbase <= P)
+                j = mid;
+            else
+                hi = mid;
+        }
+    }
+    SweepAnchor a = {0, nullptr};
+    const bool inside = lane < per_wave && reqs[j].vbase <= P && P - reqs[j].vbase < reqs[j].length &&
+                        reqs[j].length - (P - reqs[j].vbase) >= kAnchorValues;
+    for (uint64_t todo = __ballot(inside); todo;) {
+        const uint32_t l0 = __builtin_ctzll(todo);
+        const uint32_t jj = __builtin_amdgcn_readlane(j, l0);
+        const bool mine = inside && j == jj;
+        const ItemReq r = load_req(reqs, jj);
+        const uint64_t d0 = (g0 + l0) * kAnchorValues - r.vbase;
+        const uint64_t z = request_state(r, (int64_t)d0, states, jump, lane);
+        if (mine) {
+            const uint64_t *__restrict__ col = spread + (lane - l0);
+            uint64_t x = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < 16; ++q)
+                x ^= col[(16u * q + (uint32_t)((z >> (4 * q)) & 15u)) * 64u];
+            a.state = x;
+            a.dst = r.dst + (P - r.vbase);
+        }
+        todo &= ~__ballot(mine);
+    }
+    if (lane < per_wave && g0 + lane < n_groups)
+        anchors[g0 + lane] = a;
+}
+
+template <bool STAR>
+__global__ __launch_bounds__(1024) void batch_sweep_kernel(const BatchDesc *__restrict__ desc,
+                                                           const uint64_t *__restrict__ jump,
+                                                           const uint64_t *__restrict__ sweep,
+                                                           const SweepAnchor *__restrict__ anchor_,
+                                                           uint64_t n_tiles, uint64_t delta256)
+{
+    extern __shared__ __align__(16) uint64_t lds_dyn[];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    u64x2 *stage = reinterpret_cast<u64x2 *>(lds_dyn + kSweepTable) + wid * (kSweepC / 2);
+    for (uint32_t i = threadIdx.x; i < (uint32_t)kSweepTable / 2; i += blockDim.x)
+        reinterpret_cast<u64x2 *>(lds_dyn)[i] = reinterpret_cast<const u64x2 *>(sweep)[i];
+    // Four neighbouring tiles per block in each quarter of the window; a
+    // wavefront's tiles all have the same place in their groups (the grid's
+    // width is a multiple of a group).
+    const uint32_t waves = gridDim.x * kSweepWaves;
+    const uint32_t place = (wid >> 2) * (gridDim.x * 4) + blockIdx.x * 4 + (wid & 3u);
+    const uint32_t sub = place % kAnchorTiles;
+    const uint64_t sub_row = sweep[kSweepTable + 64 * sub + lane]; // T^(512 sub)
+    __syncthreads();
+    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+
+    const uint32_t m = desc->m;
+    g_req *__restrict__ reqs = (g_req *)desc->reqs;
+    g_cu64 *__restrict__ states = (g_cu64 *)desc->states;
+    g_anchor *__restrict__ anchors = (g_anchor *)anchor_;
+
+    // The tile's values, 8 per lane from the state z at its start, as the 16
+    // bytes each lane stores in each of 4 store instructions.
+    const auto values = [&](uint64_t z, u64x2(&v)[4]) {
+        uint64_t x = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 22; ++q)
+            x ^= lds_dyn[(8 * q + (uint32_t)((z >> (3 * q)) & 7u)) * 64 + lane];
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c) {
+            u64x2 w;
+            w.x = out_word<STAR>(x);
+            x = xs_step(x);
+            w.y = out_word<STAR>(x);
+            x = xs_step(x);
+            stage[4 * lane + (c ^ ((lane >> 1) & 3u))] = w;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            const uint32_t row = 16 * i + (lane >> 2); // the lane that made these two values
+            v[i] = stage[4 * row + ((lane & 3u) ^ ((row >> 1) & 3u))];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+
+    if (place >= n_tiles)
+        return;
+    uint64_t sched = 0;
+    uint64_t z = 0, dst = 0;
+    if (anchors) {
+        z = anchors[place / kAnchorTiles].state;
+        dst = reinterpret_cast<uintptr_t>(anchors[place / kAnchorTiles].dst);
+    }
+    for (uint64_t tile = place; tile < n_tiles; tile += waves) {
+        u64x2 v[4];
+        const uint64_t here = dst;
+        if (here) {
+            values(wave_matvec(sub_row, z), v);
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                asm volatile("" : "+v"(v[i])); // the values stand before the wait
+        }
+        if (anchors && tile + waves < n_tiles) {
+            z = anchors[(tile + waves) / kAnchorTiles].state;
+            dst = reinterpret_cast<uintptr_t>(anchors[(tile + waves) / kAnchorTiles].dst);
+        }
+        if (delta256) {
+            wait_clock(t0 + (sched >> 8));
+            sched += delta256;
+        }
+        if (here) {
+            g_u64 *__restrict__ o = reinterpret_cast<g_u64 *>(here) + sub * kSweepC;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i)
+                __builtin_nontemporal_store(v[i], (g_u64x2 *)(o + 2 * (64 * i + lane)));
+            continue;
+        }
+        // A tile of a shared group: every request that has values in it.
+        const uint64_t T0 = tile * kSweepC;
+        for (uint32_t j = find_vbase(reqs, m, T0, lane); j < m; ++j) {
+            const ItemReq r = load_req(reqs, j);
+            const uint64_t B = r.vbase, E = r.vbase + r.length;
+            if (B >= T0 + kSweepC)
+                break;
+            if (E <= T0)
+                continue;
+            values(request_state(r, (int64_t)(T0 - B), states, jump, lane), v);
+            g_u64 *__restrict__ o =
+                (g_u64 *)(reinterpret_cast<uintptr_t>(r.dst) + (T0 - B) * sizeof(uint64_t));
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) {
+                const uint32_t at = 2 * (64 * i + lane);
+                const uint64_t P = T0 + at;
+                const bool v0 = P >= B && P < E;
+                const bool v1 = P + 1 >= B && P + 1 < E;
+                if (v0 && v1)
+                    *(g_u64x2 *)(o + at) = v[i];
+                else if (v0)
+                    o[at] = v[i].x;
+                else if (v1)
+                    o[at + 1] = v[i].y;
+            }
+        }
+    }
+}
+
 // A batch of at most kSmallReqs requests with its table in the kernel's
 // arguments: one wave per work item, no table upload before the launch.
 template <int S, int R, bool STAR>
 __global__ __launch_bounds__(256) void batch_small_kernel(const SmallTable t,
-                                                          const uint64_t *__restrict__ pow2,
+                                                          const uint64_t *__restrict__ jump,
                                                           const uint64_t *__restrict__ spread)
 {
     constexpr int LDS_ROW = lds_row(R);
@@ -559,11 +814,10 @@ __global__ __launch_bounds__(256) void batch_small_kernel(const SmallTable t,
     const uint64_t item = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wid;
     if (item >= t.desc.n_items)
         return;
-    // The last request whose first item is at most this item (m is small).
-    uint32_t lo = 0;
-    for (uint32_t j = 1; j < t.desc.m; ++j)
-        if (t.reqs[j].item_begin <= item)
-            lo = j;
+    // The last request whose first item is at most this item: one per lane.
+    static_assert(kSmallReqs <= 64, "a lane per request");
+    const bool le = lane < t.desc.m && t.reqs[lane].item_begin <= item;
+    const uint32_t lo = 63 - __builtin_clzll(__ballot(le));
     const BatchReq &q = t.reqs[lo];
     ItemReq r;
     r.offset = q.offset;
@@ -577,8 +831,20 @@ __global__ __launch_bounds__(256) void batch_small_kernel(const SmallTable t,
     r.mix_high = q.mix_high;
     r.zero_fix = q.zero_fix;
     uint64_t x = 0;
-    (void)process_item<S, R, STAR>(r, item, false, x, lds, nullptr, pow2, spread,
+    (void)process_item<S, R, STAR>(r, item, false, x, lds, nullptr, jump, spread,
                                    (g_cu64 *)t.desc.states, lane);
+}
+
+// The staged table (page-locked host memory, mapped) to the device: what a
+// copy command does, without the copy engine's hand-over to the kernel that
+// waits for it. With four slots in turn, 62 MB in 256 requests went from 36 us
+// a call to 24, of which 20 are the kernel's own.
+__global__ __launch_bounds__(256) void batch_upload_kernel(const u64x2 *__restrict__ src,
+                                                           u64x2 *__restrict__ dst, uint32_t chunks)
+{
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < chunks;
+         i += gridDim.x * blockDim.x)
+        dst[i] = src[i];
 }
 
 template <int S, int R, bool STAR>
@@ -592,7 +858,53 @@ hipError_t launch_group_t(const BatchDesc *desc, const BatchTables &t, const rng
         delta256 = (uint64_t)(step_bytes / (c.pace_gbs * 1e9) * t.clock_khz * 1e3 * 256.0);
     }
     batch_group_kernel<S, R, STAR><<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(
-        desc, t.pow2, t.spread, t.group_nib, c.group, c.group_steps, delta256);
+        desc, t.jump, t.spread, t.group_nib, c.group, c.group_steps, delta256);
+    return hipGetLastError();
+}
+
+template <bool STAR>
+hipError_t launch_sweep(const BatchDesc *desc, const BatchTables &t, const rngx_batch_cfg &c,
+                        hipStream_t s)
+{
+    constexpr size_t lds_bytes =
+        (kSweepTable + (size_t)kSweepWaves * kSweepC) * sizeof(uint64_t); // 152 KiB
+    // More dynamic LDS than a kernel may use by default: allowed once per
+    // device (devices beyond the table, at every launch).
+    constexpr int kDevs = 16;
+    static std::atomic<bool> allowed[kDevs] = {};
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess)
+        return e;
+    const bool known = dev >= 0 && dev < kDevs;
+    if (!known || !allowed[dev].load(std::memory_order_relaxed)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(batch_sweep_kernel<STAR>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        if (e != hipSuccess)
+            return e;
+        if (known)
+            allowed[dev].store(true, std::memory_order_relaxed);
+    }
+    uint64_t delta256 = 0;
+    if (c.pace_gbs) {
+        const double step_bytes = (double)c.blocks * kSweepWaves * kSweepC * 8.0;
+        delta256 = (uint64_t)(step_bytes / (c.pace_gbs * 1e9) * t.clock_khz * 1e3 * 256.0);
+    }
+    const uint64_t n_tiles = (t.v_end + kSweepC - 1) / kSweepC;
+    if (t.anchors) {
+        // Few groups: fewer per wavefront, so that short requests, each of
+        // which costs its wavefront a jump, are spread over more of them.
+        const uint64_t n_groups = (n_tiles + kAnchorTiles - 1) / kAnchorTiles;
+        const uint32_t per_wave = n_groups > 65536 ? 64 : 16;
+        const uint64_t blocks = (n_groups + 4 * per_wave - 1) / (4 * per_wave);
+        batch_anchor_kernel<<<dim3((uint32_t)blocks), dim3(256), 0, s>>>(
+            desc, t.jump, t.anchor_spread, t.anchors, n_groups, per_wave);
+        const hipError_t e2 = hipGetLastError();
+        if (e2 != hipSuccess)
+            return e2;
+    }
+    batch_sweep_kernel<STAR><<<dim3(c.blocks), dim3(64 * kSweepWaves), lds_bytes, s>>>(
+        desc, t.jump, t.sweep, t.anchors, n_tiles, delta256);
     return hipGetLastError();
 }
 
@@ -608,10 +920,10 @@ hipError_t launch_batch_s(const BatchDesc *desc, const BatchTables &t, const rng
     const uint32_t run = c.run_items ? c.run_items : 1;
     if (c.row_values == 8)
         batch_kernel<S, 8, STAR><<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(
-            desc, t.pow2, t.spread, t.carry_nib, run, c.per_item);
+            desc, t.jump, t.spread, t.carry_nib, run, c.per_item);
     else
         batch_kernel<S, 16, STAR><<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(
-            desc, t.pow2, t.spread, t.carry_nib, run, c.per_item);
+            desc, t.jump, t.spread, t.carry_nib, run, c.per_item);
     return hipGetLastError();
 }
 
@@ -622,10 +934,10 @@ hipError_t launch_batch_small_s(const SmallTable &tab, const BatchTables &t,
     const size_t lds_bytes = (size_t)c.waves_per_block * 64 * lds_row(c.row_values) * 8;
     if (c.row_values == 8)
         batch_small_kernel<S, 8, STAR>
-            <<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(tab, t.pow2, t.spread);
+            <<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(tab, t.jump, t.spread);
     else
         batch_small_kernel<S, 16, STAR>
-            <<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(tab, t.pow2, t.spread);
+            <<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(tab, t.jump, t.spread);
     return hipGetLastError();
 }
 
@@ -643,6 +955,15 @@ __global__ __launch_bounds__(256) void checksum_kernel(const uint64_t *__restric
 }
 
 } // namespace
+
+hipError_t launch_batch_upload(const void *src_mapped, void *dst, size_t bytes, hipStream_t s)
+{
+    const uint32_t chunks = (uint32_t)(bytes / 16); // staged tables are whole 64-byte records
+    const uint32_t blocks = (chunks + 255) / 256;
+    batch_upload_kernel<<<dim3(blocks < 256 ? blocks : 256), dim3(256), 0, s>>>(
+        static_cast<const u64x2 *>(src_mapped), static_cast<u64x2 *>(dst), chunks);
+    return hipGetLastError();
+}
 
 hipError_t launch_checksum(const uint64_t *data, uint64_t n, uint64_t *acc, hipStream_t s)
 {
@@ -693,6 +1014,8 @@ template <bool STAR>
 hipError_t launch_batch_star(const rngx_batch_cfg &cfg, const BatchDesc *desc,
                              const BatchTables &t, hipStream_t s)
 {
+    if (cfg.group == kSweepOrder)
+        return launch_sweep<STAR>(desc, t, cfg, s);
     switch (cfg.values_per_lane) {
     case 8: return launch_batch_s<8, STAR>(desc, t, cfg, s);
     case 16: return launch_batch_s<16, STAR>(desc, t, cfg, s);

@@ -155,18 +155,28 @@ constexpr size_t kReqOffset = 128;
 static_assert(kReqOffset >= sizeof(BatchDesc) && kReqOffset % 64 == 0, "request offset");
 
 // A batch of at most kSmallReqs requests travels in the kernel's arguments
-// (1,088 bytes) instead of being uploaded: one launch, no copy before it.
-constexpr uint32_t kSmallReqs = 16;
+// (3,136 bytes of the 4 KiB a launch takes) instead of being uploaded: one
+// launch, no copy before it.
+constexpr uint32_t kSmallReqs = 48;
 struct SmallTable {
     BatchDesc desc;
     BatchReq reqs[kSmallReqs];
 };
+
+// Sweep order: a group of 16 tiles that lies inside one request: the state at its
+// first value and where that value goes (dst null: requests share the group).
+struct SweepAnchor {
+    uint64_t state;
+    uint64_t *dst;
+};
+constexpr uint64_t kAnchorValues = 8192;
 
 // A staging/upload slot for one batch in flight (batch.cpp).
 struct BatchSlot {
     int device = -1;          // the device its buffers, event and graph are on
     uint32_t capacity = 0;    // requests the buffers hold (power of two)
     void *staging = nullptr;  // page-locked: BatchDesc, then capacity BatchReq at kReqOffset
+    void *mapped = nullptr;   // its device-mapped address
     void *devtab = nullptr;   // device copy of the same
     hipEvent_t done = nullptr; // recorded after the slot's last launch
     hipGraphExec_t exec = nullptr;
@@ -175,6 +185,9 @@ struct BatchSlot {
     hipStream_t cap_stream = nullptr;
     uint32_t m_staged = 0;
     uint64_t n_items = 0;
+    uint64_t v_end = 0;       // end of the staged batch's virtual index space
+    SweepAnchor *anchors = nullptr; // sweep order: n_anchors anchors
+    uint64_t n_anchors = 0;
 };
 
 bool batch_cfg_valid(const rngx_batch_cfg &c);
@@ -189,30 +202,53 @@ constexpr int kCarryTable = 256;
 // Entries of the per-S lane-spread table: 16 nibble positions x 16 values x
 // 64 lanes (128 KiB).
 constexpr int kSpreadTable = 16 * 16 * 64;
+// Entries of the sweep order's lane-spread table: 22 positions of 3 bits x 8
+// values x 64 lanes (88 KiB, held in LDS).
+constexpr int kSweepTable = 22 * 8 * 64;
+// With what follows it: the rows of T^(512 a), a < 16, and the lane-spread
+// table of the anchors (steps of kAnchorValues).
+constexpr int kSweepTables = kSweepTable + 16 * 64 + kSpreadTable;
+// rngx_batch_cfg.group of the sweep order inside the library (no caller's
+// configuration holds it): values_per_lane 8, blocks and pace_gbs as set.
+constexpr uint32_t kSweepOrder = 1;
+// rngx_batch_cfg.use_graph inside the library: the table goes to the device
+// in a kernel of its own (batch_upload_kernel).
+constexpr uint32_t kUploadKernel = 2;
 // Device tables one batch launch needs, for its values-per-lane S.
 struct BatchTables {
-    const uint64_t *pow2;       // T^(2^b), b < 64: 64 rows each
+    const uint64_t *jump;       // T^(a 16^i) at (16 i + a) * 64: 64 rows each
     const uint64_t *spread;     // T^(m S) (v << 4q) at ((16 q + v) * 64 + m)
     const uint64_t *carry_nib; // T^(63 S) (next tile, same lane) as kCarryTable nibble entries
     const uint64_t *group_nib; // grouped order: T^(g 64 S - S) (tile g on), or null
+    const uint64_t *sweep;     // T^(8 m) (v << 3q) at ((8 q + v) * 64 + m)
+                               // then T^(512 a) at kSweepTable + 64 a, a < 16: 64 rows each
+    const uint64_t *anchor_spread; // T^(8192 m) (v << 4q) at ((16 q + v) * 64 + m)
+    SweepAnchor *anchors;      // sweep order: room for an anchor per 8192 virtual indices
+    uint64_t v_end;            // sweep order: end of the virtual index space
     uint32_t clock_khz;        // rate of the constant-rate clock
 };
+// Entries of the jump table: 16 digit positions x 16 digits x 64 rows.
+constexpr int kJumpTable = 16 * 16 * 64;
 // Device copies of the jump tables for the current device (thread-safe).
-int batch_tables_locked(const uint64_t **pow2, const uint64_t **spread_all, int *n_cus,
+int batch_tables_locked(const uint64_t **jump, const uint64_t **spread_all, int *n_cus,
                         const uint64_t **carry_nib_all = nullptr,
-                        const uint64_t **group_nib_all = nullptr, int *clock_khz = nullptr);
+                        const uint64_t **group_nib_all = nullptr, int *clock_khz = nullptr,
+                        const uint64_t **sweep = nullptr);
 // The configuration a launch runs: blocks 0 resolved (8 waves per compute
 // unit), or for the grouped order every block that fits, in whole groups.
 int resolve_batch_cfg(const rngx_batch_cfg &c, int n_cus, rngx_batch_cfg *out);
 // The tables of one launch's S (and group size) among the per-device ones.
-void fill_batch_tables(BatchTables &t, const rngx_batch_cfg &cfg, const uint64_t *pow2,
+void fill_batch_tables(BatchTables &t, const rngx_batch_cfg &cfg, const uint64_t *jump,
                        const uint64_t *spread_all, const uint64_t *nib_all,
-                       const uint64_t *group_all, int clock_khz);
+                       const uint64_t *group_all, const uint64_t *sweep, int clock_khz);
 // Argument checks of a batched call; *total_out = the values requested.
 int batch_validate(const rngx_req *reqs, uint32_t m, const uint64_t *out, uint64_t out_cap,
                    uint64_t *total_out);
+// Stage a packed batch for configuration `cfg`; *run receives what to launch
+// (cfg as given, or as batch_order has it).
 int batch_stage(BatchSlot &slot, const rngx_req *reqs, uint32_t m, uint64_t *out,
-                uint64_t out_cap, uint32_t values_per_lane, uint64_t *total_out);
+                uint64_t out_cap, const rngx_batch_cfg &cfg, bool as_given, rngx_batch_cfg *run,
+                uint64_t *total_out);
 // One request as staged by a host-side producer (the batch API or the server).
 struct StageReq {
     uint64_t offset;
@@ -224,6 +260,10 @@ struct StageReq {
 };
 int batch_stage_items(BatchSlot &slot, const StageReq *items, uint32_t k,
                       uint32_t values_per_lane, const uint64_t *states);
+// What runs for `values` (padded) values under configuration c. The default
+// configuration's values leave the order to the library; any other runs as
+// given. anchors: whether the caller has room for the sweep order's anchors.
+rngx_batch_cfg batch_order(const rngx_batch_cfg &c, uint64_t values, bool anchors);
 // star: emit the scrambled words. fit_grid: shrink the persistent grid to the
 // staged work (direct launches).
 int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg, bool star, hipStream_t stream,
@@ -240,6 +280,8 @@ hipError_t launch_batch(const rngx_batch_cfg &cfg, const BatchDesc *desc, const 
                         bool star, hipStream_t s);
 hipError_t launch_batch_small(const rngx_batch_cfg &cfg, const SmallTable &tab,
                               const BatchTables &t, bool star, hipStream_t s);
+// Staged table (device-mapped host address) -> device.
+hipError_t launch_batch_upload(const void *src_mapped, void *dst, size_t bytes, hipStream_t s);
 // Checksum sum_i data[i] * (2 i + 1) mod 2^64 into *acc (device, pre-zeroed).
 hipError_t launch_checksum(const uint64_t *data, uint64_t n, uint64_t *acc, hipStream_t s);
 

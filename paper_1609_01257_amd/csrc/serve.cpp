@@ -96,7 +96,6 @@ struct Server {
     uint64_t max_pending = 1u << 20;
     uint32_t max_inflight = 2;
     bool star = false; // the output scrambler, fixed at start
-    rngx_batch_cfg cfg{256, 4, 0, 0, 16, 1, 0, 0, 0, 0};
     std::thread worker;
     int worker_rc = RNGX_OK;
     std::string worker_msg;
@@ -175,29 +174,12 @@ bool admit(Server &s)
 // with 2^20; the backlog's multi-GB batches are unaffected).
 constexpr uint64_t kSmallBatchValues = 1u << 23;
 
-// Launch schedule of a served batch of `values` (padded) values. Small
-// batches are latency-bound: one wave per 1,024-value item (S = 16) spreads
-// a request over the most waves, each storing soonest (Poisson runs at
-// 2k/10k/50k req/s: p50 23/23/28 us against 28/27/33 with 4,096-value
-// items). Larger ones run in the grouped order (S = 16, groups of 32
-// wavefronts, 8 steps per region, schedule 6,250 GB/s: the batch
-// autotuner's pick on the 4,096-stream table), which served a 243 GB
-// backlog at 5.85 TB/s (median of three) against 5.52 for the persistent
-// grid with S = 256 and 3.18 with the schedule halved for two batches in
-// flight; the persistent grid had measured 5.45-5.51 against 4.90-4.97
-// for one wave per item.
-void serve_schedule(uint64_t values, rngx_batch_cfg &cfg)
-{
-    const bool small = values <= kSmallBatchValues;
-    cfg.values_per_lane = 16;
-    cfg.waves_per_block = 4;
-    cfg.row_values = 16;
-    cfg.per_item = small ? 1u : 0u;
-    cfg.run_items = small ? 1u : 0u;
-    cfg.group = small ? 0u : 32u;
-    cfg.group_steps = small ? 0u : 8u;
-    cfg.pace_gbs = small ? 0u : 6250u;
-}
+// A served batch runs in the library's own order (batch_order), whatever the
+// batch API's configuration: one wave per 1,024-value item up to 2^26 values
+// (a small batch is latency-bound: that spreads a request over the most waves,
+// each storing soonest; Poisson runs at 2k/10k/50k req/s: p50 23/23/28 us
+// against 28/27/33 with 4,096-value items), the sweep order above.
+constexpr rngx_batch_cfg kServeCfg{16, 4, 0, 0, 16, 0, 0, 32, 8, 6250};
 
 // Whether the next batch (the first max_batch admitted requests, padded as
 // launch_admitted pads them) would be small.
@@ -237,8 +219,7 @@ int launch_admitted(Server &s, Flight &f, std::vector<StageReq> &items, const Se
         r.state = ST_INFLIGHT;
         f.tickets.push_back(tk);
     }
-    rngx_batch_cfg cfg = s.cfg;
-    serve_schedule(vbase, cfg);
+    const rngx_batch_cfg cfg = batch_order(kServeCfg, vbase, true);
     int rc = batch_stage_items(f.slot, items.data(), (uint32_t)items.size(), cfg.values_per_lane,
                                s.d_states);
     if (rc == RNGX_OK)
@@ -663,10 +644,6 @@ extern "C" int rngx_serve_start(uint64_t seed, uint32_t n_states, void *pool, ui
     s.alloc.reset(pool_bytes & ~(uint64_t)255);
     s.cursor.assign(n_states, 0);
     s.max_batch = max_batch;
-    // Batch sizes vary: launch directly (no graph) with a grid fitted to the
-    // items, 4 waves per block, 8 waves per CU at most; S and the schedule
-    // are chosen per batch.
-    s.cfg = rngx_batch_cfg{256, 4, 0, 0, 16, 1, 0, 0, 0, 0};
     s.star = current_scrambler() == RNGX_SCRAMBLE_STAR;
     s.worker_rc = RNGX_OK;
     s.worker_msg.clear();

@@ -312,3 +312,74 @@ def test_scrambled_batches_match_oracle(oracle, S, per_item, graph, m):
         rngx.set_scrambler(rngx.SCRAMBLE_NONE)
     assert np.array_equal(got, exp)
     assert np.array_equal(plain, oracle.generate_batch(_oracle_reqs(oracle, r)))
+
+
+# The library's own order (the default configuration's values). Up to 2^26
+# values: one wave per item, 48 requests in the kernel's arguments, more in a
+# table that a kernel uploads.
+@pytest.mark.parametrize("entry", ["generate_batch", "generate_batch_noalloc"])
+@pytest.mark.parametrize("m", [1, 47, 48, 49, 63, 64, 65, 300])
+def test_library_order_small_batches(oracle, entry, m):
+    r = inputs.ragged_requests(m=m, seed=300 + m, max_len=30000, max_offset=10**6)
+    exp = oracle.generate_batch(_oracle_reqs(oracle, r))
+    out = torch.zeros(r.total + 9, dtype=torch.int64, device="cuda")
+    getattr(rngx, entry)(_reqs(r), out[2:2 + r.total])
+    torch.cuda.synchronize()
+    host = out.cpu().numpy().view(np.uint64)
+    assert not host[:2].any() and not host[2 + r.total:].any()
+    assert np.array_equal(host[2:2 + r.total], exp)
+
+
+# Above 2^26 values: the sweep order. Tiles of 512 values, groups of 8,192
+# with an anchor where one request holds them whole: requests that end and
+# begin around both, runs of short requests between long ones, offsets that
+# put a tile's start before value number 0 (a backward jump past the period),
+# an output at every 16 bytes of a line.
+@pytest.mark.parametrize("skew,star", [(0, False), (2, False), (14, True)])
+def test_sweep_order(oracle, skew, star):
+    rng = np.random.default_rng(40 + skew)
+    edges = np.array([w + d for w in (512, 8192, 16384, 131072) for d in (-1, 0, 1)])
+    lengths = np.concatenate([[25_000_001], edges, rng.integers(1, 40, 300), [0, 9_000_000, 0],
+                              rng.integers(400, 700, 200), [31_000_003], edges[::-1],
+                              [5_000_000, 1]]).astype(np.uint64)
+    m = len(lengths)
+    r = inputs.Requests(rng.integers(0, 2**64, m, dtype=np.uint64),
+                        rng.integers(0, 2**32, m, dtype=np.uint64).astype(np.uint32),
+                        rng.choice([0, 1, 300, 511, 513, 10**6], m).astype(np.uint64), lengths)
+    assert r.total > 1 << 26
+    exp = oracle.generate_batch(_oracle_reqs(oracle, r))
+    if star:
+        exp = oracle.scramble_array(exp)
+    rngx.set_scrambler(rngx.SCRAMBLE_STAR if star else rngx.SCRAMBLE_NONE)
+    try:
+        out = torch.zeros(r.total + 32, dtype=torch.int64, device="cuda")
+        for _ in range(2):
+            rngx.generate_batch(_reqs(r), out[skew:skew + r.total])
+        torch.cuda.synchronize()
+    finally:
+        rngx.set_scrambler(rngx.SCRAMBLE_NONE)
+    host = out.cpu().numpy().view(np.uint64)
+    assert not host[:skew].any() and not host[skew + r.total:].any()
+    assert np.array_equal(host[skew:skew + r.total], exp)
+
+
+def test_library_order_calls_in_flight_together(oracle):
+    # More calls than the library has staging slots, tables of both orders
+    # and sizes, on two streams, without a wait between them.
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    jobs = []
+    for k, (m, top) in enumerate([(5, 40000), (200, 40000), (3, 40_000_000), (200, 3000),
+                                  (48, 9000), (60, 9000), (4, 40_000_000), (500, 2000),
+                                  (1, 1), (70, 20000)]):
+        r = inputs.ragged_requests(m=m, seed=700 + k, max_len=top, max_offset=1000)
+        o = torch.zeros(r.total, dtype=torch.int64, device="cuda")
+        jobs.append((r, o))
+    torch.cuda.synchronize()
+    assert max(r.total for r, _ in jobs) > 1 << 26
+    for k, (r, o) in enumerate(jobs):
+        o.record_stream(streams[k % 2])
+        rngx.generate_batch(_reqs(r), o, stream=streams[k % 2])
+    torch.cuda.synchronize()
+    for k, (r, o) in enumerate(jobs):
+        assert np.array_equal(o.cpu().numpy().view(np.uint64),
+                              oracle.generate_batch(_oracle_reqs(oracle, r))), k

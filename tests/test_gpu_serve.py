@@ -254,3 +254,24 @@ def test_scrambled_server_matches_oracle(oracle, server):
         got = _values(pool, rngx.serve_wait(t, 60.0), L)
         assert np.array_equal(got, oracle.scramble_array(e)), (g, L)
         rngx.serve_release(t)
+
+
+def test_served_batch_in_the_sweep_order(oracle, server):
+    # One batch of more than 2^26 values (resident states, slices of the pool
+    # with their own alignment), twice, so that the second continues the
+    # streams of the first.
+    seed = 77
+    pool = server(seed, 100, 1400 << 20)
+    rng = np.random.default_rng(8)
+    lengths = np.concatenate([rng.integers(1, 9000, 60), [24_000_001, 16, 30_000_017, 8192],
+                              rng.integers(8000, 9000, 40), [15_000_000]])
+    ids = rng.integers(0, 100, len(lengths))
+    assert lengths.sum() > 1 << 26
+    hist = []
+    for _ in range(2):
+        hist += list(zip(ids.tolist(), lengths.tolist()))
+        tickets = rngx.serve_submit_many(ids, lengths)
+        exp = oracle.serve_expected(seed, hist)[-len(lengths):]
+        for t, (g, L), e in zip(tickets.tolist(), hist[-len(lengths):], exp):
+            assert np.array_equal(_values(pool, rngx.serve_wait(t, 60.0), L), e), (g, L)
+            rngx.serve_release(t)
