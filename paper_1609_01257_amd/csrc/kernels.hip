@@ -96,6 +96,9 @@ __device__ __forceinline__ void wait_until(uint64_t due)
         __builtin_amdgcn_s_sleep(2);
 }
 
+// What the Infinity Cache holds.
+constexpr uint64_t kCacheBytes = 256ull << 20;
+
 // Output words of one 128-byte line, the unit in which the device's memory
 // takes writes whole.
 template <typename T> constexpr uint32_t kLine = 128 / sizeof(T);
@@ -311,16 +314,19 @@ __device__ __forceinline__ u32x4 lds_chunk(const uint32_t *p)
     return *reinterpret_cast<const u32x4_w *>(p);
 }
 
+constexpr uint32_t kAheadRows = 4;
+
 // Keeps the value's computation before this point.
 __device__ __forceinline__ void pin(uint64_t &x) { asm volatile("" : "+v"(x)); }
 
 // Rows of one wavefront's columns, from its states x (and, for staged rows,
 // xh: the kLine states right of its columns, one per lane).
-template <typename T, int P, bool NT, bool STAR, bool SHIFT, bool WHOLE>
+// `ahead` is called once, kAheadRows rows before the end (or at the start).
+template <typename T, int P, bool NT, bool STAR, bool SHIFT, bool WHOLE, typename Ahead>
 __device__ __forceinline__ void paced_rows(uint64_t (&x)[P][Vec16<T>::E], uint64_t xh, T *row,
                                            uint32_t rows, uint64_t n, uint64_t wbase,
                                            uint32_t lane, T *stage, uint64_t t0, uint64_t &sched,
-                                           uint64_t delta256, uint32_t burst)
+                                           uint64_t delta256, uint32_t burst, const Ahead &ahead)
 {
     typedef Vec16<T> VT;
     typedef typename VT::type V16;
@@ -329,8 +335,11 @@ __device__ __forceinline__ void paced_rows(uint64_t (&x)[P][Vec16<T>::E], uint64
     // Columns from wbase to the end of the row (all that matter here).
     const uint32_t cols = (uint32_t)(n - wbase < W + L ? n - wbase : W + L);
     uint32_t left = 1;
+    const uint32_t ahead_at = rows > kAheadRows ? rows - kAheadRows : 0;
 #pragma nounroll
     for (uint32_t k = 0; k < rows; ++k) {
+        if (sizeof(T) == 8 && k == ahead_at)
+            ahead();
         if (delta256 && --left == 0) {
             wait_until(t0 + (sched >> 8));
             sched += delta256;
@@ -453,6 +462,10 @@ gen_paced_kernel(const PacedArgs a, const Polys polys)
     constexpr uint32_t W = 64u * P * E; // work-items per wavefront
     constexpr uint32_t L = kLine<T>;
     constexpr bool SEG = sizeof(Polys) > sizeof(NoPolys);
+    // Whether the next strip's states are loaded during this one's last rows:
+    // 1-2.5 % at 10^7-2^26 states x 4-64 u64; nothing, and 2 % lost at 2^26 x
+    // 2-8, for 4-byte words, whose states take twice the registers.
+    constexpr bool AHEAD = sizeof(T) == 8 && !SEG;
     __shared__ uint64_t jump_cols[SEG ? 64 : 1], jump_tab[SEG ? 256 : 1];
     extern __shared__ __align__(16) unsigned char lds_dyn[];
     const uint32_t lane = threadIdx.x & 63u;
@@ -463,17 +476,33 @@ gen_paced_kernel(const PacedArgs a, const Polys polys)
     const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
     uint64_t sched = 0;
     uint32_t have = 0; // the segment jump_tab belongs to (0: none)
+    // First column of the wavefront's part of a work item, and its states.
+    const auto column = [&](uint32_t item) {
+        const uint32_t cb = SEG ? item % a.col_blocks : item;
+        return ((uint64_t)cb * (blockDim.x >> 6) + wid) * W;
+    };
+    uint64_t xn[P][E], xhn = 0; // of the next item
+    const auto fetch = [&](uint32_t item) {
+        const uint64_t at = column(item);
+        load_states(xn, a.state_in, n, at, lane, at + W <= n);
+        if (SHIFT)
+            xhn = lane < L && at + W + lane < n ? a.state_in[at + W + lane] : 0;
+    };
+    if (AHEAD)
+        fetch(blockIdx.x);
     for (uint32_t item = blockIdx.x; item < a.items; item += gridDim.x) {
         const uint32_t seg = SEG ? item / a.col_blocks : 0;
-        const uint64_t wbase =
-            ((uint64_t)(SEG ? item - seg * a.col_blocks : item) * (blockDim.x >> 6) + wid) * W;
+        const uint64_t wbase = column(item);
         if (!SEG && wbase >= n)
             return; // later strips lie further right
-        const bool mine = wbase + W <= n;
-        uint64_t x[P][E], xh = 0;
-        load_states(x, a.state_in, n, wbase, lane, mine);
-        if (SHIFT && lane < L && wbase + W + lane < n)
-            xh = a.state_in[wbase + W + lane];
+        if (!AHEAD)
+            fetch(item);
+        uint64_t x[P][E], xh = xhn;
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                x[p][e] = xn[p][e];
         if (SEG && seg) { // uniform over the block
             if (seg != have)
                 build_jump(poly_of(polys, seg), jump_cols, jump_tab);
@@ -486,6 +515,11 @@ gen_paced_kernel(const PacedArgs a, const Polys polys)
             if (SHIFT)
                 xh = jump_by(jump_tab, xh);
         }
+        const bool more = a.items - item > gridDim.x;
+        const auto ahead = [&] {
+            if (AHEAD && more)
+                fetch(item + gridDim.x);
+        };
         if (SEG && wbase >= n)
             continue; // no columns here (the wavefront still helped with the table)
         const uint32_t k0 = seg * a.seg_rows;
@@ -493,12 +527,12 @@ gen_paced_kernel(const PacedArgs a, const Polys polys)
         T *row = out + (uint64_t)k0 * n;
         if (wbase + W + (SHIFT ? L : 0) <= n)
             paced_rows<T, P, NT, STAR, SHIFT, true>(x, xh, row, rows, n, wbase, lane, stage, t0,
-                                                    sched, a.delta256, a.burst);
+                                                    sched, a.delta256, a.burst, ahead);
         else
             paced_rows<T, P, NT, STAR, SHIFT, false>(x, xh, row, rows, n, wbase, lane, stage, t0,
-                                                     sched, a.delta256, a.burst);
+                                                     sched, a.delta256, a.burst, ahead);
         if (k0 + rows == a.iters)
-            store_states(x, a.state_out, n, wbase, lane, mine);
+            store_states(x, a.state_out, n, wbase, lane, wbase + W <= n);
     }
 }
 
@@ -566,7 +600,18 @@ hipError_t launch_paced_t(const GenPlan &plan, const Polys &polys, uint64_t *sta
     // Strips of equal size.
     const uint64_t strips = (items + grid - 1) / grid;
     grid = (items + strips - 1) / strips;
-    const double row_bytes = (double)grid * block * 16.0 * P;
+    // The schedule counts a row's own bytes. A later strip's states are read
+    // and an earlier one's written while rows are, 16 bytes per work-item
+    // more: where that is traffic to the memory (states beyond the Infinity
+    // Cache) the row's time grows by its share, and for 4-byte words, whose
+    // share is twice as large, by what exceeds 4.5 %. (2^26 states x 32 u64
+    // 5.7 -> 6.3 TB/s, x 64 u32 5.8 -> 6.1; 10^7 x 32 u32 6.1 -> 6.8. Of no
+    // use elsewhere: 2^24 x 32 u64 7.3 without, 7.1 with the excess over 3 %.)
+    const double share = 16.0 / ((double)sizeof(T) * iters);
+    const double states = strips == 1 ? 1.0
+                          : (uint64_t)n * 8 > kCacheBytes ? 1.0 + share
+                          : sizeof(T) == 4 ? std::max(1.0, (1.0 + share) / 1.045) : 1.0;
+    const double row_bytes = (double)grid * block * 16.0 * P * states;
     const double ticks = pace_gbs ? row_bytes / (pace_gbs * 1e9) * clock_khz * 1e3 : 0.0;
     PacedArgs a;
     a.state_in = state;
@@ -656,9 +701,6 @@ hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, hipStrea
     return hipGetLastError();
 }
 
-// What the Infinity Cache holds.
-static constexpr uint64_t kCacheBytes = 256ull << 20;
-
 GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, const void *out)
 {
     const uint64_t row = (uint64_t)n * (u32 ? 4 : 8), bytes = row * iters;
@@ -694,7 +736,15 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, c
     // aligned: 6.9 and 4.3). Below 256 MiB the Infinity Cache puts the parts
     // together and staging only costs (2^22 + 1 x 8: 54.7 us staged, 51.6 not).
     p.shift = !lines && iters >= 2 && (bytes > kCacheBytes || p.segs > 1);
-    p.scheduled = p.shift || (cfg.pace_gbs && iters >= 2 && p.aligned16);
+    // A few iterations of long rows end before a schedule orders anything;
+    // they run as fast without one, or faster, up to 32 bytes a stream and up
+    // to 48 where rows are on lines and the output is about the cache's size
+    // (2^26 states x 4 u64 578 us free, 600 scheduled; 2^25 x 8 u32 229 and
+    // 234; 10^7 x 12 u32 96 and 100, but 2,200,000 x 12 u32 26 and 24, and
+    // 3,000,002 x 6 u64, off lines, 36 and 34; 2^24 x 8 u64 201 and 190).
+    const bool mid = lines && bytes > kCacheBytes / 2 && bytes <= 2 * kCacheBytes;
+    const bool few = !p.shift && !narrow && row / n * iters <= (mid ? 48u : 32u);
+    p.scheduled = p.shift || (cfg.pace_gbs && iters >= 2 && p.aligned16 && !few);
     if (narrow && p.scheduled) {
         p.cfg.chunks = 1;
         p.cfg.block = std::min(cfg.block, 256u);

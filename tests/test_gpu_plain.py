@@ -524,6 +524,26 @@ def test_scrambled_segments_and_staged_rows(oracle, star):
         assert np.array_equal(got, exp), (u32, n, iters)
 
 
+# Long rows, in one strip and in several (the next one's states are read during
+# the last rows), by calls on both sides of the length that takes a schedule.
+@pytest.mark.parametrize("u32", [False, True])
+@pytest.mark.parametrize("n", [1 << 20, 1 << 21, (1 << 21) + 16, (1 << 22) + 1026, 5000000])
+def test_few_iterations_of_long_rows(oracle, u32, n):
+    counts = (1, 4, 5, 8, 9, 12, 13) if u32 else (1, 2, 4, 5, 6, 7)
+    gen = rngx.generate_u32 if u32 else rngx.generate
+    rngx.init(8, n)
+    outs = []
+    for iters in counts:
+        outs.append(torch.empty(iters * n, dtype=torch.int32 if u32 else torch.int64,
+                                device="cuda"))
+        gen(iters, outs[-1])
+    torch.cuda.synchronize()
+    got = np.concatenate([(_u32 if u32 else _u64)(o).reshape(-1, n) for o in outs])
+    assert np.array_equal(got, (oracle.generate_u32 if u32 else oracle.generate)(8, n, sum(counts)))
+    st, _, c = rngx.get_state()
+    assert np.array_equal(st, oracle.generate(8, n, 1, cursor=c).ravel())
+
+
 def test_paths_with_and_without_a_second_state_buffer_alternate(oracle):
     # In-place and out-of-place calls in turn, on two streams.
     seed, n = 5, 20003
