@@ -62,7 +62,10 @@ extern "C" {
  * (8 * n_states bytes of device memory) on the current device, launches the
  * init kernel on the library's own stream, resets the cursor to 0 and
  * restarts the profiler (as the paper starts profiling just before init).
- * Calling it again releases the previous state first.
+ * Calling it again releases the previous state first, or overwrites its
+ * buffer, after its last use, where that has room for n_states to twice as
+ * many; the init kernel then runs on the default stream if the state was last
+ * used there.
  * Errors: RNGX_E_INVAL if n_states == 0 (n_states is a 32-bit count, as the
  * paper's nseeds is a cl_uint); RNGX_E_NOMEM; RNGX_E_HIP. */
 int rngx_init(uint64_t seed, uint32_t n_states);

@@ -2,9 +2,12 @@
 //
 // One process-wide context (Generator, internal.h) holds the library-owned
 // state buffer, the library's own stream (for the init kernel) and the
-// `state_ready` event that orders every use of the state across caller
-// streams: a generate call makes its stream wait for `state_ready`,
-// launches, and re-records it.
+// event, `ready`, that orders every use of the state across caller streams: a
+// generate call makes its stream wait for it and launches, and the launch's
+// completion is the next one. The launch itself signals `state_ready`: a marker
+// recorded behind it would hold the stream for 3 us (a 5 us kernel in a row of
+// calls, with its wait and record: 8.9 us a call, with the event in the launch
+// 6.0). A logged call has an end event already and lends that.
 #include <algorithm>
 #include <atomic>
 #include <cstdarg>
@@ -105,8 +108,8 @@ namespace {
 // Free the state of a previous init (waits for its last use first).
 int release_state_locked(Generator &c)
 {
-    if (c.state_ready)
-        RNGX_HIP(hipEventSynchronize(c.state_ready));
+    if (c.ready)
+        RNGX_HIP(hipEventSynchronize(c.ready));
     if (c.state) {
         RNGX_HIP(hipFree(c.state));
         c.state = nullptr;
@@ -115,21 +118,35 @@ int release_state_locked(Generator &c)
         RNGX_HIP(hipFree(c.alt));
         c.alt = nullptr;
     }
+    c.cap = 0;
+    c.fixed = false;
     c.inited = false;
     c.n = 0;
     c.cursor = 0;
     return RNGX_OK;
 }
 
-// Free any previous state, make sure the library stream and event exist on
-// the current device, allocate n states and open a new profiling window.
-int fresh_state_locked(Generator &c, uint32_t n_states, const char *who)
+// Room for n states that the library's stream (or the default stream) may
+// write, that stream and the event on the current device, and a new profiling
+// window. The buffers of the state before are kept where they are of the size,
+// or up to twice as large (their last use is waited for on the stream): the
+// allocations and the free, which waits for the device, cost more than seeding
+// 65,536 states and taking 64 values of each does.
+int fresh_state_locked(Generator &c, uint32_t n_states, const char *who, bool on_default = false)
 {
+    int dev = -1;
+    RNGX_HIP(hipGetDevice(&dev));
+    if (c.state && !c.fixed && dev == c.device && c.cap >= n_states && c.cap / 2 <= n_states) {
+        c.inited = false;
+        c.n = 0;
+        c.cursor = 0;
+        RNGX_HIP(hipStreamWaitEvent(on_default ? nullptr : c.lib_stream, c.ready, 0));
+        c.ready = c.state_ready;
+        return prof::start(c.lib_stream);
+    }
     int rc = release_state_locked(c);
     if (rc)
         return rc;
-    int dev = -1;
-    RNGX_HIP(hipGetDevice(&dev));
     if (c.lib_stream && dev != c.device) {
         // Resources belong to another device: recreate them here (the
         // streaming pipeline's streams and events on first use).
@@ -139,11 +156,13 @@ int fresh_state_locked(Generator &c, uint32_t n_states, const char *who)
         c.lib_stream = nullptr;
         c.state_ready = nullptr;
     }
+    c.ready = nullptr;
     c.device = dev;
     if (!c.lib_stream)
         RNGX_HIP(hipStreamCreateWithFlags(&c.lib_stream, hipStreamNonBlocking));
     if (!c.state_ready)
         RNGX_HIP(hipEventCreateWithFlags(&c.state_ready, hipEventDisableTiming));
+    c.ready = c.state_ready;
     void *p = nullptr;
     hipError_t e = hipMalloc(&p, (size_t)n_states * sizeof(uint64_t));
     if (e != hipSuccess) {
@@ -152,7 +171,19 @@ int fresh_state_locked(Generator &c, uint32_t n_states, const char *who)
                          (size_t)n_states * sizeof(uint64_t), hipGetErrorString(e));
     }
     c.state = static_cast<uint64_t *>(p);
+    c.cap = n_states;
     return prof::start(c.lib_stream);
+}
+
+// The event of the states' last use, launched on s: state_ready, which that
+// launch signals (marked), or the log's end event, else state_ready recorded.
+int mark_use_locked(Generator &c, bool marked, hipEvent_t logged, hipStream_t s)
+{
+    c.ready = logged ? logged : c.state_ready;
+    c.on_default = s == nullptr;
+    if (!marked && !logged)
+        RNGX_HIP(hipEventRecord(c.state_ready, s));
+    return RNGX_OK;
 }
 
 int generate_impl(uint32_t n_iters, void *out, void *stream, bool u32)
@@ -177,22 +208,27 @@ int check_device_locked(const Generator &c)
 }
 
 hipError_t run_gen_locked(Generator &c, const rngx_launch &cfg, uint32_t n_iters, void *out,
-                          hipStream_t s, bool u32, bool star)
+                          const LaunchAt &s, bool u32, bool star)
 {
     GenPlan plan = plan_gen(cfg, u32, c.n, n_iters, out);
-    if (plan.out_of_place() && !c.alt) {
+    bool in_place = c.fixed;
+    if (plan.out_of_place() && !c.alt && !in_place) {
         void *p = nullptr;
-        if (hipMalloc(&p, (size_t)c.n * sizeof(uint64_t)) == hipSuccess) {
+        if (hipMalloc(&p, (size_t)c.cap * sizeof(uint64_t)) == hipSuccess) {
             c.alt = static_cast<uint64_t *>(p);
         } else {
-            // No room for a second copy of the states: the launch that
-            // works in place, as slow as its unaligned rows make it.
             (void)hipGetLastError();
-            plan.cfg = cfg;
-            plan.scheduled = plan.shift = false;
-            plan.segs = 1;
-            plan.seg_rows = n_iters;
+            in_place = true;
         }
+    }
+    if (plan.out_of_place() && in_place) {
+        // No room for a second copy of the states, or a graph works on this
+        // one at each replay: the launch that works in place, as slow as its
+        // unaligned or short rows make it.
+        plan.cfg = cfg;
+        plan.scheduled = plan.shift = false;
+        plan.segs = 1;
+        plan.seg_rows = n_iters;
     }
     if (plan.segs > 1 && (c.polys_rows != plan.seg_rows || c.polys_count < plan.segs)) {
         jump_polys(plan.seg_rows, plan.segs, c.polys.c);
@@ -224,7 +260,12 @@ int generate_locked(Generator &c, uint32_t n_iters, void *out, hipStream_t s, bo
     int rc = check_device_locked(c);
     if (rc)
         return rc;
-    RNGX_HIP(hipStreamWaitEvent(s, c.state_ready, 0));
+    RNGX_HIP(hipStreamWaitEvent(s, c.ready, 0));
+    // Each replay of a captured call takes the states on from where it was
+    // captured and leaves them there, so they stay in this buffer from now on;
+    // and the event such a call records is the generator's own.
+    const bool captured = capturing(s);
+    c.fixed = c.fixed || captured;
     const int tok = prof::begin("RNG_KERNEL", s);
     rngx_launch cfg = u32 ? c.cfg32 : c.cfg64;
     if (cfg.block == 0) {
@@ -235,12 +276,14 @@ int generate_locked(Generator &c, uint32_t n_iters, void *out, hipStream_t s, bo
         cfg = rngx_launch{512, 2, 1, 7000};
     }
     take_stray_error("before the rng kernel launch");
-    hipError_t e = run_gen_locked(c, cfg, n_iters, out, s, u32,
-                                  current_scrambler() == RNGX_SCRAMBLE_STAR);
-    prof::end(tok, s);
+    const bool mark = tok < 0 && !captured;
+    hipError_t e = run_gen_locked(c, cfg, n_iters, out, LaunchAt(s, mark ? c.state_ready : nullptr),
+                                  u32, current_scrambler() == RNGX_SCRAMBLE_STAR);
+    hipEvent_t logged = prof::end_event(tok, s);
     if (e != hipSuccess)
         return hip_fail(e, "rng kernel launch");
-    RNGX_HIP(hipEventRecord(c.state_ready, s));
+    if ((rc = mark_use_locked(c, mark, captured ? nullptr : logged, s)))
+        return rc;
     c.cursor += n_iters;
     return RNGX_OK;
 }
@@ -266,16 +309,28 @@ int rngx_init(uint64_t seed, uint32_t n_states)
             return rc;
         cache_applied = true;
     }
-    int rc = fresh_state_locked(c, n_states, "rngx_init");
+    // A generator last used on the default stream is seeded there (unless a
+    // capture of some other stream forbids it), to be used there again: a wait
+    // of one stream for another takes the host 10 us and the device some more.
+    hipStreamCaptureStatus st;
+    bool on_default = c.on_default;
+    if (on_default && hipStreamIsCapturing(nullptr, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        on_default = false;
+    }
+    int rc = fresh_state_locked(c, n_states, "rngx_init", on_default);
     if (rc)
         return rc;
-    const int tok = prof::begin("INIT_KERNEL", c.lib_stream);
+    hipStream_t s = on_default ? nullptr : c.lib_stream;
+    const int tok = prof::begin("INIT_KERNEL", s);
     take_stray_error("before the init kernel launch");
-    hipError_t e = launch_init(c.state, n_states, seed_mix(seed), c.lib_stream);
-    prof::end(tok, c.lib_stream);
+    hipError_t e = launch_init(c.state, n_states, seed_mix(seed),
+                               LaunchAt(s, tok < 0 ? c.state_ready : nullptr));
+    hipEvent_t logged = prof::end_event(tok, s);
     if (e != hipSuccess)
         return hip_fail(e, "init kernel launch");
-    RNGX_HIP(hipEventRecord(c.state_ready, c.lib_stream));
+    if ((rc = mark_use_locked(c, tok < 0, logged, s)))
+        return rc;
     c.seed = seed;
     c.n = n_states;
     c.cursor = 0;
@@ -295,7 +350,7 @@ int rngx_get_state(uint64_t *states, uint32_t n, uint64_t *seed, uint64_t *curso
     int rc = check_device_locked(c);
     if (rc)
         return rc;
-    RNGX_HIP(hipStreamWaitEvent(c.lib_stream, c.state_ready, 0));
+    RNGX_HIP(hipStreamWaitEvent(c.lib_stream, c.ready, 0));
     RNGX_HIP(hipMemcpyAsync(states, c.state, (size_t)n * sizeof(uint64_t),
                             hipMemcpyDeviceToHost, c.lib_stream));
     RNGX_HIP(hipStreamSynchronize(c.lib_stream));
@@ -370,7 +425,8 @@ int rngx_shutdown(void)
         RNGX_NOTE(hipEventDestroy(c.state_ready));
     if (c.lib_stream)
         RNGX_NOTE(hipStreamDestroy(c.lib_stream));
-    c.state_ready = nullptr;
+    c.state_ready = c.ready = nullptr;
+    c.on_default = false;
     c.lib_stream = nullptr;
     c.device = -1;
     return rc;
@@ -477,7 +533,9 @@ int rngx_profile_start(void)
     clear_error();
     if (!c.lib_stream)
         return set_error(RNGX_E_NOINIT, "rngx_profile_start called before rngx_init");
-    return prof::start(c.lib_stream);
+    const int rc = prof::start(c.lib_stream); // waits for what the log holds
+    c.ready = c.state_ready;
+    return rc;
 }
 
 int rngx_profile_reset(void) { return rngx_profile_start(); }

@@ -849,7 +849,7 @@ __global__ __launch_bounds__(256) void batch_upload_kernel(const u64x2 *__restri
 
 template <int S, int R, bool STAR>
 hipError_t launch_group_t(const BatchDesc *desc, const BatchTables &t, const rngx_batch_cfg &c,
-                          size_t lds_bytes, hipStream_t s)
+                          size_t lds_bytes, const LaunchAt &s)
 {
     uint64_t delta256 = 0;
     if (c.pace_gbs) {
@@ -857,14 +857,13 @@ hipError_t launch_group_t(const BatchDesc *desc, const BatchTables &t, const rng
         const double step_bytes = (double)c.blocks * c.waves_per_block * 64.0 * S * 8.0;
         delta256 = (uint64_t)(step_bytes / (c.pace_gbs * 1e9) * t.clock_khz * 1e3 * 256.0);
     }
-    batch_group_kernel<S, R, STAR><<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(
-        desc, t.jump, t.spread, t.group_nib, c.group, c.group_steps, delta256);
-    return hipGetLastError();
+    return launch_on(s, batch_group_kernel<S, R, STAR>, c.blocks, 64 * c.waves_per_block, lds_bytes,
+                     desc, t.jump, t.spread, t.group_nib, c.group, c.group_steps, delta256);
 }
 
 template <bool STAR>
 hipError_t launch_sweep(const BatchDesc *desc, const BatchTables &t, const rngx_batch_cfg &c,
-                        hipStream_t s)
+                        const LaunchAt &s)
 {
     constexpr size_t lds_bytes =
         (kSweepTable + (size_t)kSweepWaves * kSweepC) * sizeof(uint64_t); // 152 KiB
@@ -897,20 +896,19 @@ hipError_t launch_sweep(const BatchDesc *desc, const BatchTables &t, const rngx_
         const uint64_t n_groups = (n_tiles + kAnchorTiles - 1) / kAnchorTiles;
         const uint32_t per_wave = n_groups > 65536 ? 64 : 16;
         const uint64_t blocks = (n_groups + 4 * per_wave - 1) / (4 * per_wave);
-        batch_anchor_kernel<<<dim3((uint32_t)blocks), dim3(256), 0, s>>>(
-            desc, t.jump, t.anchor_spread, t.anchors, n_groups, per_wave);
-        const hipError_t e2 = hipGetLastError();
+        const hipError_t e2 = launch_on(s.stream, batch_anchor_kernel, (uint32_t)blocks, 256, 0,
+                                        desc, t.jump, t.anchor_spread, t.anchors, n_groups,
+                                        per_wave);
         if (e2 != hipSuccess)
             return e2;
     }
-    batch_sweep_kernel<STAR><<<dim3(c.blocks), dim3(64 * kSweepWaves), lds_bytes, s>>>(
-        desc, t.jump, t.sweep, t.anchors, n_tiles, delta256);
-    return hipGetLastError();
+    return launch_on(s, batch_sweep_kernel<STAR>, c.blocks, 64 * kSweepWaves, lds_bytes, desc,
+                     t.jump, t.sweep, t.anchors, n_tiles, delta256);
 }
 
 template <int S, bool STAR>
 hipError_t launch_batch_s(const BatchDesc *desc, const BatchTables &t, const rngx_batch_cfg &c,
-                          hipStream_t s)
+                          const LaunchAt &s)
 {
     const size_t lds_bytes =
         (kCarryTable + (size_t)c.waves_per_block * 64 * lds_row(c.row_values)) * sizeof(uint64_t);
@@ -918,27 +916,20 @@ hipError_t launch_batch_s(const BatchDesc *desc, const BatchTables &t, const rng
         return c.row_values == 8 ? launch_group_t<S, 8, STAR>(desc, t, c, lds_bytes, s)
                                  : launch_group_t<S, 16, STAR>(desc, t, c, lds_bytes, s);
     const uint32_t run = c.run_items ? c.run_items : 1;
-    if (c.row_values == 8)
-        batch_kernel<S, 8, STAR><<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(
-            desc, t.jump, t.spread, t.carry_nib, run, c.per_item);
-    else
-        batch_kernel<S, 16, STAR><<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(
-            desc, t.jump, t.spread, t.carry_nib, run, c.per_item);
-    return hipGetLastError();
+    return launch_on(s, c.row_values == 8 ? batch_kernel<S, 8, STAR> : batch_kernel<S, 16, STAR>,
+                     c.blocks, 64 * c.waves_per_block, lds_bytes, desc, t.jump, t.spread,
+                     t.carry_nib, run, c.per_item);
 }
 
 template <int S, bool STAR>
 hipError_t launch_batch_small_s(const SmallTable &tab, const BatchTables &t,
-                                const rngx_batch_cfg &c, hipStream_t s)
+                                const rngx_batch_cfg &c, const LaunchAt &s)
 {
     const size_t lds_bytes = (size_t)c.waves_per_block * 64 * lds_row(c.row_values) * 8;
-    if (c.row_values == 8)
-        batch_small_kernel<S, 8, STAR>
-            <<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(tab, t.jump, t.spread);
-    else
-        batch_small_kernel<S, 16, STAR>
-            <<<dim3(c.blocks), dim3(64 * c.waves_per_block), lds_bytes, s>>>(tab, t.jump, t.spread);
-    return hipGetLastError();
+    return launch_on(s,
+                     c.row_values == 8 ? batch_small_kernel<S, 8, STAR>
+                                       : batch_small_kernel<S, 16, STAR>,
+                     c.blocks, 64 * c.waves_per_block, lds_bytes, tab, t.jump, t.spread);
 }
 
 __global__ __launch_bounds__(256) void checksum_kernel(const uint64_t *__restrict__ d, uint64_t n,
@@ -1012,7 +1003,7 @@ hipError_t batch_group_occupancy(const rngx_batch_cfg &c, int *blocks_per_cu)
 
 template <bool STAR>
 hipError_t launch_batch_star(const rngx_batch_cfg &cfg, const BatchDesc *desc,
-                             const BatchTables &t, hipStream_t s)
+                             const BatchTables &t, const LaunchAt &s)
 {
     if (cfg.group == kSweepOrder)
         return launch_sweep<STAR>(desc, t, cfg, s);
@@ -1030,7 +1021,7 @@ hipError_t launch_batch_star(const rngx_batch_cfg &cfg, const BatchDesc *desc,
 
 template <bool STAR>
 hipError_t launch_batch_small_star(const rngx_batch_cfg &cfg, const SmallTable &tab,
-                                   const BatchTables &t, hipStream_t s)
+                                   const BatchTables &t, const LaunchAt &s)
 {
     switch (cfg.values_per_lane) {
     case 8: return launch_batch_small_s<8, STAR>(tab, t, cfg, s);
@@ -1045,14 +1036,14 @@ hipError_t launch_batch_small_star(const rngx_batch_cfg &cfg, const SmallTable &
 }
 
 hipError_t launch_batch(const rngx_batch_cfg &cfg, const BatchDesc *desc, const BatchTables &t,
-                        bool star, hipStream_t s)
+                        bool star, const LaunchAt &s)
 {
     return star ? launch_batch_star<true>(cfg, desc, t, s)
                 : launch_batch_star<false>(cfg, desc, t, s);
 }
 
 hipError_t launch_batch_small(const rngx_batch_cfg &cfg, const SmallTable &tab,
-                              const BatchTables &t, bool star, hipStream_t s)
+                              const BatchTables &t, bool star, const LaunchAt &s)
 {
     return star ? launch_batch_small_star<true>(cfg, tab, t, s)
                 : launch_batch_small_star<false>(cfg, tab, t, s);

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
 
 #include <cstdint>
 #include <mutex>
@@ -23,6 +24,38 @@ void clear_error();
         if (rngx_e_ != hipSuccess)                       \
             return ::rngx::hip_fail(rngx_e_, #call);     \
     } while (0)
+
+// ---- launches ---------------------------------------------------------------
+// Where a kernel is launched, and the event (if any) that its completion
+// signals. An event recorded behind the launch instead is a packet of its own,
+// which the stream's next kernel waits for: 2.9 us a launch.
+struct LaunchAt {
+    hipStream_t stream;
+    hipEvent_t done;
+    LaunchAt(hipStream_t s, hipEvent_t e = nullptr) : stream(s), done(e) {}
+};
+
+// Whether a caller captures `s` into a graph (the default stream never is).
+inline bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s && hipStreamIsCapturing(s, &st) != hipSuccess)
+        (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
+}
+
+template <typename P> struct Arg { using type = P; }; // keeps P out of deduction
+
+template <typename... P>
+hipError_t launch_on(const LaunchAt &at, void (*kernel)(P...), uint32_t grid, uint32_t block,
+                     size_t lds, const typename Arg<P>::type &...args)
+{
+    void *ptrs[] = {const_cast<void *>(static_cast<const void *>(&args))...};
+    const void *const f = reinterpret_cast<const void *>(kernel);
+    return at.done ? hipExtLaunchKernel(f, dim3(grid), dim3(block), ptrs, lds, at.stream, nullptr,
+                                        at.done, 0)
+                   : hipLaunchKernel(f, dim3(grid), dim3(block), ptrs, lds, at.stream);
+}
 
 // ---- the two hashes of the init kernel (host copies, used to fold the seed)
 // Listing S4, "low bits": six-round 32-bit integer hash.
@@ -277,9 +310,9 @@ rngx_batch_cfg current_batch_cfg();
 void release_server(); // serve.cpp: stop the server, free its resources
 int checksum_locked(const uint64_t *data, uint64_t n, hipStream_t s, uint64_t *result);
 hipError_t launch_batch(const rngx_batch_cfg &cfg, const BatchDesc *desc, const BatchTables &t,
-                        bool star, hipStream_t s);
+                        bool star, const LaunchAt &s);
 hipError_t launch_batch_small(const rngx_batch_cfg &cfg, const SmallTable &tab,
-                              const BatchTables &t, bool star, hipStream_t s);
+                              const BatchTables &t, bool star, const LaunchAt &s);
 // Staged table (device-mapped host address) -> device.
 hipError_t launch_batch_upload(const void *src_mapped, void *dst, size_t bytes, hipStream_t s);
 // Checksum sum_i data[i] * (2 i + 1) mod 2^64 into *acc (device, pre-zeroed).
@@ -313,7 +346,7 @@ void note_hip(hipError_t e, const char *what);
 void take_stray_error(const char *where);
 
 // ---- kernel launchers (kernels.hip) ---------------------------------------
-hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, hipStream_t s);
+hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, const LaunchAt &s);
 // How one plain launch covers its rows.
 struct GenPlan {
     rngx_launch cfg{};      // as configured, or narrowed for short rows
@@ -337,7 +370,7 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, c
 // when the plan is out of place.
 hipError_t launch_gen(const GenPlan &plan, const JumpPolys &polys, bool u32, bool star,
                       uint64_t *state, uint64_t *alt, uint32_t n, uint32_t iters, void *out,
-                      hipStream_t s);
+                      const LaunchAt &s);
 bool launch_cfg_valid(const rngx_launch &cfg);
 // copy.hip: device buffer -> page-locked host memory (device-mapped address).
 hipError_t launch_d2h(const void *src, void *dst_mapped, size_t bytes, uint32_t blocks,
@@ -353,10 +386,16 @@ struct Generator {
     uint64_t cursor = 0;
     uint64_t *state = nullptr;       // n states, library-owned device memory
     uint64_t *alt = nullptr;         // n more, once an out-of-place launch needs them
+    uint32_t cap = 0;                // states either buffer has room for
+    bool fixed = false;              // a graph holds `state`'s address: no launch leaves it
     JumpPolys polys{};               // for segments of polys_rows iterations
     uint32_t polys_rows = 0, polys_count = 0;
     hipStream_t lib_stream = nullptr; // the init kernel's stream
-    hipEvent_t state_ready = nullptr; // last use of `state` (any stream)
+    hipEvent_t state_ready = nullptr; // last use of `state` (any stream), unless logged
+    // The event that marks the last use: state_ready or, of a logged
+    // operation, the log's end event (valid until its window is restarted).
+    hipEvent_t ready = nullptr;
+    bool on_default = false; // that use was on the default stream
     rngx_launch cfg64{512, 2, 1, 7000}; // row-scheduled; see rngx_launch in rngx.h
     rngx_launch cfg32{0, 0, 0, 0};      // block 0: the library's choice (generate_locked)
     // Streams and events of the device-to-host pipeline (pipeline.cpp).
@@ -377,7 +416,7 @@ int generate_locked(Generator &g, uint32_t n_iters, void *out, hipStream_t s, bo
 // One launch of n_iters iterations in configuration `cfg`: the states are
 // advanced in g.state (which may be another buffer afterwards).
 hipError_t run_gen_locked(Generator &g, const rngx_launch &cfg, uint32_t n_iters, void *out,
-                          hipStream_t s, bool u32, bool star);
+                          const LaunchAt &s, bool u32, bool star);
 int check_device_locked(const Generator &g);
 void release_pipeline_locked(Generator &g);
 

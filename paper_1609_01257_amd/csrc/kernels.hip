@@ -538,14 +538,13 @@ gen_paced_kernel(const PacedArgs a, const Polys polys)
 
 template <typename T, int P, bool NT, bool AL, bool STAR>
 hipError_t launch_gen_t(uint32_t block, uint64_t *state, uint32_t n, uint32_t iters, T *out,
-                        hipStream_t s)
+                        const LaunchAt &s)
 {
     constexpr uint64_t WAVE_ITEMS = 64ull * P * Vec16<T>::E;
     const uint64_t waves = (n + WAVE_ITEMS - 1) / WAVE_ITEMS;
     const uint64_t blocks = (waves * 64 + block - 1) / block;
-    gen_kernel<T, P, NT, AL, STAR>
-        <<<dim3((uint32_t)blocks), dim3(block), 0, s>>>(state, n, iters, out);
-    return hipGetLastError();
+    return launch_on(s, gen_kernel<T, P, NT, AL, STAR>, (uint32_t)blocks, block, 0, state, n,
+                     iters, out);
 }
 
 // The scheduled launch: grid = every block that fits on the device at once
@@ -555,7 +554,7 @@ hipError_t launch_gen_t(uint32_t block, uint64_t *state, uint32_t n, uint32_t it
 template <typename T, int P, bool NT, bool STAR, bool SHIFT, typename Polys>
 hipError_t launch_paced_t(const GenPlan &plan, const Polys &polys, uint64_t *state,
                           uint64_t *state_out, uint32_t n, uint32_t iters, void *out,
-                          hipStream_t s)
+                          const LaunchAt &s)
 {
     const uint32_t block = plan.cfg.block, pace_gbs = plan.cfg.pace_gbs;
     constexpr uint32_t W = 64u * P * Vec16<T>::E;
@@ -627,14 +626,13 @@ hipError_t launch_paced_t(const GenPlan &plan, const Polys &polys, uint64_t *sta
     const double rows_per_us = ticks > 0 ? clock_khz * 1e-3 / ticks : 0.0;
     a.burst = rows_per_us > 8.0 ? 8u : rows_per_us > 1.0 ? (uint32_t)rows_per_us : 1u;
     a.delta256 = (uint64_t)(ticks * 256.0 * a.burst);
-    gen_paced_kernel<T, P, NT, STAR, SHIFT, Polys>
-        <<<dim3((uint32_t)grid), dim3(block), lds, s>>>(a, polys);
-    return hipGetLastError();
+    return launch_on(s, gen_paced_kernel<T, P, NT, STAR, SHIFT, Polys>, (uint32_t)grid, block, lds,
+                     a, polys);
 }
 
 template <typename T, int P, bool STAR, bool SHIFT, typename Polys>
 hipError_t launch_paced_nt(const GenPlan &plan, const Polys &polys, uint64_t *state, uint64_t *so,
-                           uint32_t n, uint32_t iters, T *out, hipStream_t s)
+                           uint32_t n, uint32_t iters, T *out, const LaunchAt &s)
 {
     return plan.cfg.nontemporal
                ? launch_paced_t<T, P, true, STAR, SHIFT>(plan, polys, state, so, n, iters, out, s)
@@ -644,7 +642,7 @@ hipError_t launch_paced_nt(const GenPlan &plan, const Polys &polys, uint64_t *st
 
 template <typename T, int P, bool STAR>
 hipError_t launch_gen_p(const GenPlan &plan, const JumpPolys &polys, uint64_t *state,
-                        uint64_t *alt, uint32_t n, uint32_t iters, T *out, hipStream_t s)
+                        uint64_t *alt, uint32_t n, uint32_t iters, T *out, const LaunchAt &s)
 {
     if (plan.scheduled) {
         uint64_t *const so = plan.out_of_place() ? alt : state;
@@ -673,7 +671,7 @@ hipError_t launch_gen_p(const GenPlan &plan, const JumpPolys &polys, uint64_t *s
 
 template <typename T, bool STAR>
 hipError_t launch_gen_typed(const GenPlan &plan, const JumpPolys &polys, uint64_t *state,
-                            uint64_t *alt, uint32_t n, uint32_t iters, T *out, hipStream_t s)
+                            uint64_t *alt, uint32_t n, uint32_t iters, T *out, const LaunchAt &s)
 {
     switch (plan.cfg.chunks) {
     case 1: return launch_gen_p<T, 1, STAR>(plan, polys, state, alt, n, iters, out, s);
@@ -691,14 +689,13 @@ bool launch_cfg_valid(const rngx_launch &cfg)
            (cfg.pace_gbs == 0 || (cfg.pace_gbs >= 1000 && cfg.pace_gbs <= 20000));
 }
 
-hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, hipStream_t s)
+hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, const LaunchAt &s)
 {
     const uint32_t block = 256;
     uint64_t blocks = ((uint64_t)n + block - 1) / block;
     if (blocks > 65536)
         blocks = 65536;
-    init_kernel<<<dim3((uint32_t)blocks), dim3(block), 0, s>>>(state, n, mix);
-    return hipGetLastError();
+    return launch_on(s, init_kernel, (uint32_t)blocks, block, 0, state, n, mix);
 }
 
 GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, const void *out)
@@ -759,7 +756,7 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, c
 
 hipError_t launch_gen(const GenPlan &plan, const JumpPolys &polys, bool u32, bool star,
                       uint64_t *state, uint64_t *alt, uint32_t n, uint32_t iters, void *out,
-                      hipStream_t s)
+                      const LaunchAt &s)
 {
     uint32_t *o32 = static_cast<uint32_t *>(out);
     uint64_t *o64 = static_cast<uint64_t *>(out);

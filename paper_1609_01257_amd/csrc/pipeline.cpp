@@ -6,8 +6,8 @@
 // Step k generates `iters_per_step` iterations into device buffer k % 2 on
 // the generation stream and copies it into host slot k % host_slots on the
 // copy stream. HIP events replace the paper's two semaphores:
-//   - the copy of step k waits for the generator's own state_ready event,
-//     recorded right after generation k;
+//   - the copy of step k waits for the generator's own event of its last use,
+//     which the end of generation k signals;
 //   - generation k waits for the end of the copy of step k - 2, which read
 //     the same device buffer: the profiler's end event of that copy when it
 //     was profiled, else `copy_done[k % 2]`.
@@ -245,9 +245,9 @@ extern "C" int rngx_stream_to_host(uint32_t n_steps, uint32_t iters_per_step, in
             drain();
             return rc;
         }
-        // generate_locked recorded state_ready on gs right after the kernel:
-        // it marks the generation's end, so no event of our own is queued.
-        PIPE_HIP(hipStreamWaitEvent(cs, g.state_ready, 0));
+        // The generator's event marks the end of the kernel on gs, so no event
+        // of our own is queued.
+        PIPE_HIP(hipStreamWaitEvent(cs, g.ready, 0));
         if (k == fail_at) {
             // Test hook: this step's copy "fails" before it is enqueued, as
             // a read error in the paper's communications thread would.

@@ -361,7 +361,7 @@ extern "C" int rngx_autotune_plain(uint32_t n_iters, int u32, void *out, uint32_
     }
     RNGX_HIP(hipEventCreate(&sc.e0));
     RNGX_HIP(hipEventCreate(&sc.e1));
-    RNGX_HIP(hipStreamWaitEvent(s, g.state_ready, 0));
+    RNGX_HIP(hipStreamWaitEvent(s, g.ready, 0));
     RNGX_HIP(hipMemcpyAsync(sc.snap, g.state, state_bytes, hipMemcpyDeviceToDevice, s));
 
     // The output checked as 64-bit words (a u32 output of odd length leaves
@@ -514,6 +514,7 @@ extern "C" int rngx_autotune_plain(uint32_t n_iters, int u32, void *out, uint32_
     if ((rc = restore()))
         return rc;
     RNGX_HIP(hipEventRecord(g.state_ready, s));
+    g.ready = g.state_ready;
     RNGX_HIP(hipStreamSynchronize(s));
     result->best_ms = best;
     result->best_gbs = ((double)out_bytes + 16.0 * g.n) / (best * 1e-3) / 1e9;

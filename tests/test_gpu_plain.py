@@ -562,3 +562,57 @@ def test_paths_with_and_without_a_second_state_buffer_alternate(oracle):
     exp = oracle.generate(seed, n, k)
     for at, iters, o in outs:
         assert np.array_equal(_u64(o).reshape(iters, n), exp[at:at + iters]), at
+
+
+# A captured call takes the states on at each replay, also between eager calls,
+# whose launches would otherwise leave them in another buffer.
+@pytest.mark.parametrize("logged", [False, True])
+@pytest.mark.parametrize("n", [4096, 4099, 1 << 16])
+def test_captured_call_goes_on_at_each_replay(oracle, logged, n):
+    iters, replays = 64, 4
+    rngx.profile_enable(logged)
+    try:
+        rngx.init(13, n)
+        out = torch.zeros(iters * n, dtype=torch.int64, device="cuda")
+        s, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        rngx.generate(iters, out)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=s):
+            rngx.generate(iters, out, stream=s)
+        got = [_u64(out).copy()]
+        for i in range(replays):
+            graph.replay()
+            torch.cuda.synchronize()
+            got.append(_u64(out).copy())
+            if i % 2:
+                rngx.generate(iters, out)
+                torch.cuda.synchronize()
+                got.append(_u64(out).copy())
+        exp = oracle.generate(13, n, iters * len(got))
+        assert np.array_equal(np.concatenate(got).reshape(-1, n), exp)
+    finally:
+        rngx.profile_enable(True)
+
+
+# Buffers kept from one generator to the next (the sizes rise and fall within a
+# factor of two and beyond), with the last use on the default or another stream.
+@pytest.mark.parametrize("logged", [False, True])
+def test_reseeding_waits_for_the_last_use_of_kept_buffers(oracle, logged):
+    rngx.profile_enable(logged)
+    try:
+        side, kept = torch.cuda.Stream(), []
+        for i, n in enumerate([20003, 20003, 15000, 20003, 9999, 4096, 8192, 8192, 50000, 25000]):
+            rngx.init(i, n)
+            s = side if i % 3 == 1 else None
+            out = torch.empty(200 * n, dtype=torch.int64, device="cuda")
+            if s is not None:
+                out.record_stream(s)
+                s.wait_stream(torch.cuda.current_stream())
+            for part in out.view(4, -1):
+                rngx.generate(50, part, **({"stream": s} if s is not None else {}))
+            kept.append((i, n, out))
+        torch.cuda.synchronize()
+        for i, n, out in kept:
+            assert np.array_equal(_u64(out).reshape(200, n), oracle.generate(i, n, 200)), (i, n)
+    finally:
+        rngx.profile_enable(True)
