@@ -328,12 +328,19 @@ static bool library_order(const rngx_batch_cfg &c)
 // 256 156 / 139, 2.4 GB in 512 415 / 368; the grouped order 66 / 68 / 114 /
 // 168 / 425 in this sequence). Requests shorter than an anchor's 8,192 values
 // cost both the same (850 MB in 100,000: 675 / 650, in both mostly staging).
+//
+// The items are written in half lines of 8 values up to 256 MiB, which the
+// caches put together: half the LDS, so that 32 wavefronts fit on a compute
+// unit instead of 16 (181 MB in 4,096 requests 54 us a call -> 50, 254 MB in
+// 512 50.5 -> 48.4, 62 MB in 256 the same). Beyond those caches half lines cost
+// more than that (462 MB in 40: 79 us in whole lines, 94 in halves).
 rngx_batch_cfg batch_order(const rngx_batch_cfg &c, uint64_t values, bool anchors)
 {
     if (!library_order(c))
         return c;
     if (values <= kItemOrderValues)
-        return rngx_batch_cfg{16, 4, 0, kUploadKernel, 16, 1, 1, 0, 0, 0};
+        return rngx_batch_cfg{16, 4, 0, kUploadKernel, values <= kItemOrderValues / 2 ? 8u : 16u,
+                              1, 1, 0, 0, 0};
     if (!anchors)
         return c;
     return rngx_batch_cfg{8, 4, 0, kUploadKernel, 8, 0, 0, kSweepOrder, 1, 7000};

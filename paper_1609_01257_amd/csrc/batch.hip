@@ -337,7 +337,7 @@ __global__ __launch_bounds__(256) void batch_kernel(const BatchDesc *__restrict_
                                                     const uint64_t *__restrict__ jump,
                                                     const uint64_t *__restrict__ spread,
                                                     const uint64_t *__restrict__ carry_nib,
-                                                    uint32_t run_items, uint32_t per_item)
+                                                    uint32_t run_items)
 {
     constexpr int LDS_ROW = lds_row(R);
     // Dynamic LDS: 64 * LDS_ROW u64 per wave, then the carry table (rows
@@ -349,12 +349,9 @@ __global__ __launch_bounds__(256) void batch_kernel(const BatchDesc *__restrict_
     const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint64_t *carry_tab = lds_dyn + (size_t)(blockDim.x >> 6) * 64 * LDS_ROW;
     uint64_t *lds = lds_dyn + (size_t)wid * 64 * LDS_ROW;
-    if (!per_item) {
-        // Only runs carry state; the barrier is uniform (per_item is).
-        for (uint32_t i = threadIdx.x; i < (uint32_t)kCarryTable; i += blockDim.x)
-            carry_tab[i] = carry_nib[i];
-        __syncthreads();
-    }
+    for (uint32_t i = threadIdx.x; i < (uint32_t)kCarryTable; i += blockDim.x)
+        carry_tab[i] = carry_nib[i];
+    __syncthreads();
 
     const uint64_t n_items = desc->n_items;
     const uint32_t m = desc->m;
@@ -375,18 +372,9 @@ __global__ __launch_bounds__(256) void batch_kernel(const BatchDesc *__restrict_
     uint32_t lo = 0;
     bool carry = false;
     uint64_t x = 0;
-    if (per_item) {
-        // One wave per work item: the grid covers the items exactly once.
-        item = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wid;
-        if (item >= n_items)
-            return;
-        run_end = item + 1;
-    }
     for (;;) {
         item = uniform64(item);
         if (item >= run_end) {
-            if (per_item)
-                break;
             uint64_t want = 1;
             if (run_items > 1) {
                 const uint64_t share = (n_items > seen ? n_items - seen : 0) / (2 * n_waves);
@@ -400,8 +388,7 @@ __global__ __launch_bounds__(256) void batch_kernel(const BatchDesc *__restrict_
             carry = false;
         }
         if (!carry) {
-            lo = per_item ? find_request(reqs, m, item, lane) : bisect_request(reqs, m, item);
-            lo = __builtin_amdgcn_readfirstlane(lo);
+            lo = __builtin_amdgcn_readfirstlane(bisect_request(reqs, m, item));
             req_end = uniform64(lo + 1 < m ? (uint64_t)reqs[lo + 1].item_begin : n_items);
         }
         const ItemReq r = load_req(reqs, lo);
@@ -416,6 +403,32 @@ __global__ __launch_bounds__(256) void batch_kernel(const BatchDesc *__restrict_
         carry = __builtin_amdgcn_readfirstlane(
                     (uint32_t)(full && item < run_end && item < req_end)) != 0;
     }
+}
+
+// One wave per work item: the grid covers the items exactly once. Apart from
+// the loop of batch_kernel, so that it takes half of that kernel's registers
+// (34-36, not 88) and eight wavefronts a SIMD. What bounds it is the chain of
+// loads before an item's first store, and above the caches the stores: two, four
+// or eight items in a run, each carried from the last, came out no faster (62 MB
+// in 256 requests 20.6 us alone, 21.4, 24.8 and 27.5 in runs; 797 MB 156, 149
+// with two).
+template <int S, int R, bool STAR>
+__global__ __launch_bounds__(256, 8) void batch_item_kernel(const BatchDesc *__restrict__ desc,
+                                                            const uint64_t *__restrict__ jump,
+                                                            const uint64_t *__restrict__ spread)
+{
+    extern __shared__ uint64_t lds_dyn[];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint64_t *lds = lds_dyn + (size_t)wid * 64 * lds_row(R);
+    const uint64_t item = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wid;
+    if (item >= desc->n_items)
+        return;
+    g_req *__restrict__ reqs = (g_req *)desc->reqs;
+    const ItemReq r = load_req(reqs, find_request(reqs, desc->m, item, lane));
+    uint64_t x = 0;
+    (void)process_item<S, R, STAR>(r, item, false, x, lds, nullptr, jump, spread,
+                                   (g_cu64 *)desc->states, lane);
 }
 
 // A full tile at virtual index T0 of a request whose output index 0 is at
@@ -915,10 +928,16 @@ hipError_t launch_batch_s(const BatchDesc *desc, const BatchTables &t, const rng
     if (c.group)
         return c.row_values == 8 ? launch_group_t<S, 8, STAR>(desc, t, c, lds_bytes, s)
                                  : launch_group_t<S, 16, STAR>(desc, t, c, lds_bytes, s);
+    if (c.per_item)
+        return launch_on(s,
+                         c.row_values == 8 ? batch_item_kernel<S, 8, STAR>
+                                           : batch_item_kernel<S, 16, STAR>,
+                         c.blocks, 64 * c.waves_per_block,
+                         lds_bytes - kCarryTable * sizeof(uint64_t), desc, t.jump, t.spread);
     const uint32_t run = c.run_items ? c.run_items : 1;
     return launch_on(s, c.row_values == 8 ? batch_kernel<S, 8, STAR> : batch_kernel<S, 16, STAR>,
                      c.blocks, 64 * c.waves_per_block, lds_bytes, desc, t.jump, t.spread,
-                     t.carry_nib, run, c.per_item);
+                     t.carry_nib, run);
 }
 
 template <int S, bool STAR>

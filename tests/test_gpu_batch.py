@@ -330,6 +330,26 @@ def test_library_order_small_batches(oracle, entry, m):
     assert np.array_equal(host[2:2 + r.total], exp)
 
 
+# Half lines up to 2^25 values, whole lines above, by both kernels of the order.
+@pytest.mark.parametrize("m,total", [(48, 1 << 25), (48, (1 << 25) + 1), (49, 1 << 25),
+                                     (49, (1 << 25) + 1)])
+def test_library_order_rows(oracle, m, total):
+    rng = np.random.default_rng(m)
+    lengths = np.full(m, total // (m + 2), dtype=np.uint64)
+    lengths[:8] = (1, 15, 16, 17, 1023, 1024, 1025, 0)
+    lengths[-1] = total - int(lengths[:-1].sum())
+    r = inputs.Requests(rng.integers(0, 2**64, m, dtype=np.uint64),
+                        rng.integers(0, 2**32, m, dtype=np.uint64).astype(np.uint32),
+                        rng.integers(0, 1000, m).astype(np.uint64), lengths)
+    assert r.total == total
+    out = torch.zeros(total + 9, dtype=torch.int64, device="cuda")
+    rngx.generate_batch(_reqs(r), out[2:2 + total])
+    torch.cuda.synchronize()
+    host = out.cpu().numpy().view(np.uint64)
+    assert not host[:2].any() and not host[2 + total:].any()
+    assert np.array_equal(host[2:2 + total], oracle.generate_batch(_oracle_reqs(oracle, r)))
+
+
 # Above 2^26 values: the sweep order. Tiles of 512 values, groups of 8,192
 # with an anchor where one request holds them whole: requests that end and
 # begin around both, runs of short requests between long ones, offsets that
