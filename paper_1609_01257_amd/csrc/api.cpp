@@ -210,7 +210,7 @@ int check_device_locked(const Generator &c)
 hipError_t run_gen_locked(Generator &c, const rngx_launch &cfg, uint32_t n_iters, void *out,
                           const LaunchAt &s, bool u32, bool star)
 {
-    GenPlan plan = plan_gen(cfg, u32, c.n, n_iters, out);
+    GenPlan plan = plan_gen(cfg, u32, star, c.n, n_iters, out);
     bool in_place = c.fixed;
     if (plan.out_of_place() && !c.alt && !in_place) {
         void *p = nullptr;

@@ -365,7 +365,8 @@ constexpr uint32_t kMaxSegs = 256;
 struct JumpPolys {
     uint64_t c[kMaxSegs];
 };
-GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, const void *out);
+GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32_t iters,
+                 const void *out);
 // alt: n more states, needed (and then holding the states after the launch)
 // when the plan is out of place.
 hipError_t launch_gen(const GenPlan &plan, const JumpPolys &polys, bool u32, bool star,

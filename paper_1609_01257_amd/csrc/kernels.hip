@@ -239,8 +239,8 @@ __global__ __launch_bounds__(1024) void gen_kernel(uint64_t *__restrict__ state,
 // (u64); below some 500 they cannot have enough stores under way. So the
 // iterations are cut into segments, each computed by its own blocks from the
 // states jumped ahead by T^(first row) (build_jump, jump_by); the blocks of
-// the last segment write the new states. 4,096 x 10,000 u64: 1,650 -> 63 us
-// (0.2 -> 5.2 TB/s), 65,536 x 1,000: 173 -> 80 us.
+// the last segment write the new states. 4,096 x 10,000 u64: 1,650 -> 55 us
+// (0.2 -> 6.0 TB/s), 65,536 x 1,000: 173 -> 80 us.
 //
 // In both, wavefronts read states that others advance, so the new states go
 // to another buffer.
@@ -698,7 +698,8 @@ hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, const La
     return launch_on(s, init_kernel, (uint32_t)blocks, block, 0, state, n, mix);
 }
 
-GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, const void *out)
+GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32_t iters,
+                 const void *out)
 {
     const uint64_t row = (uint64_t)n * (u32 ? 4 : 8), bytes = row * iters;
     const uintptr_t at = reinterpret_cast<uintptr_t>(out) | (iters > 1 ? row : 0);
@@ -707,21 +708,42 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, c
     p.cfg = cfg;
     p.seg_rows = iters;
     p.aligned16 = at % 16 == 0;
-    // Narrow rows, below 4 MiB: as configured they would leave wavefronts or
-    // whole compute units without work, so every lane takes one chunk and
-    // every block is small. Fewer than 512 wavefronts (a wavefront writes an
-    // aligned row in about 55 ns, so they fall short of the memory's rate)
-    // or 4096 (staged rows, about 220 ns each; stored word by word, 300 and
-    // more) and at least 64 iterations (24 off the lines; a segment's jump
-    // costs about 2.5 us): the iterations are cut into segments of at least 8. 4,096 x 10,000 u64: 63 us against 1,650 in one
-    // segment of 512 x 2; 65,536 x 64, one segment: 10.1 us against 11.7 in
-    // two and 16.1 with blocks of 512 x 2.
+    // Narrow rows, below 4 MiB (3 on the lines, where 3.4 MiB x 500 is as fast
+    // as configured, but for the heaviest steps): as configured they would leave
+    // wavefronts or whole compute units without work, so every lane takes one
+    // chunk and blocks are small.
+    // Too few wavefronts to fall in with the memory's rate, and at least 64
+    // iterations (24 off the lines; a segment's jump costs about 2.5 us): the
+    // iterations are cut into segments of at least 8.
+    //
+    // How many: an aligned row of 1 KiB takes a wavefront about 55 ns, and some
+    // 525 of them hold the rate; 800 where its words are 4 bytes, twice the
+    // steps, or scrambled, 900 where both; staged, a row takes 220 ns and
+    // more. More segments than that are more places written at once, which the
+    // memory takes more slowly (4,096 x 10,000 u64: 54 us in 16 segments, 60
+    // in 32, 68 in 128, 1,650 in one of 512 x 2; 12,800 x 3,276: 53 in 5, 62 in
+    // 6; 65,536 x 640: 51 in two, 63 in one; scrambled 4,096 x 10,000: 73 in
+    // 16, 53 in 24, 61 in 32; u32 51,200 x 1,638: 66 in 3, 68 in 5). Outputs
+    // that the Infinity Cache takes wait for the rows alone, and run at 1,024
+    // (4,096 x 1,000: 9.6 us, 11.4 in half as many); unaligned, they are better
+    // off word by word where one segment keeps the device busy (262,273 x 99
+    // u64: 34 us, 40 in two staged ones; 65,537 x 399: 65 and 44 in three).
     const uint64_t waves = (row + 1023) / 1024;
-    const bool narrow = cfg.pace_gbs && iters >= 2 && waves < 4096;
+    const bool heaviest = u32 && star, heavy = u32 || star;
+    const bool narrow =
+        cfg.pace_gbs && iters >= 2 && waves < (lines && !heaviest ? 3072u : 4096u);
+    const bool cached = bytes <= kCacheBytes * 3 / 4;
     if (narrow && iters >= (lines ? 64u : 24u)) {
-        const uint64_t target = lines ? (waves < 512 ? 1024 : 1) : 4096;
-        const uint64_t segs =
-            std::min<uint64_t>({(target + waves / 2) / waves, iters / 8, kMaxSegs});
+        uint64_t segs = 1;
+        if (!lines && !(bytes <= kCacheBytes && waves >= (heavy ? 1800u : 768u)))
+            segs = ((u32 && !cached && waves >= 200 && waves < 1600 ? 6144 : 4096) + waves / 2) /
+                   waves;
+        else if (lines && cached && waves < 512)
+            segs = (1024 + waves / 2) / waves;
+        else if (lines && !cached && waves < 768)
+            segs = std::max<uint64_t>(
+                2, ((heaviest ? 900 : heavy ? 800 : 525) + waves / 2) / waves);
+        segs = std::min<uint64_t>({segs, iters / 8, kMaxSegs});
         if (segs > 1) {
             p.seg_rows = (uint32_t)((iters + segs - 1) / segs);
             p.segs = (iters + p.seg_rows - 1) / p.seg_rows;
@@ -743,13 +765,26 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, uint32_t n, uint32_t iters, c
     const bool few = !p.shift && !narrow && row / n * iters <= (mid ? 48u : 32u);
     p.scheduled = p.shift || (cfg.pace_gbs && iters >= 2 && p.aligned16 && !few);
     if (narrow && p.scheduled) {
+        // From 1,536 wavefronts blocks of 512 (262,144 x 1,000 u64: 303 us,
+        // 322 with 256; below, 102,400 x 1,000 u32: 122 with 256, 131).
         p.cfg.chunks = 1;
-        p.cfg.block = std::min(cfg.block, 256u);
+        p.cfg.block =
+            std::min(cfg.block, lines && !cached && !heaviest && waves >= 1536 ? 512u : 256u);
         // Outputs well inside that cache run ahead of HBM's rate, so a
         // schedule only holds them back (131,072 x 100 u64: 5.25 TB/s free,
         // below 5.1 scheduled; 65,536 x 1,000: 5.5 free, 6.5 scheduled).
-        if (bytes <= kCacheBytes * 3 / 4)
+        // Many staged segments: a rate that they hold, 6/7 or 13/14 of the
+        // configured one, above which they fall behind for good (at 6,000,
+        // 6,500 and 7,000 GB/s: 16,387 x 10,000 u64, 32 segments, 230, 214,
+        // 264 us; 4,099 x 10,000, 124, 66, 73, 79; 131,073 x 2,000, 4, 354,
+        // 327, 308; 65,537 x 1,000 u32, 24, 48, 52, 54; 131,073 x 2,000 u32,
+        // 12, 179, 166, 189).
+        if (cached)
             p.cfg.pace_gbs = 0;
+        else if (!lines && p.segs >= (u32 ? 20u : 64u))
+            p.cfg.pace_gbs = cfg.pace_gbs * 6 / 7;
+        else if (!lines && p.segs >= (u32 ? 2u : 6u))
+            p.cfg.pace_gbs = cfg.pace_gbs * 13 / 14;
     }
     return p;
 }

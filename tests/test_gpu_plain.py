@@ -516,6 +516,24 @@ def test_staged_rows(oracle, u32, n, offset):
     assert c == iters + 1 and np.array_equal(st, oracle.generate(6, n, 1, cursor=c).ravel())
 
 
+# Short rows of outputs above 192 MiB: segments on a schedule, one segment of
+# small and of large blocks, on the lines and off them.
+@pytest.mark.parametrize("u32,n,iters", [(False, 4096, 6200), (False, 4099, 6200),
+                                         (False, 65536, 400), (False, 114688, 230),
+                                         (False, 262144, 100), (False, 262147, 130),
+                                         (True, 4099, 12400), (True, 65537, 780),
+                                         (True, 131072, 400), (True, 600001, 115)])
+@pytest.mark.parametrize("scrambled", [False, True])
+def test_scheduled_short_rows(oracle, scrambled, u32, n, iters):
+    rngx.set_scrambler(rngx.SCRAMBLE_STAR if scrambled else rngx.SCRAMBLE_NONE)
+    try:
+        got = run(21, n, iters, u32=u32)
+    finally:
+        rngx.set_scrambler(rngx.SCRAMBLE_NONE)
+    want = getattr(oracle, "generate" + ("_star" if scrambled else "") + ("_u32" if u32 else ""))
+    assert np.array_equal(got, want(21, n, iters))
+
+
 def test_scrambled_segments_and_staged_rows(oracle, star):
     for u32, n, iters in [(False, 4099, 100), (True, 4099, 100), (True, 8192, 100),
                           (True, (1 << 23) + 1, 9)]:
