@@ -716,10 +716,10 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     // iterations (24 off the lines; a segment's jump costs about 2.5 us): the
     // iterations are cut into segments of at least 8.
     //
-    // How many: an aligned row of 1 KiB takes a wavefront about 55 ns, and some
-    // 525 of them hold the rate; 800 where its words are 4 bytes, twice the
-    // steps, or scrambled, 900 where both; staged, a row takes 220 ns and
-    // more. More segments than that are more places written at once, which the
+    // How many: an aligned row of 1 KiB takes a wavefront about 55 ns, and at
+    // least 480 of them hold the rate; about 755 where its words are 4 bytes,
+    // twice the steps, or scrambled, 900 where both; staged, a row takes 220 ns
+    // and more. More segments than that are more places written at once, which the
     // memory takes more slowly (4,096 x 10,000 u64: 54 us in 16 segments, 60
     // in 32, 68 in 128, 1,650 in one of 512 x 2; 12,800 x 3,276: 53 in 5, 62 in
     // 6; 65,536 x 640: 51 in two, 63 in one; scrambled 4,096 x 10,000: 73 in
@@ -741,8 +741,8 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
         else if (lines && cached && waves < 512)
             segs = (1024 + waves / 2) / waves;
         else if (lines && !cached && waves < 768)
-            segs = std::max<uint64_t>(
-                2, ((heaviest ? 900 : heavy ? 800 : 525) + waves / 2) / waves);
+            segs = std::max<uint64_t>(2, heavy ? ((heaviest ? 900 : 755) + waves / 2) / waves
+                                               : (480 + waves - 1) / waves);
         segs = std::min<uint64_t>({segs, iters / 8, kMaxSegs});
         if (segs > 1) {
             p.seg_rows = (uint32_t)((iters + segs - 1) / segs);
@@ -773,14 +773,18 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
         // Outputs well inside that cache run ahead of HBM's rate, so a
         // schedule only holds them back (131,072 x 100 u64: 5.25 TB/s free,
         // below 5.1 scheduled; 65,536 x 1,000: 5.5 free, 6.5 scheduled).
-        // Many staged segments: a rate that they hold, 6/7 or 13/14 of the
-        // configured one, above which they fall behind for good (at 6,000,
-        // 6,500 and 7,000 GB/s: 16,387 x 10,000 u64, 32 segments, 230, 214,
-        // 264 us; 4,099 x 10,000, 124, 66, 73, 79; 131,073 x 2,000, 4, 354,
-        // 327, 308; 65,537 x 1,000 u32, 24, 48, 52, 54; 131,073 x 2,000 u32,
-        // 12, 179, 166, 189).
+        // Many segments: a rate that they hold, 6/7, 13/14 or, of heavier
+        // steps on the lines, 27/28 of the configured one, above which they fall behind for good
+        // (at 6,000, 6,500 and 7,000 GB/s: 16,387 x 10,000 u64, 32 segments,
+        // 230, 214, 264 us; 4,099 x 10,000, 124, 66, 73, 79; 131,073 x 2,000,
+        // 4, 354, 327, 308; 65,537 x 1,000 u32, 24, 48, 52, 54; 131,073 x
+        // 2,000 u32, 12, 179, 166, 189; aligned, at 6,500, 6,750 and 7,000:
+        // 25,600 x 6,553 u32, 8, 107, 106, 123; 32,768 x 5,120, 6, 107, 104,
+        // 104; scrambled u64 12,800 x 6,553, 8, 107, 104, 116).
         if (cached)
             p.cfg.pace_gbs = 0;
+        else if (lines && heavy && p.segs > 1)
+            p.cfg.pace_gbs = cfg.pace_gbs * 27 / 28;
         else if (!lines && p.segs >= (u32 ? 20u : 64u))
             p.cfg.pace_gbs = cfg.pace_gbs * 6 / 7;
         else if (!lines && p.segs >= (u32 ? 2u : 6u))
