@@ -3,11 +3,13 @@
 // One process-wide context (Generator, internal.h) holds the library-owned
 // state buffer, the library's own stream (for the init kernel) and the
 // event, `ready`, that orders every use of the state across caller streams: a
-// generate call makes its stream wait for it and launches, and the launch's
-// completion is the next one. The launch itself signals `state_ready`: a marker
-// recorded behind it would hold the stream for 3 us (a 5 us kernel in a row of
-// calls, with its wait and record: 8.9 us a call, with the event in the launch
-// 6.0). A logged call has an end event already and lends that.
+// generate call makes its stream wait for it, launches and records the next
+// one. A logged call has recorded its end event already, and lends that: a
+// record more holds the stream for 3 us (18 us a call of 5 us in a row of such,
+// 15 without). The event stays a record behind the launch: as the launch's own
+// (hipExtLaunchKernel) a row of calls gains 0.3 us each (4,096 x 100: 8.4 and
+// 8.1), but a call that finds the device idle takes the host 7 us more (20.7
+// and 27.8 until the device is done).
 #include <algorithm>
 #include <atomic>
 #include <cstdarg>
@@ -175,13 +177,13 @@ int fresh_state_locked(Generator &c, uint32_t n_states, const char *who, bool on
     return prof::start(c.lib_stream);
 }
 
-// The event of the states' last use, launched on s: state_ready, which that
-// launch signals (marked), or the log's end event, else state_ready recorded.
-int mark_use_locked(Generator &c, bool marked, hipEvent_t logged, hipStream_t s)
+// The event of the states' last use, launched on s: the log's end event, else
+// state_ready, recorded here.
+int mark_use_locked(Generator &c, hipEvent_t logged, hipStream_t s)
 {
     c.ready = logged ? logged : c.state_ready;
     c.on_default = s == nullptr;
-    if (!marked && !logged)
+    if (!logged)
         RNGX_HIP(hipEventRecord(c.state_ready, s));
     return RNGX_OK;
 }
@@ -208,7 +210,7 @@ int check_device_locked(const Generator &c)
 }
 
 hipError_t run_gen_locked(Generator &c, const rngx_launch &cfg, uint32_t n_iters, void *out,
-                          const LaunchAt &s, bool u32, bool star)
+                          hipStream_t s, bool u32, bool star)
 {
     GenPlan plan = plan_gen(cfg, u32, star, c.n, n_iters, out);
     bool in_place = c.fixed;
@@ -276,13 +278,12 @@ int generate_locked(Generator &c, uint32_t n_iters, void *out, hipStream_t s, bo
         cfg = rngx_launch{512, 2, 1, 7000};
     }
     take_stray_error("before the rng kernel launch");
-    const bool mark = tok < 0 && !captured;
-    hipError_t e = run_gen_locked(c, cfg, n_iters, out, LaunchAt(s, mark ? c.state_ready : nullptr),
-                                  u32, current_scrambler() == RNGX_SCRAMBLE_STAR);
+    hipError_t e = run_gen_locked(c, cfg, n_iters, out, s, u32,
+                                  current_scrambler() == RNGX_SCRAMBLE_STAR);
     hipEvent_t logged = prof::end_event(tok, s);
     if (e != hipSuccess)
         return hip_fail(e, "rng kernel launch");
-    if ((rc = mark_use_locked(c, mark, captured ? nullptr : logged, s)))
+    if ((rc = mark_use_locked(c, captured ? nullptr : logged, s)))
         return rc;
     c.cursor += n_iters;
     return RNGX_OK;
@@ -324,12 +325,11 @@ int rngx_init(uint64_t seed, uint32_t n_states)
     hipStream_t s = on_default ? nullptr : c.lib_stream;
     const int tok = prof::begin("INIT_KERNEL", s);
     take_stray_error("before the init kernel launch");
-    hipError_t e = launch_init(c.state, n_states, seed_mix(seed),
-                               LaunchAt(s, tok < 0 ? c.state_ready : nullptr));
+    hipError_t e = launch_init(c.state, n_states, seed_mix(seed), s);
     hipEvent_t logged = prof::end_event(tok, s);
     if (e != hipSuccess)
         return hip_fail(e, "init kernel launch");
-    if ((rc = mark_use_locked(c, tok < 0, logged, s)))
+    if ((rc = mark_use_locked(c, logged, s)))
         return rc;
     c.seed = seed;
     c.n = n_states;

@@ -588,11 +588,6 @@ int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipSt
     tabs.v_end = slot.v_end;
     const BatchDesc *ddesc = static_cast<const BatchDesc *>(slot.devtab);
     const int tok = prof::begin(prof_name, stream);
-    // A batch that ends in a launch of its own marks the slot's event with
-    // that launch's completion, unless the log's end event comes in between or
-    // a graph takes the launch.
-    const bool mark = cfg.use_graph != 1 && tok < 0 && !capturing(stream);
-    const LaunchAt at(stream, mark ? slot.done : nullptr);
     if (cfg.use_graph == 1) {
         const bool same = slot.exec && slot.exec_cfg.values_per_lane == cfg.values_per_lane &&
                           slot.exec_cfg.waves_per_block == cfg.waves_per_block &&
@@ -647,7 +642,7 @@ int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipSt
         std::memcpy(st.reqs, static_cast<const char *>(slot.staging) + kReqOffset,
                     (size_t)slot.m_staged * sizeof(BatchReq));
         take_stray_error("before the batch kernel launch");
-        hipError_t e = launch_batch_small(cfg, st, tabs, star, at);
+        hipError_t e = launch_batch_small(cfg, st, tabs, star, stream);
         if (e != hipSuccess)
             return hip_fail(e, "batch kernel launch");
     } else {
@@ -658,13 +653,12 @@ int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipSt
         else
             RNGX_HIP(hipMemcpyAsync(slot.devtab, slot.staging, bytes, hipMemcpyHostToDevice,
                                     stream));
-        hipError_t e = launch_batch(cfg, ddesc, tabs, star, at);
+        hipError_t e = launch_batch(cfg, ddesc, tabs, star, stream);
         if (e != hipSuccess)
             return hip_fail(e, "batch kernel launch");
     }
     prof::end(tok, stream);
-    if (!mark)
-        RNGX_HIP(hipEventRecord(slot.done, stream));
+    RNGX_HIP(hipEventRecord(slot.done, stream));
     return RNGX_OK;
 }
 

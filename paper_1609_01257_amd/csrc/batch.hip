@@ -862,7 +862,7 @@ __global__ __launch_bounds__(256) void batch_upload_kernel(const u64x2 *__restri
 
 template <int S, int R, bool STAR>
 hipError_t launch_group_t(const BatchDesc *desc, const BatchTables &t, const rngx_batch_cfg &c,
-                          size_t lds_bytes, const LaunchAt &s)
+                          size_t lds_bytes, hipStream_t s)
 {
     uint64_t delta256 = 0;
     if (c.pace_gbs) {
@@ -876,7 +876,7 @@ hipError_t launch_group_t(const BatchDesc *desc, const BatchTables &t, const rng
 
 template <bool STAR>
 hipError_t launch_sweep(const BatchDesc *desc, const BatchTables &t, const rngx_batch_cfg &c,
-                        const LaunchAt &s)
+                        hipStream_t s)
 {
     constexpr size_t lds_bytes =
         (kSweepTable + (size_t)kSweepWaves * kSweepC) * sizeof(uint64_t); // 152 KiB
@@ -909,7 +909,7 @@ hipError_t launch_sweep(const BatchDesc *desc, const BatchTables &t, const rngx_
         const uint64_t n_groups = (n_tiles + kAnchorTiles - 1) / kAnchorTiles;
         const uint32_t per_wave = n_groups > 65536 ? 64 : 16;
         const uint64_t blocks = (n_groups + 4 * per_wave - 1) / (4 * per_wave);
-        const hipError_t e2 = launch_on(s.stream, batch_anchor_kernel, (uint32_t)blocks, 256, 0,
+        const hipError_t e2 = launch_on(s, batch_anchor_kernel, (uint32_t)blocks, 256, 0,
                                         desc, t.jump, t.anchor_spread, t.anchors, n_groups,
                                         per_wave);
         if (e2 != hipSuccess)
@@ -921,7 +921,7 @@ hipError_t launch_sweep(const BatchDesc *desc, const BatchTables &t, const rngx_
 
 template <int S, bool STAR>
 hipError_t launch_batch_s(const BatchDesc *desc, const BatchTables &t, const rngx_batch_cfg &c,
-                          const LaunchAt &s)
+                          hipStream_t s)
 {
     const size_t lds_bytes =
         (kCarryTable + (size_t)c.waves_per_block * 64 * lds_row(c.row_values)) * sizeof(uint64_t);
@@ -942,7 +942,7 @@ hipError_t launch_batch_s(const BatchDesc *desc, const BatchTables &t, const rng
 
 template <int S, bool STAR>
 hipError_t launch_batch_small_s(const SmallTable &tab, const BatchTables &t,
-                                const rngx_batch_cfg &c, const LaunchAt &s)
+                                const rngx_batch_cfg &c, hipStream_t s)
 {
     const size_t lds_bytes = (size_t)c.waves_per_block * 64 * lds_row(c.row_values) * 8;
     return launch_on(s,
@@ -1022,7 +1022,7 @@ hipError_t batch_group_occupancy(const rngx_batch_cfg &c, int *blocks_per_cu)
 
 template <bool STAR>
 hipError_t launch_batch_star(const rngx_batch_cfg &cfg, const BatchDesc *desc,
-                             const BatchTables &t, const LaunchAt &s)
+                             const BatchTables &t, hipStream_t s)
 {
     if (cfg.group == kSweepOrder)
         return launch_sweep<STAR>(desc, t, cfg, s);
@@ -1040,7 +1040,7 @@ hipError_t launch_batch_star(const rngx_batch_cfg &cfg, const BatchDesc *desc,
 
 template <bool STAR>
 hipError_t launch_batch_small_star(const rngx_batch_cfg &cfg, const SmallTable &tab,
-                                   const BatchTables &t, const LaunchAt &s)
+                                   const BatchTables &t, hipStream_t s)
 {
     switch (cfg.values_per_lane) {
     case 8: return launch_batch_small_s<8, STAR>(tab, t, cfg, s);
@@ -1055,14 +1055,14 @@ hipError_t launch_batch_small_star(const rngx_batch_cfg &cfg, const SmallTable &
 }
 
 hipError_t launch_batch(const rngx_batch_cfg &cfg, const BatchDesc *desc, const BatchTables &t,
-                        bool star, const LaunchAt &s)
+                        bool star, hipStream_t s)
 {
     return star ? launch_batch_star<true>(cfg, desc, t, s)
                 : launch_batch_star<false>(cfg, desc, t, s);
 }
 
 hipError_t launch_batch_small(const rngx_batch_cfg &cfg, const SmallTable &tab,
-                              const BatchTables &t, bool star, const LaunchAt &s)
+                              const BatchTables &t, bool star, hipStream_t s)
 {
     return star ? launch_batch_small_star<true>(cfg, tab, t, s)
                 : launch_batch_small_star<false>(cfg, tab, t, s);

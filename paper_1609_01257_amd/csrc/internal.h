@@ -2,7 +2,6 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
-#include <hip/hip_ext.h>
 
 #include <cstdint>
 #include <mutex>
@@ -26,15 +25,6 @@ void clear_error();
     } while (0)
 
 // ---- launches ---------------------------------------------------------------
-// Where a kernel is launched, and the event (if any) that its completion
-// signals. An event recorded behind the launch instead is a packet of its own,
-// which the stream's next kernel waits for: 2.9 us a launch.
-struct LaunchAt {
-    hipStream_t stream;
-    hipEvent_t done;
-    LaunchAt(hipStream_t s, hipEvent_t e = nullptr) : stream(s), done(e) {}
-};
-
 // Whether a caller captures `s` into a graph (the default stream never is).
 inline bool capturing(hipStream_t s)
 {
@@ -46,15 +36,14 @@ inline bool capturing(hipStream_t s)
 
 template <typename P> struct Arg { using type = P; }; // keeps P out of deduction
 
+// A kernel launch that returns its own error.
 template <typename... P>
-hipError_t launch_on(const LaunchAt &at, void (*kernel)(P...), uint32_t grid, uint32_t block,
-                     size_t lds, const typename Arg<P>::type &...args)
+hipError_t launch_on(hipStream_t s, void (*kernel)(P...), uint32_t grid, uint32_t block, size_t lds,
+                     const typename Arg<P>::type &...args)
 {
     void *ptrs[] = {const_cast<void *>(static_cast<const void *>(&args))...};
-    const void *const f = reinterpret_cast<const void *>(kernel);
-    return at.done ? hipExtLaunchKernel(f, dim3(grid), dim3(block), ptrs, lds, at.stream, nullptr,
-                                        at.done, 0)
-                   : hipLaunchKernel(f, dim3(grid), dim3(block), ptrs, lds, at.stream);
+    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(block), ptrs,
+                           lds, s);
 }
 
 // ---- the two hashes of the init kernel (host copies, used to fold the seed)
@@ -310,9 +299,9 @@ rngx_batch_cfg current_batch_cfg();
 void release_server(); // serve.cpp: stop the server, free its resources
 int checksum_locked(const uint64_t *data, uint64_t n, hipStream_t s, uint64_t *result);
 hipError_t launch_batch(const rngx_batch_cfg &cfg, const BatchDesc *desc, const BatchTables &t,
-                        bool star, const LaunchAt &s);
+                        bool star, hipStream_t s);
 hipError_t launch_batch_small(const rngx_batch_cfg &cfg, const SmallTable &tab,
-                              const BatchTables &t, bool star, const LaunchAt &s);
+                              const BatchTables &t, bool star, hipStream_t s);
 // Staged table (device-mapped host address) -> device.
 hipError_t launch_batch_upload(const void *src_mapped, void *dst, size_t bytes, hipStream_t s);
 // Checksum sum_i data[i] * (2 i + 1) mod 2^64 into *acc (device, pre-zeroed).
@@ -346,7 +335,7 @@ void note_hip(hipError_t e, const char *what);
 void take_stray_error(const char *where);
 
 // ---- kernel launchers (kernels.hip) ---------------------------------------
-hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, const LaunchAt &s);
+hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, hipStream_t s);
 // How one plain launch covers its rows.
 struct GenPlan {
     rngx_launch cfg{};      // as configured, or narrowed for short rows
@@ -371,7 +360,7 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
 // when the plan is out of place.
 hipError_t launch_gen(const GenPlan &plan, const JumpPolys &polys, bool u32, bool star,
                       uint64_t *state, uint64_t *alt, uint32_t n, uint32_t iters, void *out,
-                      const LaunchAt &s);
+                      hipStream_t s);
 bool launch_cfg_valid(const rngx_launch &cfg);
 // copy.hip: device buffer -> page-locked host memory (device-mapped address).
 hipError_t launch_d2h(const void *src, void *dst_mapped, size_t bytes, uint32_t blocks,
@@ -417,7 +406,7 @@ int generate_locked(Generator &g, uint32_t n_iters, void *out, hipStream_t s, bo
 // One launch of n_iters iterations in configuration `cfg`: the states are
 // advanced in g.state (which may be another buffer afterwards).
 hipError_t run_gen_locked(Generator &g, const rngx_launch &cfg, uint32_t n_iters, void *out,
-                          const LaunchAt &s, bool u32, bool star);
+                          hipStream_t s, bool u32, bool star);
 int check_device_locked(const Generator &g);
 void release_pipeline_locked(Generator &g);
 

@@ -538,7 +538,7 @@ gen_paced_kernel(const PacedArgs a, const Polys polys)
 
 template <typename T, int P, bool NT, bool AL, bool STAR>
 hipError_t launch_gen_t(uint32_t block, uint64_t *state, uint32_t n, uint32_t iters, T *out,
-                        const LaunchAt &s)
+                        hipStream_t s)
 {
     constexpr uint64_t WAVE_ITEMS = 64ull * P * Vec16<T>::E;
     const uint64_t waves = (n + WAVE_ITEMS - 1) / WAVE_ITEMS;
@@ -554,7 +554,7 @@ hipError_t launch_gen_t(uint32_t block, uint64_t *state, uint32_t n, uint32_t it
 template <typename T, int P, bool NT, bool STAR, bool SHIFT, typename Polys>
 hipError_t launch_paced_t(const GenPlan &plan, const Polys &polys, uint64_t *state,
                           uint64_t *state_out, uint32_t n, uint32_t iters, void *out,
-                          const LaunchAt &s)
+                          hipStream_t s)
 {
     const uint32_t block = plan.cfg.block, pace_gbs = plan.cfg.pace_gbs;
     constexpr uint32_t W = 64u * P * Vec16<T>::E;
@@ -632,7 +632,7 @@ hipError_t launch_paced_t(const GenPlan &plan, const Polys &polys, uint64_t *sta
 
 template <typename T, int P, bool STAR, bool SHIFT, typename Polys>
 hipError_t launch_paced_nt(const GenPlan &plan, const Polys &polys, uint64_t *state, uint64_t *so,
-                           uint32_t n, uint32_t iters, T *out, const LaunchAt &s)
+                           uint32_t n, uint32_t iters, T *out, hipStream_t s)
 {
     return plan.cfg.nontemporal
                ? launch_paced_t<T, P, true, STAR, SHIFT>(plan, polys, state, so, n, iters, out, s)
@@ -642,7 +642,7 @@ hipError_t launch_paced_nt(const GenPlan &plan, const Polys &polys, uint64_t *st
 
 template <typename T, int P, bool STAR>
 hipError_t launch_gen_p(const GenPlan &plan, const JumpPolys &polys, uint64_t *state,
-                        uint64_t *alt, uint32_t n, uint32_t iters, T *out, const LaunchAt &s)
+                        uint64_t *alt, uint32_t n, uint32_t iters, T *out, hipStream_t s)
 {
     if (plan.scheduled) {
         uint64_t *const so = plan.out_of_place() ? alt : state;
@@ -671,7 +671,7 @@ hipError_t launch_gen_p(const GenPlan &plan, const JumpPolys &polys, uint64_t *s
 
 template <typename T, bool STAR>
 hipError_t launch_gen_typed(const GenPlan &plan, const JumpPolys &polys, uint64_t *state,
-                            uint64_t *alt, uint32_t n, uint32_t iters, T *out, const LaunchAt &s)
+                            uint64_t *alt, uint32_t n, uint32_t iters, T *out, hipStream_t s)
 {
     switch (plan.cfg.chunks) {
     case 1: return launch_gen_p<T, 1, STAR>(plan, polys, state, alt, n, iters, out, s);
@@ -689,7 +689,7 @@ bool launch_cfg_valid(const rngx_launch &cfg)
            (cfg.pace_gbs == 0 || (cfg.pace_gbs >= 1000 && cfg.pace_gbs <= 20000));
 }
 
-hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, const LaunchAt &s)
+hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, hipStream_t s)
 {
     const uint32_t block = 256;
     uint64_t blocks = ((uint64_t)n + block - 1) / block;
@@ -795,7 +795,7 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
 
 hipError_t launch_gen(const GenPlan &plan, const JumpPolys &polys, bool u32, bool star,
                       uint64_t *state, uint64_t *alt, uint32_t n, uint32_t iters, void *out,
-                      const LaunchAt &s)
+                      hipStream_t s)
 {
     uint32_t *o32 = static_cast<uint32_t *>(out);
     uint64_t *o64 = static_cast<uint64_t *>(out);
