@@ -165,17 +165,20 @@ int rngx_hip_notes(uint64_t *released, uint64_t *stray, char *text, size_t cap, 
  *         ahead of the schedule wait; those behind run freely, so the grid
  *         moves down the rows together instead of drifting apart (each wait
  *         is bounded; the schedule never changes a value). Used for calls of
- *         at least 2 iterations. With a schedule, a call whose rows are
- *         shorter than 4 MiB runs with one chunk and blocks of at most 256,
- *         its iterations cut into segments that run side by side where the
- *         rows alone would not fill the device, and without waits if its
- *         output stays below 192 MiB.
+ *         at least 2 iterations, but not for the few (up to 32 bytes of
+ *         output per stream, 48 at some sizes) of long rows. With a schedule,
+ *         a call whose rows are shorter than 4 MiB (3 MiB on 128-byte lines)
+ *         runs with one chunk and blocks of at most 256 or 512, its iterations
+ *         cut into segments that run side by side, at up to a seventh less
+ *         than the rate, where the rows alone would not fill the device, and
+ *         without waits if its output stays below 192 MiB.
  * Rows that do not start on 128-byte lines (an odd or ragged n_states, an
  * output offset) are staged through LDS into whole lines when the output is
  * larger than 256 MiB or cut into segments, with at most 2 chunks. Staged
  * rows and segments keep a second buffer of 8 * n_states bytes from the first
- * such call to the next rngx_init, rngx_set_state or rngx_shutdown; if it
- * cannot be allocated, the unscheduled kernel runs in its place.
+ * such call on, as long as the state's own is kept; if it cannot be allocated,
+ * or once a generate call of this state was captured into a graph, the
+ * unscheduled kernel runs in its place.
  * Defaults: u64 block 512, 2 chunks, non-temporal stores, schedule 7000
  * GB/s; u32 block 0, the library's choice, which is the same launch
  * (measured on MI355X: 6.8-7.1 TB/s at every size from 2^20 to 2^26 states
