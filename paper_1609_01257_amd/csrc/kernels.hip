@@ -746,7 +746,7 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
         segs = std::min<uint64_t>({segs, iters / 8, kMaxSegs});
         if (segs > 1) {
             p.seg_rows = (uint32_t)((iters + segs - 1) / segs);
-            p.segs = (iters + p.seg_rows - 1) / p.seg_rows;
+            p.segs = (uint32_t)(((uint64_t)iters + p.seg_rows - 1) / p.seg_rows);
         }
     }
     // Rows off the 128-byte lines are staged where the memory takes the

@@ -1,0 +1,48 @@
+"""The library's plan of a plain launch, for tests that have to know which kernel a call takes
+(test helper). ``helpers/plan.cpp`` (built here into ``helpers/libplan.so``, linked to
+librngx.so) asks the library's own plan_gen; no device is needed."""
+from __future__ import annotations
+
+import ctypes
+import os
+import subprocess
+
+from paper_1609_01257_amd import build as _pkg
+from paper_1609_01257_amd import rngx
+
+_HERE = os.path.dirname(os.path.abspath(__file__))
+_SRC = os.path.join(_HERE, "helpers", "plan.cpp")
+_LIB = os.path.join(_HERE, "helpers", "libplan.so")
+_FIELDS = ("block", "chunks", "nontemporal", "pace_gbs", "aligned16", "scheduled", "shift", "segs",
+           "seg_rows")
+
+
+def build(force: bool = True) -> str:
+    sources = [_SRC, os.path.join(_pkg.CSRC, "internal.h")]
+    if force or not os.path.exists(_LIB) or \
+            max(map(os.path.getmtime, sources)) > os.path.getmtime(_LIB):
+        tmp = _LIB + ".tmp%d" % os.getpid()
+        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-fPIC", "-shared",
+                        "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I",
+                        os.path.join(_pkg.ROOT, "include"), "-I", _pkg.CSRC, "-o", tmp, _SRC,
+                        "-L", _pkg.PKG, "-l:librngx.so",
+                        "-Wl,-rpath,$ORIGIN/../../paper_1609_01257_amd"], check=True)
+        os.replace(tmp, _LIB)
+    return _LIB
+
+
+_lib = None
+
+
+def query(n, iters, u32=False, star=False, out=0, launch=None):
+    """The plan as a dict; launch: (block, chunks, nontemporal, pace_gbs), by default the
+    library's own."""
+    global _lib
+    if _lib is None:
+        build(force=False)
+        _lib = ctypes.CDLL(_LIB)
+    v = (ctypes.c_uint32 * len(_FIELDS))()
+    _lib.plan_query(ctypes.byref(rngx.Launch(*(launch or (512, 2, 1, 7000)))),
+                    ctypes.c_int(u32), ctypes.c_int(star), ctypes.c_uint32(n),
+                    ctypes.c_uint32(iters), ctypes.c_uint64(out), v)
+    return dict(zip(_FIELDS, v))

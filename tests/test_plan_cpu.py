@@ -1,0 +1,18 @@
+"""The plan of a plain launch (which kernel, shape and segments a call takes), on the CPU."""
+import pytest
+
+from tests import plan
+
+
+# The segments cover the iterations exactly, each with rows of its own, also where their number
+# of rows added to the iterations passes 2^32.
+@pytest.mark.parametrize("u32", [False, True])
+@pytest.mark.parametrize("n", [1, 7, 16, 128, 1024, 4096, 4099, 65536, 100003, 262147])
+def test_segments_cover_the_iterations(n, u32):
+    counts = {1, 2, 23, 24, 63, 64, 65, 100, 257, 10000, 2**31, 2**32 - 2**24, 2**32 - 2**24 + 1,
+              2**32 - 10**6, 2**32 - 2, 2**32 - 1}
+    for iters in sorted(counts):
+        for out in (0, 8):
+            p = plan.query(n, iters, u32=u32, out=out)
+            assert p["segs"] >= 1 and p["seg_rows"] >= 1, (iters, p)
+            assert (p["segs"] - 1) * p["seg_rows"] < iters <= p["segs"] * p["seg_rows"], (iters, p)
