@@ -297,6 +297,8 @@ void release_batch();
 // The batch API's launch configuration (rngx_set_batch_cfg / the autotuner).
 rngx_batch_cfg current_batch_cfg();
 void release_server(); // serve.cpp: stop the server, free its resources
+// serve.cpp: what a served batch of `values` (padded) values runs.
+rngx_batch_cfg serve_order(uint64_t values);
 int checksum_locked(const uint64_t *data, uint64_t n, hipStream_t s, uint64_t *result);
 hipError_t launch_batch(const rngx_batch_cfg &cfg, const BatchDesc *desc, const BatchTables &t,
                         bool star, hipStream_t s);

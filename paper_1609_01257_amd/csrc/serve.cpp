@@ -167,19 +167,11 @@ bool admit(Server &s)
     return progress;
 }
 
-// Batches of at most this many (padded) values (64 MiB) are latency-bound:
-// they run one wave per small item, and one may run above the in-flight
-// cap. Batches of a few requests of up to 2^22 values each stay below it
-// (Poisson runs at 2k/10k/50k req/s, p99 55/55/69 us against 65/60/76-84
-// with 2^20; the backlog's multi-GB batches are unaffected).
+// Batches of at most this many (padded) values (64 MiB) are latency-bound: one
+// may run above the in-flight cap. Batches of a few requests of up to 2^22
+// values each stay below it (Poisson runs at 2k/10k/50k req/s, p99 55/55/69 us
+// against 65/60/76-84 with 2^20; the backlog's multi-GB batches are unaffected).
 constexpr uint64_t kSmallBatchValues = 1u << 23;
-
-// A served batch runs in the library's own order (batch_order), whatever the
-// batch API's configuration: one wave per 1,024-value item up to 2^26 values
-// (a small batch is latency-bound: that spreads a request over the most waves,
-// each storing soonest; Poisson runs at 2k/10k/50k req/s: p50 23/23/28 us
-// against 28/27/33 with 4,096-value items), the sweep order above.
-constexpr rngx_batch_cfg kServeCfg{16, 4, 0, 0, 16, 0, 0, 32, 8, 6250};
 
 // Whether the next batch (the first max_batch admitted requests, padded as
 // launch_admitted pads them) would be small.
@@ -219,7 +211,7 @@ int launch_admitted(Server &s, Flight &f, std::vector<StageReq> &items, const Se
         r.state = ST_INFLIGHT;
         f.tickets.push_back(tk);
     }
-    const rngx_batch_cfg cfg = batch_order(kServeCfg, vbase, true);
+    const rngx_batch_cfg cfg = serve_order(vbase);
     int rc = batch_stage_items(f.slot, items.data(), (uint32_t)items.size(), cfg.values_per_lane,
                                s.d_states);
     if (rc == RNGX_OK)
@@ -565,6 +557,24 @@ void stop_locked(Server &s, std::unique_lock<std::mutex> &lk)
 }
 
 } // namespace
+
+// A served batch of `values` (padded) values, whatever the batch API's
+// configuration: up to 192 MiB one wave per 1,024-value item, as the batch API
+// has it (a small batch is latency-bound: that spreads a request over the most
+// waves, each storing soonest; Poisson runs at 2k/10k/50k req/s: p50 23/23/28
+// us against 28/27/33 with 4,096-value items). Above, the grouped order, not
+// the batch API's sweep order: two batches are in flight, and the sweep's, one
+// block of 152 KiB of LDS on each compute unit, do not run side by side. A
+// backlog of 243 GB, TB/s, in batches of 1,600, 100, 64, 48, 32, 24 and 16
+// requests of 4.8 MB: 5.64, 5.81, 5.26, 4.87, 4.59, 4.32, 3.88 so; with the
+// sweep order above 2^26 values and items below 5.20, 5.34, 4.95, 4.74, 4.49,
+// 4.29, 3.83; with the line at 2^24 5.65, 5.82, 5.29, 4.92, 4.21, 4.01, 3.76,
+// at 2^25 5.65, 5.83, 5.13, 4.65, 4.54, 4.29, 3.80.
+rngx_batch_cfg serve_order(uint64_t values)
+{
+    constexpr rngx_batch_cfg grouped{16, 4, 0, 0, 16, 0, 0, 32, 8, 6250};
+    return values <= 3ull << 23 ? batch_order(grouped, values, false) : grouped;
+}
 
 void release_server()
 {

@@ -1,5 +1,6 @@
 // How the library covers one plain launch (plan_gen), for the tests: which kernel, blocks,
-// segments and rate a call of these sizes, at this output address, takes. Host code only.
+// segments and rate a call of these sizes, at this output address, takes; and the order a served
+// batch runs in (serve_order). Host code only.
 #include "internal.h"
 
 extern "C" void plan_query(const rngx_launch *cfg, int u32, int star, uint32_t n, uint32_t iters,
@@ -16,4 +17,9 @@ extern "C" void plan_query(const rngx_launch *cfg, int u32, int star, uint32_t n
     v[6] = p.shift;
     v[7] = p.segs;
     v[8] = p.seg_rows;
+}
+
+extern "C" void serve_order_query(uint64_t values, rngx_batch_cfg *cfg)
+{
+    *cfg = rngx::serve_order(values);
 }

@@ -1,6 +1,6 @@
-"""The library's plan of a plain launch, for tests that have to know which kernel a call takes
+"""The library's plans of its launches, for tests that have to know which kernel a call takes
 (test helper). ``helpers/plan.cpp`` (built here into ``helpers/libplan.so``, linked to
-librngx.so) asks the library's own plan_gen; no device is needed."""
+librngx.so) asks the library's own functions; no device is needed."""
 from __future__ import annotations
 
 import ctypes
@@ -34,15 +34,26 @@ def build(force: bool = True) -> str:
 _lib = None
 
 
-def query(n, iters, u32=False, star=False, out=0, launch=None):
-    """The plan as a dict; launch: (block, chunks, nontemporal, pace_gbs), by default the
-    library's own."""
+def lib():
     global _lib
     if _lib is None:
         build(force=False)
         _lib = ctypes.CDLL(_LIB)
+    return _lib
+
+
+def query(n, iters, u32=False, star=False, out=0, launch=None):
+    """The plan of a plain launch as a dict; launch: (block, chunks, nontemporal, pace_gbs), by
+    default the library's own."""
     v = (ctypes.c_uint32 * len(_FIELDS))()
-    _lib.plan_query(ctypes.byref(rngx.Launch(*(launch or (512, 2, 1, 7000)))),
-                    ctypes.c_int(u32), ctypes.c_int(star), ctypes.c_uint32(n),
-                    ctypes.c_uint32(iters), ctypes.c_uint64(out), v)
+    lib().plan_query(ctypes.byref(rngx.Launch(*(launch or (512, 2, 1, 7000)))),
+                     ctypes.c_int(u32), ctypes.c_int(star), ctypes.c_uint32(n),
+                     ctypes.c_uint32(iters), ctypes.c_uint64(out), v)
     return dict(zip(_FIELDS, v))
+
+
+def served(values):
+    """The configuration a served batch of this many (padded) values runs."""
+    c = rngx.BatchCfg()
+    lib().serve_order_query(ctypes.c_uint64(values), ctypes.byref(c))
+    return {name: getattr(c, name) for name, _ in c._fields_}

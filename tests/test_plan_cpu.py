@@ -16,3 +16,14 @@ def test_segments_cover_the_iterations(n, u32):
             p = plan.query(n, iters, u32=u32, out=out)
             assert p["segs"] >= 1 and p["seg_rows"] >= 1, (iters, p)
             assert (p["segs"] - 1) * p["seg_rows"] < iters <= p["segs"] * p["seg_rows"], (iters, p)
+
+
+# Served batches: one wave per item up to 192 MiB, above that the grouped order (the sweep order
+# of the batch API holds a compute unit for itself, which costs batches that run side by side).
+@pytest.mark.parametrize("values,per_item,group", [
+    (16, 1, 0), (1 << 23, 1, 0), ((1 << 23) + 16, 1, 0), (3 << 23, 1, 0), ((3 << 23) + 16, 0, 32),
+    (1 << 26, 0, 32), ((1 << 26) + 16, 0, 32), (2 * 10**9, 0, 32)])
+def test_served_order(values, per_item, group):
+    c = plan.served(values)
+    assert (c["per_item"], c["group"]) == (per_item, group)
+    assert c["values_per_lane"] == 16 and c["waves_per_block"] == 4
