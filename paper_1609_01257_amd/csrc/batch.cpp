@@ -341,9 +341,11 @@ rngx_batch_cfg batch_order(const rngx_batch_cfg &c, uint64_t values, bool anchor
     if (values <= kItemOrderValues)
         return rngx_batch_cfg{16, 4, 0, kUploadKernel, values <= kItemOrderValues / 2 ? 8u : 16u,
                               1, 1, 0, 0, 0};
-    if (!anchors)
-        return c;
-    return rngx_batch_cfg{8, 4, 0, kUploadKernel, 8, 0, 0, kSweepOrder, 1, 7000};
+    if (anchors)
+        return rngx_batch_cfg{8, 4, 0, kUploadKernel, 8, 0, 0, kSweepOrder, 1, 7000};
+    rngx_batch_cfg grouped = c;
+    grouped.use_graph = kUploadKernel;
+    return grouped;
 }
 
 int resolve_batch_cfg(const rngx_batch_cfg &c, int n_cus, rngx_batch_cfg *out)
@@ -386,8 +388,8 @@ void fill_batch_tables(BatchTables &t, const rngx_batch_cfg &cfg, const uint64_t
     t.clock_khz = (uint32_t)clock_khz;
 }
 
-int batch_stage_items(BatchSlot &slot, const StageReq *items, uint32_t k,
-                      uint32_t values_per_lane, const uint64_t *states)
+// The slot, once its previous batch no longer uses its buffers.
+static int slot_ready(BatchSlot &slot)
 {
     // A slot's buffers, event and graph belong to the device they were made
     // on; when another device is current, the slot starts over there.
@@ -397,13 +399,23 @@ int batch_stage_items(BatchSlot &slot, const StageReq *items, uint32_t k,
         free_slot(slot);
         slot.device = dev;
     }
+    if (!slot.done)
+        RNGX_HIP(hipEventCreateWithFlags(&slot.done, hipEventDisableTiming));
+    RNGX_HIP(hipEventSynchronize(slot.done));
+    return RNGX_OK;
+}
+
+int batch_stage_items(BatchSlot &slot, const StageReq *items, uint32_t k,
+                      uint32_t values_per_lane, const uint64_t *states)
+{
+    const int rc = slot_ready(slot);
+    if (rc)
+        return rc;
     // Grow the slot to a power-of-two capacity (>= 64 requests).
     if (k > slot.capacity || !slot.staging) {
         uint32_t cap = 64;
         while (cap < k)
             cap <<= 1;
-        if (slot.done)
-            RNGX_HIP(hipEventSynchronize(slot.done));
         if (slot.exec) {
             RNGX_NOTE(hipGraphExecDestroy(slot.exec));
             slot.exec = nullptr;
@@ -437,10 +449,6 @@ int batch_stage_items(BatchSlot &slot, const StageReq *items, uint32_t k,
         }
         slot.capacity = cap;
     }
-    if (!slot.done)
-        RNGX_HIP(hipEventCreateWithFlags(&slot.done, hipEventDisableTiming));
-    // The slot's previous batch must have read its table before we rewrite it.
-    RNGX_HIP(hipEventSynchronize(slot.done));
 
     const uint64_t C = 64ull * values_per_lane;
     BatchDesc *desc = static_cast<BatchDesc *>(slot.staging);
@@ -502,6 +510,27 @@ static uint64_t line_skew(const uint64_t *out)
     return (reinterpret_cast<uintptr_t>(out) & 127u) / sizeof(uint64_t);
 }
 
+// Room for the sweep order's anchors of a batch that ends at virtual index
+// v_end, in a slot that is ready; false if there is no memory for them.
+static bool slot_anchors(BatchSlot &slot, uint64_t v_end)
+{
+    const uint64_t need = (v_end + kAnchorValues - 1) / kAnchorValues;
+    if (need <= slot.n_anchors)
+        return true;
+    if (slot.anchors)
+        RNGX_NOTE(hipFree(slot.anchors));
+    slot.anchors = nullptr;
+    slot.n_anchors = 0;
+    void *p = nullptr;
+    if (hipMalloc(&p, need * sizeof(SweepAnchor)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    slot.anchors = static_cast<SweepAnchor *>(p);
+    slot.n_anchors = need;
+    return true;
+}
+
 int batch_stage(BatchSlot &slot, const rngx_req *reqs, uint32_t m, uint64_t *out,
                 uint64_t out_cap, const rngx_batch_cfg &cfg, bool as_given, rngx_batch_cfg *run,
                 uint64_t *total_out)
@@ -509,13 +538,19 @@ int batch_stage(BatchSlot &slot, const rngx_req *reqs, uint32_t m, uint64_t *out
     int rc = batch_validate(reqs, m, out, out_cap, total_out);
     if (rc || *total_out == 0)
         return rc;
+    const uint64_t skew = line_skew(out);
     *run = as_given ? cfg : batch_order(cfg, *total_out, true);
+    if (run->group == kSweepOrder) {
+        if ((rc = slot_ready(slot)))
+            return rc;
+        if (!slot_anchors(slot, skew + *total_out))
+            *run = batch_order(cfg, *total_out, false);
+    }
     // Packed layout: the virtual index of a value is its output index plus
     // the skew of `out` in its 128-byte line, so tile rows fall on whole
     // lines of the output.
     std::vector<StageReq> items;
     items.reserve(m);
-    const uint64_t skew = line_skew(out);
     uint64_t base = 0;
     for (uint32_t j = 0; j < m; ++j) {
         const uint64_t len = reqs[j].length;
@@ -533,27 +568,6 @@ int batch_stage(BatchSlot &slot, const rngx_req *reqs, uint32_t m, uint64_t *out
     }
     return batch_stage_items(slot, items.data(), (uint32_t)items.size(),
                              run->values_per_lane, nullptr);
-}
-
-// The slot's anchors, grown to the staged batch; null (the sweep order then
-// searches and jumps for every tile) when there is no memory for them.
-static SweepAnchor *slot_anchors(BatchSlot &slot)
-{
-    const uint64_t need = (slot.v_end + kAnchorValues - 1) / kAnchorValues;
-    if (need > slot.n_anchors) {
-        if (slot.anchors)
-            RNGX_NOTE(hipFree(slot.anchors));
-        slot.anchors = nullptr;
-        slot.n_anchors = 0;
-        void *p = nullptr;
-        if (hipMalloc(&p, need * sizeof(SweepAnchor)) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        slot.anchors = static_cast<SweepAnchor *>(p);
-        slot.n_anchors = need;
-    }
-    return slot.anchors;
 }
 
 int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipStream_t stream,
@@ -584,7 +598,7 @@ int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipSt
     BatchTables tabs;
     fill_batch_tables(tabs, cfg, jump, spread_all, nib_all, group_all, sweep, clock_khz);
     if (cfg.group == kSweepOrder)
-        tabs.anchors = slot_anchors(slot);
+        tabs.anchors = slot.anchors;
     tabs.v_end = slot.v_end;
     const BatchDesc *ddesc = static_cast<const BatchDesc *>(slot.devtab);
     const int tok = prof::begin(prof_name, stream);

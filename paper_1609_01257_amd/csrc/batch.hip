@@ -754,11 +754,8 @@ __global__ __launch_bounds__(1024) void batch_sweep_kernel(const BatchDesc *__re
     if (place >= n_tiles)
         return;
     uint64_t sched = 0;
-    uint64_t z = 0, dst = 0;
-    if (anchors) {
-        z = anchors[place / kAnchorTiles].state;
-        dst = reinterpret_cast<uintptr_t>(anchors[place / kAnchorTiles].dst);
-    }
+    uint64_t z = anchors[place / kAnchorTiles].state;
+    uint64_t dst = reinterpret_cast<uintptr_t>(anchors[place / kAnchorTiles].dst);
     for (uint64_t tile = place; tile < n_tiles; tile += waves) {
         u64x2 v[4];
         const uint64_t here = dst;
@@ -768,7 +765,7 @@ __global__ __launch_bounds__(1024) void batch_sweep_kernel(const BatchDesc *__re
             for (uint32_t i = 0; i < 4; ++i)
                 asm volatile("" : "+v"(v[i])); // the values stand before the wait
         }
-        if (anchors && tile + waves < n_tiles) {
+        if (tile + waves < n_tiles) {
             z = anchors[(tile + waves) / kAnchorTiles].state;
             dst = reinterpret_cast<uintptr_t>(anchors[(tile + waves) / kAnchorTiles].dst);
         }
@@ -903,18 +900,15 @@ hipError_t launch_sweep(const BatchDesc *desc, const BatchTables &t, const rngx_
         delta256 = (uint64_t)(step_bytes / (c.pace_gbs * 1e9) * t.clock_khz * 1e3 * 256.0);
     }
     const uint64_t n_tiles = (t.v_end + kSweepC - 1) / kSweepC;
-    if (t.anchors) {
-        // Few groups: fewer per wavefront, so that short requests, each of
-        // which costs its wavefront a jump, are spread over more of them.
-        const uint64_t n_groups = (n_tiles + kAnchorTiles - 1) / kAnchorTiles;
-        const uint32_t per_wave = n_groups > 65536 ? 64 : 16;
-        const uint64_t blocks = (n_groups + 4 * per_wave - 1) / (4 * per_wave);
-        const hipError_t e2 = launch_on(s, batch_anchor_kernel, (uint32_t)blocks, 256, 0,
-                                        desc, t.jump, t.anchor_spread, t.anchors, n_groups,
-                                        per_wave);
-        if (e2 != hipSuccess)
-            return e2;
-    }
+    // Few groups: fewer per wavefront, so that short requests, each of
+    // which costs its wavefront a jump, are spread over more of them.
+    const uint64_t n_groups = (n_tiles + kAnchorTiles - 1) / kAnchorTiles;
+    const uint32_t per_wave = n_groups > 65536 ? 64 : 16;
+    const uint64_t blocks = (n_groups + 4 * per_wave - 1) / (4 * per_wave);
+    e = launch_on(s, batch_anchor_kernel, (uint32_t)blocks, 256, 0, desc, t.jump, t.anchor_spread,
+                  t.anchors, n_groups, per_wave);
+    if (e != hipSuccess)
+        return e;
     return launch_on(s, batch_sweep_kernel<STAR>, c.blocks, 64 * kSweepWaves, lds_bytes, desc,
                      t.jump, t.sweep, t.anchors, n_tiles, delta256);
 }

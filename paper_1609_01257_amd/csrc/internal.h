@@ -245,7 +245,7 @@ struct BatchTables {
     const uint64_t *sweep;     // T^(8 m) (v << 3q) at ((8 q + v) * 64 + m)
                                // then T^(512 a) at kSweepTable + 64 a, a < 16: 64 rows each
     const uint64_t *anchor_spread; // T^(8192 m) (v << 4q) at ((16 q + v) * 64 + m)
-    SweepAnchor *anchors;      // sweep order: room for an anchor per 8192 virtual indices
+    SweepAnchor *anchors;      // sweep order: room for an anchor per 8192 virtual indices, else null
     uint64_t v_end;            // sweep order: end of the virtual index space
     uint32_t clock_khz;        // rate of the constant-rate clock
 };
@@ -267,7 +267,7 @@ void fill_batch_tables(BatchTables &t, const rngx_batch_cfg &cfg, const uint64_t
 int batch_validate(const rngx_req *reqs, uint32_t m, const uint64_t *out, uint64_t out_cap,
                    uint64_t *total_out);
 // Stage a packed batch for configuration `cfg`; *run receives what to launch
-// (cfg as given, or as batch_order has it).
+// (cfg as given, or as batch_order has it with the memory there is).
 int batch_stage(BatchSlot &slot, const rngx_req *reqs, uint32_t m, uint64_t *out,
                 uint64_t out_cap, const rngx_batch_cfg &cfg, bool as_given, rngx_batch_cfg *run,
                 uint64_t *total_out);

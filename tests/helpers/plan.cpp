@@ -1,6 +1,6 @@
 // How the library covers one plain launch (plan_gen), for the tests: which kernel, blocks,
-// segments and rate a call of these sizes, at this output address, takes; and the order a served
-// batch runs in (serve_order). Host code only.
+// segments and rate a call of these sizes, at this output address, takes; the order a served or
+// an API batch runs in (serve_order, batch_order). Host code only.
 #include "internal.h"
 
 extern "C" void plan_query(const rngx_launch *cfg, int u32, int star, uint32_t n, uint32_t iters,
@@ -22,4 +22,27 @@ extern "C" void plan_query(const rngx_launch *cfg, int u32, int star, uint32_t n
 extern "C" void serve_order_query(uint64_t values, rngx_batch_cfg *cfg)
 {
     *cfg = rngx::serve_order(values);
+}
+
+// The API's default configuration; anchors: whether there is memory for the sweep order's.
+static const rngx_batch_cfg kDefault{16, 4, 0, 1, 16, 0, 0, 32, 8, 6250};
+extern "C" void batch_order_query(uint64_t values, int anchors, rngx_batch_cfg *cfg)
+{
+    *cfg = rngx::batch_order(kDefault, values, anchors != 0);
+}
+
+// One batch, whatever its size, as the default configuration runs a large one without memory for
+// anchors; returns when it is done.
+extern "C" int batch_without_anchors(const rngx_req *reqs, uint32_t m, uint64_t *out,
+                                     uint64_t out_cap)
+{
+    const rngx_batch_cfg cfg = rngx::batch_order(kDefault, ~(uint64_t)0, false);
+    rngx::BatchSlot slot;
+    rngx_batch_cfg run;
+    uint64_t total = 0;
+    int rc = rngx::batch_stage(slot, reqs, m, out, out_cap, cfg, true, &run, &total);
+    if (rc == RNGX_OK)
+        rc = rngx::batch_launch(slot, run, false, nullptr);
+    rngx::release_slot(slot);
+    return rc;
 }

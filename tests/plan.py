@@ -57,3 +57,17 @@ def served(values):
     c = rngx.BatchCfg()
     lib().serve_order_query(ctypes.c_uint64(values), ctypes.byref(c))
     return {name: getattr(c, name) for name, _ in c._fields_}
+
+
+def batch(values, anchors=True):
+    """The configuration an API batch of this many values runs under the default one."""
+    c = rngx.BatchCfg()
+    lib().batch_order_query(ctypes.c_uint64(values), ctypes.c_int(anchors), ctypes.byref(c))
+    return {name: getattr(c, name) for name, _ in c._fields_}
+
+
+def run_batch_without_anchors(reqs, out):
+    """One batch on the null stream as a large one runs without memory for anchors."""
+    rc = lib().batch_without_anchors(ctypes.c_void_p(reqs.ctypes.data), ctypes.c_uint32(len(reqs)),
+                                     ctypes.c_void_p(out.data_ptr()), ctypes.c_uint64(out.numel()))
+    assert rc == rngx.RNGX_OK, rngx.last_error()

@@ -403,3 +403,18 @@ def test_library_order_calls_in_flight_together(oracle):
     for k, (r, o) in enumerate(jobs):
         assert np.array_equal(o.cpu().numpy().view(np.uint64),
                               oracle.generate_batch(_oracle_reqs(oracle, r))), k
+
+
+# A large batch without memory for the sweep order's anchors: groups, the table uploaded by a
+# kernel. (Small ones here take the same path.)
+@pytest.mark.parametrize("m,top", [(1, 100000), (48, 30000), (300, 30000), (40, 1000000)])
+def test_batches_without_anchors(oracle, m, top):
+    from tests import plan
+    r = inputs.ragged_requests(m=m, seed=900 + m, max_len=top, max_offset=10**6)
+    out = torch.zeros(r.total + 9, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    plan.run_batch_without_anchors(_reqs(r), out[2:2 + r.total])
+    torch.cuda.synchronize()
+    host = out.cpu().numpy().view(np.uint64)
+    assert not host[:2].any() and not host[2 + r.total:].any()
+    assert np.array_equal(host[2:2 + r.total], oracle.generate_batch(_oracle_reqs(oracle, r)))

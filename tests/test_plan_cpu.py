@@ -27,3 +27,19 @@ def test_served_order(values, per_item, group):
     c = plan.served(values)
     assert (c["per_item"], c["group"]) == (per_item, group)
     assert c["values_per_lane"] == 16 and c["waves_per_block"] == 4
+
+
+# The batch API's own order: items up to 2^26 values (half lines up to 2^25); above, the sweep
+# order or, without memory for its anchors, groups, launched without a graph all the same.
+UPLOAD, SWEEP = 2, 1
+
+
+@pytest.mark.parametrize("anchors", [False, True])
+def test_batch_order(anchors):
+    for values, rows in [(1, 8), (1 << 25, 8), ((1 << 25) + 1, 16), (1 << 26, 16)]:
+        c = plan.batch(values, anchors)
+        assert (c["per_item"], c["row_values"], c["group"], c["use_graph"]) == (1, rows, 0, UPLOAD)
+    c = plan.batch((1 << 26) + 1, anchors)
+    assert (c["per_item"], c["use_graph"]) == (0, UPLOAD)
+    assert (c["group"], c["values_per_lane"], c["pace_gbs"]) == \
+        ((SWEEP, 8, 7000) if anchors else (32, 16, 6250))
