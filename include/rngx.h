@@ -388,8 +388,9 @@ int rngx_generate_batch_noalloc(const rngx_req *reqs, uint32_t m, uint64_t *out,
  *   for the one before it;
  *   above, the sweep order: all wavefronts of the grid take consecutive
  *   512-value tiles, then all move on together, at 7000 GB/s, from starting
- *   states that a first kernel prepares (16 bytes of device memory per 8,192
- *   values, kept with the staging buffer, given back by rngx_shutdown). 6.9
+ *   states that a first kernel prepares (2 MiB of device memory, above 8 GiB
+ *   up to 32 bytes per 8,192 values, kept with the staging buffer, given back
+ *   by rngx_shutdown; without it the grouped order runs, directly). 6.9
  *   TB/s on a 4,096-stream table on MI355X, against 6.2 for the grouped order
  *   and 5.9 for the persistent grid with S = 256.
  * The output never depends on the configuration. */

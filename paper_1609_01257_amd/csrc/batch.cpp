@@ -521,13 +521,14 @@ static bool slot_anchors(BatchSlot &slot, uint64_t v_end)
         RNGX_NOTE(hipFree(slot.anchors));
     slot.anchors = nullptr;
     slot.n_anchors = 0;
+    const uint64_t room = anchor_room(need);
     void *p = nullptr;
-    if (hipMalloc(&p, need * sizeof(SweepAnchor)) != hipSuccess) {
+    if (hipMalloc(&p, room * sizeof(SweepAnchor)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
     slot.anchors = static_cast<SweepAnchor *>(p);
-    slot.n_anchors = need;
+    slot.n_anchors = room;
     return true;
 }
 

@@ -192,6 +192,16 @@ struct SweepAnchor {
     uint64_t *dst;
 };
 constexpr uint64_t kAnchorValues = 8192;
+// Anchors allocated where `need` are needed: a power of two, at least 2^17 (2
+// MiB, for 8 GiB of values). Growing frees the buffer before, which waits for
+// the device: a slot does so at most 5 times up to 256 GiB of values.
+constexpr uint64_t anchor_room(uint64_t need)
+{
+    uint64_t room = 1u << 17;
+    while (room < need)
+        room <<= 1;
+    return room;
+}
 
 // A staging/upload slot for one batch in flight (batch.cpp).
 struct BatchSlot {

@@ -46,3 +46,5 @@ extern "C" int batch_without_anchors(const rngx_req *reqs, uint32_t m, uint64_t 
     rngx::release_slot(slot);
     return rc;
 }
+
+extern "C" uint64_t anchor_room_query(uint64_t need) { return rngx::anchor_room(need); }

@@ -71,3 +71,9 @@ def run_batch_without_anchors(reqs, out):
     rc = lib().batch_without_anchors(ctypes.c_void_p(reqs.ctypes.data), ctypes.c_uint32(len(reqs)),
                                      ctypes.c_void_p(out.data_ptr()), ctypes.c_uint64(out.numel()))
     assert rc == rngx.RNGX_OK, rngx.last_error()
+
+
+def anchor_room(need):
+    """Anchors that a slot allocates where it needs this many (one for 8,192 values)."""
+    lib().anchor_room_query.restype = ctypes.c_uint64
+    return lib().anchor_room_query(ctypes.c_uint64(need))

@@ -43,3 +43,17 @@ def test_batch_order(anchors):
     assert (c["per_item"], c["use_graph"]) == (0, UPLOAD)
     assert (c["group"], c["values_per_lane"], c["pace_gbs"]) == \
         ((SWEEP, 8, 7000) if anchors else (32, 16, 6250))
+
+
+def test_anchors_of_growing_batches_are_seldom_allocated():
+    # Batches of 512 MiB up to 256 GiB, each a little larger than the one before.
+    have = allocated = 0
+    values = (1 << 26) + 1
+    while values <= 1 << 35:
+        need = -(-values // 8192)
+        if need > have:
+            allocated += 1
+            have = plan.anchor_room(need)
+            assert need <= have <= max(2 * need, 1 << 17)
+        values += values // 100
+    assert allocated <= 6
