@@ -177,8 +177,9 @@ int rngx_hip_notes(uint64_t *released, uint64_t *stray, char *text, size_t cap, 
  * larger than 256 MiB or cut into segments, with at most 2 chunks. Staged
  * rows and segments keep a second buffer of 8 * n_states bytes from the first
  * such call on, as long as the state's own is kept; if it cannot be allocated,
- * or once a generate call of this state was captured into a graph, the
- * unscheduled kernel runs in its place.
+ * or once a generate call of this state was captured into a graph, such calls
+ * run in one segment, their rows written where they lie (on the schedule if
+ * these are 16-byte aligned).
  * Defaults: u64 block 512, 2 chunks, non-temporal stores, schedule 7000
  * GB/s; u32 block 0, the library's choice, which is the same launch
  * (measured on MI355X: 6.8-7.1 TB/s at every size from 2^20 to 2^26 states

@@ -212,25 +212,17 @@ int check_device_locked(const Generator &c)
 hipError_t run_gen_locked(Generator &c, const rngx_launch &cfg, uint32_t n_iters, void *out,
                           hipStream_t s, bool u32, bool star)
 {
-    GenPlan plan = plan_gen(cfg, u32, star, c.n, n_iters, out);
-    bool in_place = c.fixed;
-    if (plan.out_of_place() && !c.alt && !in_place) {
+    // A graph works on the states where they are at each replay (fixed).
+    GenPlan plan = plan_gen(cfg, u32, star, c.n, n_iters, out, c.fixed);
+    if (plan.out_of_place() && !c.alt) {
         void *p = nullptr;
         if (hipMalloc(&p, (size_t)c.cap * sizeof(uint64_t)) == hipSuccess) {
             c.alt = static_cast<uint64_t *>(p);
         } else {
+            // No room for a second copy of the states.
             (void)hipGetLastError();
-            in_place = true;
+            plan = plan_gen(cfg, u32, star, c.n, n_iters, out, true);
         }
-    }
-    if (plan.out_of_place() && in_place) {
-        // No room for a second copy of the states, or a graph works on this
-        // one at each replay: the launch that works in place, as slow as its
-        // unaligned or short rows make it.
-        plan.cfg = cfg;
-        plan.scheduled = plan.shift = false;
-        plan.segs = 1;
-        plan.seg_rows = n_iters;
     }
     if (plan.segs > 1 && (c.polys_rows != plan.seg_rows || c.polys_count < plan.segs)) {
         jump_polys(plan.seg_rows, plan.segs, c.polys.c);

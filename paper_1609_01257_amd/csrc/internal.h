@@ -366,8 +366,9 @@ constexpr uint32_t kMaxSegs = 256;
 struct JumpPolys {
     uint64_t c[kMaxSegs];
 };
+// in_place: the states have to stay in their buffer.
 GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32_t iters,
-                 const void *out);
+                 const void *out, bool in_place);
 // alt: n more states, needed (and then holding the states after the launch)
 // when the plan is out of place.
 hipError_t launch_gen(const GenPlan &plan, const JumpPolys &polys, bool u32, bool star,

@@ -699,7 +699,7 @@ hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, hipStrea
 }
 
 GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32_t iters,
-                 const void *out)
+                 const void *out, bool in_place)
 {
     const uint64_t row = (uint64_t)n * (u32 ? 4 : 8), bytes = row * iters;
     const uintptr_t at = reinterpret_cast<uintptr_t>(out) | (iters > 1 ? row : 0);
@@ -729,11 +729,17 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     // off word by word where one segment keeps the device busy (262,273 x 99
     // u64: 34 us, 40 in two staged ones; 65,537 x 399: 65 and 44 in three).
     const uint64_t waves = (row + 1023) / 1024;
+    // In place there are no segments and no staging; rows that would be staged
+    // then run as configured from 768 wavefronts on (1,800 of 4-byte words): 262,146
+    // x 500 u64 245 us so, 280 narrow; 98,306 x 1,300 232 and 254; 65,538 x 1,000
+    // 178 and 121; u32 524,292 x 500 277 and 282; 400,004 x 660 299 and 285.
     const bool heaviest = u32 && star, heavy = u32 || star;
-    const bool narrow =
-        cfg.pace_gbs && iters >= 2 && waves < (lines && !heaviest ? 3072u : 4096u);
+    const uint32_t wide = in_place && !lines && bytes > kCacheBytes ? (u32 ? 1800u : 768u)
+                          : lines && !heaviest                      ? 3072u
+                                                                    : 4096u;
+    const bool narrow = cfg.pace_gbs && iters >= 2 && waves < wide;
     const bool cached = bytes <= kCacheBytes * 3 / 4;
-    if (narrow && iters >= (lines ? 64u : 24u)) {
+    if (narrow && !in_place && iters >= (lines ? 64u : 24u)) {
         uint64_t segs = 1;
         if (!lines && !(bytes <= kCacheBytes && waves >= (heavy ? 1800u : 768u)))
             segs = ((u32 && !cached && waves >= 200 && waves < 1600 ? 6144 : 4096) + waves / 2) /
@@ -754,7 +760,7 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     // (10^6 + 3 states x 256 u64: 6.89 TB/s staged, 4.13 not; 10^6 + 2, 16-byte
     // aligned: 6.9 and 4.3). Below 256 MiB the Infinity Cache puts the parts
     // together and staging only costs (2^22 + 1 x 8: 54.7 us staged, 51.6 not).
-    p.shift = !lines && iters >= 2 && (bytes > kCacheBytes || p.segs > 1);
+    p.shift = !in_place && !lines && iters >= 2 && (bytes > kCacheBytes || p.segs > 1);
     // A few iterations of long rows end before a schedule orders anything;
     // they run as fast without one, or faster, up to 32 bytes a stream and up
     // to 48 where rows are on lines and the output is about the cache's size

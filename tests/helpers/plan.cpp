@@ -4,10 +4,11 @@
 #include "internal.h"
 
 extern "C" void plan_query(const rngx_launch *cfg, int u32, int star, uint32_t n, uint32_t iters,
-                           uint64_t out, uint32_t *v)
+                           uint64_t out, int in_place, uint32_t *v)
 {
-    const rngx::GenPlan p = rngx::plan_gen(*cfg, u32 != 0, star != 0, n, iters,
-                                           reinterpret_cast<const void *>((uintptr_t)out));
+    const rngx::GenPlan p =
+        rngx::plan_gen(*cfg, u32 != 0, star != 0, n, iters,
+                       reinterpret_cast<const void *>((uintptr_t)out), in_place != 0);
     v[0] = p.cfg.block;
     v[1] = p.cfg.chunks;
     v[2] = p.cfg.nontemporal;

@@ -42,13 +42,13 @@ def lib():
     return _lib
 
 
-def query(n, iters, u32=False, star=False, out=0, launch=None):
+def query(n, iters, u32=False, star=False, out=0, launch=None, in_place=False):
     """The plan of a plain launch as a dict; launch: (block, chunks, nontemporal, pace_gbs), by
-    default the library's own."""
+    default the library's own; in_place: the states stay in their buffer, as after a capture."""
     v = (ctypes.c_uint32 * len(_FIELDS))()
     lib().plan_query(ctypes.byref(rngx.Launch(*(launch or (512, 2, 1, 7000)))),
                      ctypes.c_int(u32), ctypes.c_int(star), ctypes.c_uint32(n),
-                     ctypes.c_uint32(iters), ctypes.c_uint64(out), v)
+                     ctypes.c_uint32(iters), ctypes.c_uint64(out), ctypes.c_int(in_place), v)
     return dict(zip(_FIELDS, v))
 
 

@@ -634,3 +634,30 @@ def test_reseeding_waits_for_the_last_use_of_kept_buffers(oracle, logged):
             assert np.array_equal(_u64(out).reshape(200, n), oracle.generate(i, n, 200)), (i, n)
     finally:
         rngx.profile_enable(True)
+
+
+# The same on shapes that would be staged or segmented if their states could leave their buffer:
+# rows 16-byte aligned off the lines and not aligned at all, long and short.
+@pytest.mark.parametrize("u32,n,iters", [(False, (1 << 20) + 2, 40), (True, (1 << 20) + 4, 80),
+                                         (False, (1 << 20) + 3, 40), (False, 4098, 10000),
+                                         (False, 262146, 140), (True, 65536, 1100),
+                                         (True, 4099, 300)])
+def test_calls_after_a_capture(oracle, u32, n, iters):
+    gen, want = (rngx.generate_u32, oracle.generate_u32) if u32 else (rngx.generate,
+                                                                     oracle.generate)
+    back = _u32 if u32 else _u64
+    rngx.init(17, n)
+    out = torch.zeros(iters * n, dtype=torch.int32 if u32 else torch.int64, device="cuda")
+    s, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    gen(iters, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(back(out).reshape(iters, n), want(17, n, iters))
+    with torch.cuda.graph(graph, stream=s):
+        gen(iters, out, stream=s)
+    for k in (1, 2, 3):
+        if k == 2:
+            gen(iters, out)
+        else:
+            graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(back(out).reshape(iters, n), want(17, n, iters, cursor=k * iters)), k

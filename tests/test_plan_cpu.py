@@ -57,3 +57,35 @@ def test_anchors_of_growing_batches_are_seldom_allocated():
             assert need <= have <= max(2 * need, 1 << 17)
         values += values // 100
     assert allocated <= 6
+
+
+# With the states in place (after a capture, or without memory for a second buffer) a call stays
+# in one segment and unstaged, and keeps to its row schedule wherever its rows are 16-byte aligned.
+@pytest.mark.parametrize("u32,n,iters,out", [
+    (False, 4096, 100, 0), (False, 4096, 10000, 0), (False, 4098, 10000, 0), (False, 65536, 1000, 0),
+    (False, 262146, 500, 0), (False, (1 << 20) + 2, 256, 0), (False, 1 << 20, 256, 16),
+    (True, 4096, 10000, 0), (True, 4100, 10000, 16), (True, (1 << 20) + 4, 256, 0),
+    (True, 65536, 2000, 0), (False, 4099, 10000, 0), (False, (1 << 20) + 3, 256, 0),
+    (True, (1 << 20) + 4, 256, 4)])
+def test_in_place_plans(u32, n, iters, out):
+    away = plan.query(n, iters, u32=u32, out=out)
+    p = plan.query(n, iters, u32=u32, out=out, in_place=True)
+    assert away["segs"] > 1 or away["shift"]
+    assert (p["segs"], p["seg_rows"], p["shift"]) == (1, iters, 0)
+    size = 4 if u32 else 8
+    assert p["scheduled"] == int(n * size % 16 == 0 and out % 16 == 0)
+
+
+# A plan that is in place anyway is the same with and without that condition.
+@pytest.mark.parametrize("u32", [False, True])
+@pytest.mark.parametrize("star", [False, True])
+def test_in_place_changes_no_other_plan(u32, star):
+    same = 0
+    for n in (100, 4096, 4099, 65536, 114688, 262144, 262147, 1 << 20, (1 << 20) + 2, 1 << 24):
+        for iters in (1, 2, 5, 13, 63, 64, 400, 5000):
+            for out in (0, 16, 8):
+                a = plan.query(n, iters, u32=u32, star=star, out=out)
+                if a["segs"] == 1 and not a["shift"]:
+                    assert a == plan.query(n, iters, u32=u32, star=star, out=out, in_place=True)
+                    same += 1
+    assert same > 100
