@@ -360,6 +360,15 @@ struct GenPlan {
     // another buffer.
     bool out_of_place() const { return shift || segs > 1; }
 };
+// Staged rows: where, in a wavefront's stage of `size` words, a lane finds its
+// word after the row's last whole chunk of E (the row has `lim` words from
+// stage word d on). Lanes without such a word stay inside the stage.
+__host__ __device__ constexpr uint32_t stage_tail(uint32_t d, uint32_t lim, uint32_t lane,
+                                                  uint32_t E, uint32_t size)
+{
+    const uint32_t at = d + (lim & ~(E - 1)) + (lane & (E - 1));
+    return at < size ? at : size - 1;
+}
 // Coefficients of T^(k seg_rows) = sum over i of c[k]_i T^i for each segment
 // k (kernel argument, 2 KiB).
 constexpr uint32_t kMaxSegs = 256;

@@ -366,7 +366,7 @@ __device__ __forceinline__ void paced_rows(uint64_t (&x)[P][Vec16<T>::E], uint64
             const T head = stage[lane];
             T tail = 0;
             if (!WHOLE)
-                tail = stage[d + (lim & ~(E - 1u)) + (lane & (E - 1u))];
+                tail = stage[stage_tail(d, lim, lane, E, W + L)];
             wave_lds_fence();
             // The next states are formed while the LDS answers.
             __builtin_amdgcn_sched_barrier(0);

@@ -49,3 +49,20 @@ extern "C" int batch_without_anchors(const rngx_req *reqs, uint32_t m, uint64_t 
 }
 
 extern "C" uint64_t anchor_room_query(uint64_t need) { return rngx::anchor_room(need); }
+
+// Every place stage_tail gives for wavefronts of W columns, chunks of E words and lines of L, over
+// all columns left in the row and all line offsets: how many lie outside the stage, or are not
+// the word that the lane stores.
+extern "C" uint32_t stage_tail_faults(uint32_t E, uint32_t L, uint32_t W)
+{
+    uint32_t faults = 0;
+    for (uint32_t cols = 1; cols < W + L; ++cols)
+        for (uint32_t d = 0; d < L; ++d)
+            for (uint32_t lane = 0; lane < 64; ++lane) {
+                const uint32_t lim = d >= cols ? 0 : cols - d;
+                const uint32_t at = rngx::stage_tail(d, lim, lane, E, W + L);
+                const bool stores = lane < lim % E && lim < W;
+                faults += at >= W + L || (stores && at != d + lim - lim % E + lane);
+            }
+    return faults;
+}

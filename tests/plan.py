@@ -77,3 +77,9 @@ def anchor_room(need):
     """Anchors that a slot allocates where it needs this many (one for 8,192 values)."""
     lib().anchor_room_query.restype = ctypes.c_uint64
     return lib().anchor_room_query(ctypes.c_uint64(need))
+
+
+def stage_tail_faults(chunk, line, columns):
+    """Reads of a staged row's last words that miss their word or leave the stage."""
+    return lib().stage_tail_faults(ctypes.c_uint32(chunk), ctypes.c_uint32(line),
+                                   ctypes.c_uint32(columns))

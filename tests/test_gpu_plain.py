@@ -661,3 +661,14 @@ def test_calls_after_a_capture(oracle, u32, n, iters):
             graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(back(out).reshape(iters, n), want(17, n, iters, cursor=k * iters)), k
+
+
+# Staged rows whose last wavefronts have one word less than a line right of their columns, at
+# every offset of a row in its line (n is odd, so the rows pass through all of them).
+@pytest.mark.parametrize("u32,n", [(False, 128 + 15), (False, 5 * 128 + 15), (False, 2048 + 15),
+                                   (True, 256 + 31), (True, 5 * 256 + 31), (True, 4096 + 31)])
+def test_staged_rows_that_end_a_word_before_a_line(oracle, u32, n):
+    for iters, offset in [(40, 0), (64, 1), (100, 3)]:
+        got = run(23, n, iters, u32=u32, offset=offset, pre=1)
+        exp = (oracle.generate_u32 if u32 else oracle.generate)(23, n, iters, cursor=1)
+        assert np.array_equal(got, exp), (iters, offset)

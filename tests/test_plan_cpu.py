@@ -89,3 +89,11 @@ def test_in_place_changes_no_other_plan(u32, star):
                     assert a == plan.query(n, iters, u32=u32, star=star, out=out, in_place=True)
                     same += 1
     assert same > 100
+
+
+# Staged rows: the words after a row's last whole chunk are read inside the wavefront's stage, for
+# every number of columns left and every offset of the row in its line.
+@pytest.mark.parametrize("chunk,line,columns", [(2, 16, 128), (2, 16, 256), (4, 32, 256),
+                                                (4, 32, 512)])
+def test_staged_row_ends_stay_inside_the_stage(chunk, line, columns):
+    assert plan.stage_tail_faults(chunk, line, columns) == 0
