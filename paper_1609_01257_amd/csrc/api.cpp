@@ -216,6 +216,7 @@ hipError_t run_gen_locked(Generator &c, const rngx_launch &cfg, uint32_t n_iters
     GenPlan plan = plan_gen(cfg, u32, star, c.n, n_iters, out, c.fixed);
     if (plan.out_of_place() && !c.alt) {
         void *p = nullptr;
+        AllocDuringCapture relaxed;
         if (hipMalloc(&p, (size_t)c.cap * sizeof(uint64_t)) == hipSuccess) {
             c.alt = static_cast<uint64_t *>(p);
         } else {

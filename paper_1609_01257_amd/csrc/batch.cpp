@@ -517,6 +517,7 @@ static bool slot_anchors(BatchSlot &slot, uint64_t v_end)
     const uint64_t need = (v_end + kAnchorValues - 1) / kAnchorValues;
     if (need <= slot.n_anchors)
         return true;
+    AllocDuringCapture relaxed;
     if (slot.anchors)
         RNGX_NOTE(hipFree(slot.anchors));
     slot.anchors = nullptr;

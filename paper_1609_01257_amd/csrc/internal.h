@@ -17,6 +17,14 @@ int set_error(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3
 int hip_fail(hipError_t e, const char *what);
 void clear_error();
 
+// HIP errors with no caller to return them to (rngx_hip_notes).
+// note_hip: the status of one of the library's own HIP calls on a release
+// path. A failure is consumed (so that it is not reported later by an
+// unrelated hipGetLastError, the library's or the application's) and
+// recorded with `what`.
+void note_hip(hipError_t e, const char *what);
+#define RNGX_NOTE(call) ::rngx::note_hip((call), #call)
+
 #define RNGX_HIP(call)                                   \
     do {                                                 \
         hipError_t rngx_e_ = (call);                     \
@@ -33,6 +41,18 @@ inline bool capturing(hipStream_t s)
         (void)hipGetLastError();
     return st != hipStreamCaptureStatusNone;
 }
+
+// While one is alive, this thread's allocations leave alone what other streams
+// capture: an allocation, also another thread's, invalidates a capture in the
+// (default) global mode. For calls that otherwise only enqueue work.
+class AllocDuringCapture {
+  public:
+    AllocDuringCapture() { RNGX_NOTE(hipThreadExchangeStreamCaptureMode(&mode_)); }
+    ~AllocDuringCapture() { RNGX_NOTE(hipThreadExchangeStreamCaptureMode(&mode_)); }
+
+  private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
 
 template <typename P> struct Arg { using type = P; }; // keeps P out of deduction
 
@@ -331,13 +351,6 @@ void power_rows(uint64_t k, uint64_t *rows_out);
 // The polynomials of T^(k rows), k < count.
 void jump_polys(uint64_t rows, uint32_t count, uint64_t *c);
 
-// HIP errors with no caller to return them to (rngx_hip_notes).
-// note_hip: the status of one of the library's own HIP calls on a release
-// path. A failure is consumed (so that it is not reported later by an
-// unrelated hipGetLastError, the library's or the application's) and
-// recorded with `what`.
-void note_hip(hipError_t e, const char *what);
-#define RNGX_NOTE(call) ::rngx::note_hip((call), #call)
 // The launchers below read a launch's status with hipGetLastError, which
 // also returns an older error that no call has consumed yet. Every library
 // call consumes the status of its own HIP calls, so an error still pending

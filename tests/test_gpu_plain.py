@@ -672,3 +672,43 @@ def test_staged_rows_that_end_a_word_before_a_line(oracle, u32, n):
         got = run(23, n, iters, u32=u32, offset=offset, pre=1)
         exp = (oracle.generate_u32 if u32 else oracle.generate)(23, n, iters, cursor=1)
         assert np.array_equal(got, exp), (iters, offset)
+
+
+def _beside_a_capture(work):
+    """Run work(stream) on one stream while another is captured in the global mode; the capture
+    has to stand and to replay."""
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    x = torch.zeros(1000, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=a):
+        x.add_(1)
+        work(b)
+    for k in (1, 2, 3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (x == k).all()
+
+
+# Calls on one stream while another one is captured, that allocate what they need once: the
+# second state buffer, and the states at which a large batch's tiles start.
+def test_generate_beside_a_capture(oracle):
+    n, iters = 4099, 100
+    rngx.shutdown()
+    rngx.init(29, n)
+    out = torch.zeros(iters * n, dtype=torch.int64, device="cuda")
+    _beside_a_capture(lambda s: rngx.generate(iters, out, stream=s))
+    assert np.array_equal(_u64(out).reshape(iters, n), oracle.generate(29, n, iters))
+
+
+def test_large_batch_beside_a_capture(oracle):
+    rngx.shutdown()
+    small = torch.empty(1000, dtype=torch.int64, device="cuda")
+    rngx.generate_batch(rngx.make_reqs([1], [0], [0], [1000]), small)  # the slot's own buffers
+    seeds, gids, offs, lens = [3, 4, 5], [0, 1, 2], [5, 0, 77], [50_000_000, 17_000_000, 200_001]
+    out = torch.zeros(sum(lens), dtype=torch.int64, device="cuda")
+    assert out.numel() > 1 << 26
+    reqs = rngx.make_reqs(seeds, gids, offs, lens)
+    _beside_a_capture(lambda s: rngx.generate_batch(reqs, out, stream=s))
+    assert np.array_equal(_u64(out),
+                          oracle.generate_batch(oracle.make_reqs(seeds, gids, offs, lens)))
