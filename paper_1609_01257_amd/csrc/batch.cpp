@@ -719,6 +719,7 @@ int noalloc_scratch_locked(BatchGlobals &g, int dev, unsigned char **ptr)
 // turn when all are busy.
 BatchSlot *free_api_slot(BatchGlobals &g, uint32_t m)
 {
+    take_stray_error("before a batch slot is chosen"); // clearing "not ready" would clear it
     BatchSlot *idle = nullptr;
     for (BatchSlot &slot : g.api_slot) {
         if (slot.done && hipEventQuery(slot.done) != hipSuccess) {

@@ -418,3 +418,24 @@ def test_batches_without_anchors(oracle, m, top):
     host = out.cpu().numpy().view(np.uint64)
     assert not host[:2].any() and not host[2 + r.total:].any()
     assert np.array_equal(host[2:2 + r.total], oracle.generate_batch(_oracle_reqs(oracle, r)))
+
+
+@pytest.mark.parametrize("busy", [False, True])
+def test_error_left_pending_is_noted_by_a_batch_call(busy):
+    # An error that another HIP call left pending is recorded, also where the
+    # call before still runs and the library asks whether it has ended.
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    reqs = rngx.make_reqs([1, 2], [0, 1], [0, 5], [1000, 3000])
+    out = torch.empty(4000, dtype=torch.int64, device="cuda")
+    rngx.generate_batch(reqs, out)
+    torch.cuda.synchronize()
+    if busy:
+        torch.cuda._sleep(20_000_000)
+        rngx.generate_batch(reqs, out)
+    rngx.hip_notes(clear=True)
+    assert hip.hipSetDevice(10**6) != 0
+    rngx.generate_batch(reqs, out)
+    notes = rngx.hip_notes(clear=True)
+    torch.cuda.synchronize()
+    assert notes["stray"] == 1 and "hipErrorInvalidDevice" in notes["notes"][0]
