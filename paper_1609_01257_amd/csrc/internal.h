@@ -438,9 +438,13 @@ struct Generator {
 Generator &generator();
 // Enqueue n_iters iterations into `out` on stream `s`; caller holds g.mu.
 int generate_locked(Generator &g, uint32_t n_iters, void *out, hipStream_t s, bool u32);
-// One launch of n_iters iterations in configuration `cfg`: the states are
-// advanced in g.state (which may be another buffer afterwards).
-hipError_t run_gen_locked(Generator &g, const rngx_launch &cfg, uint32_t n_iters, void *out,
+// How one launch of n_iters iterations in configuration `cfg` runs, with what it
+// needs on the host and in memory made ready; then the launch, before another
+// is prepared: the states are advanced in g.state (another buffer afterwards
+// when the plan is out of place).
+GenPlan prepare_gen_locked(Generator &g, const rngx_launch &cfg, uint32_t n_iters, const void *out,
+                           bool u32, bool star);
+hipError_t run_gen_locked(Generator &g, const GenPlan &plan, uint32_t n_iters, void *out,
                           hipStream_t s, bool u32, bool star);
 int check_device_locked(const Generator &g);
 void release_pipeline_locked(Generator &g);

@@ -384,9 +384,10 @@ extern "C" int rngx_autotune_plain(uint32_t n_iters, int u32, void *out, uint32_
         int rc2 = restore();
         if (rc2)
             return rc2;
+        const GenPlan plan = prepare_gen_locked(g, cfg, n_iters, out, u32 != 0, star);
         RNGX_HIP(hipEventRecord(sc.e0, s));
         for (uint32_t r = 0; r < n; ++r)
-            RNGX_HIP(run_gen_locked(g, cfg, n_iters, out, s, u32 != 0, star));
+            RNGX_HIP(run_gen_locked(g, plan, n_iters, out, s, u32 != 0, star));
         RNGX_HIP(hipEventRecord(sc.e1, s));
         RNGX_HIP(hipEventSynchronize(sc.e1));
         float t = 0.f;
@@ -399,7 +400,8 @@ extern "C" int rngx_autotune_plain(uint32_t n_iters, int u32, void *out, uint32_
         if (rc2)
             return rc2;
         take_stray_error("before an autotuned rng kernel launch");
-        RNGX_HIP(run_gen_locked(g, cfg, n_iters, out, s, u32 != 0, star));
+        RNGX_HIP(run_gen_locked(g, prepare_gen_locked(g, cfg, n_iters, out, u32 != 0, star), n_iters,
+                                out, s, u32 != 0, star));
         uint64_t sum = 0;
         rc2 = rngx_checksum(static_cast<const uint64_t *>(out), words, s, &sum);
         if (rc2)
@@ -510,7 +512,9 @@ extern "C" int rngx_autotune_plain(uint32_t n_iters, int u32, void *out, uint32_
     // generator is left exactly as it was (state and cursor).
     if ((rc = restore()))
         return rc;
-    RNGX_HIP(run_gen_locked(g, result->best, n_iters, out, s, u32 != 0, star));
+    RNGX_HIP(run_gen_locked(g,
+                            prepare_gen_locked(g, result->best, n_iters, out, u32 != 0, star),
+                            n_iters, out, s, u32 != 0, star));
     if ((rc = restore()))
         return rc;
     RNGX_HIP(hipEventRecord(g.state_ready, s));

@@ -712,3 +712,21 @@ def test_large_batch_beside_a_capture(oracle):
     _beside_a_capture(lambda s: rngx.generate_batch(reqs, out, stream=s))
     assert np.array_equal(_u64(out),
                           oracle.generate_batch(oracle.make_reqs(seeds, gids, offs, lens)))
+
+
+def test_logged_time_leaves_out_the_host_s_preparation():
+    # Each call of another number of rows per segment prepares 256 polynomials, some 50 us on
+    # the host. On an idle stream its logged time is the same as the next call's, which has them.
+    n = 128
+    rngx.init(1, n)
+    out = torch.empty(256 * 40 * n, dtype=torch.int64, device="cuda")
+    rngx.generate(256 * 40, out)
+    torch.cuda.synchronize()
+    rngx.profile_reset()
+    for k in range(8, 38):
+        for _ in range(2):
+            rngx.generate(256 * k, out)
+            torch.cuda.synchronize()
+    us = [(e[3] - e[2]) / 1e3 for e in rngx.profile_events() if e[0] == "RNG_KERNEL"]
+    assert len(us) == 60
+    assert np.median(us[0::2]) < np.median(us[1::2]) + 20.0
