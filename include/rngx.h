@@ -169,9 +169,9 @@ int rngx_hip_notes(uint64_t *released, uint64_t *stray, char *text, size_t cap, 
  *         output per stream, 48 at some sizes) of long rows. With a schedule,
  *         a call whose rows are shorter than 4 MiB (3 MiB on 128-byte lines)
  *         runs with one chunk and blocks of at most 256 or 512, its iterations
- *         cut into segments that run side by side, at up to a seventh less
- *         than the rate, where the rows alone would not fill the device, and
- *         without waits if its output stays below 192 MiB.
+ *         cut into segments that run side by side, many of them at no more
+ *         than 6000 to 6750 GB/s, where the rows alone would not fill the
+ *         device, and without waits if its output stays below 192 MiB.
  * Rows that do not start on 128-byte lines (an odd or ragged n_states, an
  * output offset) are staged through LDS into whole lines when the output is
  * larger than 256 MiB or cut into segments, with at most 2 chunks. Staged

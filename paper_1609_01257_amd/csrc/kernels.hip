@@ -779,22 +779,22 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
         // Outputs well inside that cache run ahead of HBM's rate, so a
         // schedule only holds them back (131,072 x 100 u64: 5.25 TB/s free,
         // below 5.1 scheduled; 65,536 x 1,000: 5.5 free, 6.5 scheduled).
-        // Many segments: a rate that they hold, 6/7, 13/14 or, of heavier
-        // steps on the lines, 27/28 of the configured one, above which they fall behind for good
-        // (at 6,000, 6,500 and 7,000 GB/s: 16,387 x 10,000 u64, 32 segments,
-        // 230, 214, 264 us; 4,099 x 10,000, 124, 66, 73, 79; 131,073 x 2,000,
-        // 4, 354, 327, 308; 65,537 x 1,000 u32, 24, 48, 52, 54; 131,073 x
-        // 2,000 u32, 12, 179, 166, 189; aligned, at 6,500, 6,750 and 7,000:
-        // 25,600 x 6,553 u32, 8, 107, 106, 123; 32,768 x 5,120, 6, 107, 104,
-        // 104; scrambled u64 12,800 x 6,553, 8, 107, 104, 116).
+        // Many segments: at most a rate that they hold, above which they fall
+        // behind for good (at 6,000, 6,500 and 7,000 GB/s: 16,387 x 10,000
+        // u64, 32 segments, 230, 214, 264 us; 4,099 x 10,000, 124, 66, 73, 79;
+        // 131,073 x 2,000, 4, 354, 327, 308; 65,537 x 1,000 u32, 24, 48, 52,
+        // 54; 131,073 x 2,000 u32, 12, 179, 166, 189; aligned, at 6,500, 6,750
+        // and 7,000: 25,600 x 6,553 u32, 8, 107, 106, 123; 32,768 x 5,120, 6,
+        // 107, 104, 104; scrambled u64 12,800 x 6,553, 8, 107, 104, 116).
+        const uint32_t pace = cfg.pace_gbs;
         if (cached)
             p.cfg.pace_gbs = 0;
         else if (lines && heavy && p.segs > 1)
-            p.cfg.pace_gbs = cfg.pace_gbs * 27 / 28;
+            p.cfg.pace_gbs = std::min(pace, 6750u);
         else if (!lines && p.segs >= (u32 ? 20u : 64u))
-            p.cfg.pace_gbs = cfg.pace_gbs * 6 / 7;
+            p.cfg.pace_gbs = std::min(pace, 6000u);
         else if (!lines && p.segs >= (u32 ? 2u : 6u))
-            p.cfg.pace_gbs = cfg.pace_gbs * 13 / 14;
+            p.cfg.pace_gbs = std::min(pace, 6500u);
     }
     return p;
 }

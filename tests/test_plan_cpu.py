@@ -97,3 +97,15 @@ def test_in_place_changes_no_other_plan(u32, star):
                                                 (4, 32, 512)])
 def test_staged_row_ends_stay_inside_the_stage(chunk, line, columns):
     assert plan.stage_tail_faults(chunk, line, columns) == 0
+
+
+# Many segments run at most at a rate that they hold; a lower rate that the caller has set stays.
+@pytest.mark.parametrize("u32,n,iters,most", [
+    (False, 4099, 10000, 6000), (False, 16387, 10000, 6500), (False, 131073, 2000, 7500),
+    (True, 65537, 1000, 6000), (True, 131073, 2000, 6500), (True, 25600, 6553, 6750),
+    (False, 4096, 10000, 7500), (False, 1 << 22, 256, 7500)])
+def test_rates_of_segments(u32, n, iters, most):
+    for pace in (1000, 5000, 6000, 7000, 7500, 20000):
+        p = plan.query(n, iters, u32=u32, launch=(512, 2, 1, pace))
+        assert p["scheduled"]
+        assert p["pace_gbs"] == (min(pace, most) if most < 7500 else pace)
