@@ -730,3 +730,62 @@ def test_logged_time_leaves_out_the_host_s_preparation():
     us = [(e[3] - e[2]) / 1e3 for e in rngx.profile_events() if e[0] == "RNG_KERNEL"]
     assert len(us) == 60
     assert np.median(us[0::2]) < np.median(us[1::2]) + 20.0
+
+
+# Scheduled launches of every shape by calls that are long enough to be scheduled, which the plan
+# is asked to confirm: several strips, a partial last wavefront, waits that are long (1,000 GB/s),
+# scrambled words, a call that continues another.
+@pytest.mark.parametrize("scrambled", [False, True])
+@pytest.mark.parametrize("u32,block,chunks,nt,pace,n", PACED + [
+    (False, 128, 2, 0, 4000, (1 << 21) + 2), (True, 64, 2, 1, 3000, (1 << 21) + 1028),
+    (True, 1024, 1, 1, 5000, (1 << 22) + 4), (False, 1024, 4, 1, 7000, (1 << 21) + 6)])
+def test_scheduled_launches_of_every_shape(oracle, scrambled, u32, block, chunks, nt, pace, n):
+    from tests import plan
+    parts, seed = ((13, 15) if u32 else (7, 7)), 4243
+    want = getattr(oracle, "generate" + ("_star" if scrambled else "") + ("_u32" if u32 else ""))
+    gen = rngx.generate_u32 if u32 else rngx.generate
+    default = rngx.get_launch(u32)
+    try:
+        rngx.set_launch(u32, block, chunks, nt, pace)
+        rngx.set_scrambler(rngx.SCRAMBLE_STAR if scrambled else rngx.SCRAMBLE_NONE)
+        rngx.init(seed, n)
+        at = 0
+        for iters in parts:
+            out = torch.empty(iters * n, dtype=torch.int32 if u32 else torch.int64, device="cuda")
+            p = plan.query(n, iters, u32=u32, star=scrambled, out=out.data_ptr(),
+                           launch=(block, chunks, nt, pace))
+            assert p["scheduled"] and not p["shift"] and p["segs"] == 1
+            assert (p["block"], p["chunks"], p["pace_gbs"]) == (block, chunks, pace)
+            gen(iters, out)
+            torch.cuda.synchronize()
+            got = (_u32 if u32 else _u64)(out).reshape(iters, n)
+            assert np.array_equal(got, want(seed, n, iters, cursor=at)), iters
+            at += iters
+    finally:
+        rngx.set_scrambler(rngx.SCRAMBLE_NONE)
+        rngx.set_launch(u32, **default)
+
+
+# Staged rows and segments under other launches than the default one: blocks of one and of 16
+# wavefronts, one and four chunks, normal stores, no schedule, a slow and a fast one.
+LAUNCHES = [(64, 1, 1, 7000), (1024, 4, 0, 3000), (256, 2, 0, 0), (1024, 1, 1, 0), (64, 4, 0, 20000)]
+
+
+@pytest.mark.parametrize("launch", LAUNCHES)
+@pytest.mark.parametrize("u32,n,iters", [(False, (1 << 22) + 1, 9), (True, (1 << 23) + 33, 9),
+                                         (False, 4096, 300), (False, 4099, 300), (True, 4099, 300),
+                                         (True, 16384, 300)])
+def test_staged_rows_and_segments_under_every_launch(oracle, launch, u32, n, iters):
+    from tests import plan
+    p = plan.query(n, iters, u32=u32, launch=launch)
+    assert p["shift"] if n > 1 << 20 else (p["segs"] > 1) == (launch[3] > 0)
+    default = rngx.get_launch(u32)
+    try:
+        rngx.set_launch(u32, *launch)
+        got = run(14, n, iters, u32=u32, pre=1)
+    finally:
+        rngx.set_launch(u32, **default)
+    want = oracle.generate_u32 if u32 else oracle.generate
+    assert np.array_equal(got, want(14, n, iters, cursor=1))
+    st, _, c = rngx.get_state()
+    assert c == iters + 1 and np.array_equal(st, oracle.generate(14, n, 1, cursor=c).ravel())
