@@ -573,7 +573,7 @@ int batch_stage(BatchSlot &slot, const rngx_req *reqs, uint32_t m, uint64_t *out
 }
 
 int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipStream_t stream,
-                 bool fit_grid, const char *prof_name)
+                 const char *prof_name)
 {
     const uint64_t *jump = nullptr, *spread_all = nullptr, *nib_all = nullptr, *group_all = nullptr,
                    *sweep = nullptr;
@@ -592,10 +592,6 @@ int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipSt
             return set_error(RNGX_E_INVAL, "batch: %llu work items exceed one grid",
                              (unsigned long long)slot.n_items);
         cfg.blocks = (uint32_t)std::max<uint64_t>(1, need);
-    } else if (fit_grid && !cfg.use_graph && !cfg.group) {
-        const uint64_t need = (slot.n_items + cfg.waves_per_block - 1) / cfg.waves_per_block;
-        if (need < cfg.blocks)
-            cfg.blocks = (uint32_t)std::max<uint64_t>(1, need);
     }
     BatchTables tabs;
     fill_batch_tables(tabs, cfg, jump, spread_all, nib_all, group_all, sweep, clock_khz);

@@ -593,7 +593,8 @@ __global__ __launch_bounds__(256) void batch_group_kernel(const BatchDesc *__res
 // wavefronts per compute unit share the table: one block.
 //
 // Tiles of a group that requests share are found by search and jump, as the
-// other orders do.
+// other orders do. (Served batches, the ones with resident states, never take
+// this order.)
 //
 // Measured, 4,096 streams of 2^10 ... 2^24 values, 56 GB: 6.92 TB/s at a
 // schedule of 7,000 GB/s (6.19 in the grouped order; 5.4 at 7,250, past what
@@ -627,14 +628,13 @@ __device__ __forceinline__ uint32_t find_vbase(g_req *__restrict__ reqs, uint32_
 // State at value number offset + d of request r's stream (d < 0 for positions
 // before the request), modulo the order 2^64 - 1 of the step.
 __device__ __forceinline__ uint64_t request_state(const ItemReq &r, int64_t d,
-                                                  g_cu64 *__restrict__ states,
                                                   const uint64_t *__restrict__ jump, uint32_t lane)
 {
     SeedMix mix;
     mix.mix_low = r.mix_low;
     mix.mix_high = r.mix_high;
     mix.zero_fix = r.zero_fix;
-    const uint64_t x0 = uniform64(states ? states[r.gid] : init_state(mix, r.gid));
+    const uint64_t x0 = uniform64(init_state(mix, r.gid));
     const uint64_t k = r.offset + (uint64_t)d - (d < 0 && r.offset < (uint64_t)-d ? 1u : 0u);
     return wave_jump(jump, lane, x0, k);
 }
@@ -655,7 +655,6 @@ __global__ __launch_bounds__(256) void batch_anchor_kernel(const BatchDesc *__re
         return;
     const uint32_t m = desc->m;
     g_req *__restrict__ reqs = (g_req *)desc->reqs;
-    g_cu64 *__restrict__ states = (g_cu64 *)desc->states;
     const uint64_t P = (g0 + lane) * kAnchorValues;
     const uint32_t j0 = find_vbase(reqs, m, g0 * kAnchorValues, lane);
     const uint32_t j1 = find_vbase(reqs, m, (g0 + per_wave - 1) * kAnchorValues, lane);
@@ -678,7 +677,7 @@ __global__ __launch_bounds__(256) void batch_anchor_kernel(const BatchDesc *__re
         const bool mine = inside && j == jj;
         const ItemReq r = load_req(reqs, jj);
         const uint64_t d0 = (g0 + l0) * kAnchorValues - r.vbase;
-        const uint64_t z = request_state(r, (int64_t)d0, states, jump, lane);
+        const uint64_t z = request_state(r, (int64_t)d0, jump, lane);
         if (mine) {
             const uint64_t *__restrict__ col = spread + (lane - l0);
             uint64_t x = 0;
@@ -719,7 +718,6 @@ __global__ __launch_bounds__(1024) void batch_sweep_kernel(const BatchDesc *__re
 
     const uint32_t m = desc->m;
     g_req *__restrict__ reqs = (g_req *)desc->reqs;
-    g_cu64 *__restrict__ states = (g_cu64 *)desc->states;
     g_anchor *__restrict__ anchors = (g_anchor *)anchor_;
 
     // The tile's values, 8 per lane from the state z at its start, as the 16
@@ -789,7 +787,7 @@ __global__ __launch_bounds__(1024) void batch_sweep_kernel(const BatchDesc *__re
                 break;
             if (E <= T0)
                 continue;
-            values(request_state(r, (int64_t)(T0 - B), states, jump, lane), v);
+            values(request_state(r, (int64_t)(T0 - B), jump, lane), v);
             g_u64 *__restrict__ o =
                 (g_u64 *)(reinterpret_cast<uintptr_t>(r.dst) + (T0 - B) * sizeof(uint64_t));
 #pragma unroll

@@ -316,10 +316,9 @@ int batch_stage_items(BatchSlot &slot, const StageReq *items, uint32_t k,
 // configuration's values leave the order to the library; any other runs as
 // given. anchors: whether the caller has room for the sweep order's anchors.
 rngx_batch_cfg batch_order(const rngx_batch_cfg &c, uint64_t values, bool anchors);
-// star: emit the scrambled words. fit_grid: shrink the persistent grid to the
-// staged work (direct launches).
+// star: emit the scrambled words.
 int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg, bool star, hipStream_t stream,
-                 bool fit_grid = false, const char *prof_name = "BATCH_KERNEL");
+                 const char *prof_name = "BATCH_KERNEL");
 // The output scrambler set by rngx_set_scrambler (api.cpp; lock-free read).
 int current_scrambler();
 void release_slot(BatchSlot &slot);

@@ -215,7 +215,7 @@ int launch_admitted(Server &s, Flight &f, std::vector<StageReq> &items, const Se
     int rc = batch_stage_items(f.slot, items.data(), (uint32_t)items.size(), cfg.values_per_lane,
                                s.d_states);
     if (rc == RNGX_OK)
-        rc = batch_launch(f.slot, cfg, s.star, f.stream, true, "SERVE_KERNEL");
+        rc = batch_launch(f.slot, cfg, s.star, f.stream, "SERVE_KERNEL");
     const uint64_t t = now_ns();
     for (uint64_t tk : f.tickets)
         s.reqs.find(tk)->t_launch = t;
