@@ -35,6 +35,7 @@
 #include <cstring>
 #include <vector>
 
+#include "device.h"
 #include "internal.h"
 
 namespace rngx {
@@ -154,18 +155,6 @@ __device__ __forceinline__ uint64_t next_item(unsigned long long *counter, uint3
     return ((uint64_t)hi << 32) | lo;
 }
 
-// y = M x for a lane's own x, M given as 16 tables of 16 entries (entry v of
-// table q is M (v << 4q)) held in LDS: the XOR of one lookup per nibble of x.
-// Each table spans 128 bytes, so the lanes' lookups never share a bank.
-__device__ __forceinline__ uint64_t lane_carry(const uint64_t *__restrict__ tab, uint64_t x)
-{
-    uint64_t y = 0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q)
-        y ^= tab[16 * q + (uint32_t)((x >> (4 * q)) & 15u)];
-    return y;
-}
-
 // The word emitted for state x: the state (the paper's generator) or, for the
 // scrambled variant, the state times 2685821657736338717 modulo 2^64 (the
 // xorshift* multiplier of Vigna, 2016).
@@ -223,7 +212,7 @@ __device__ __forceinline__ bool process_item(const ItemReq &r, uint64_t item, bo
     const uint64_t T0 = (r.first_tile + (item - r.item_begin)) * C;
 
     if (carry) {
-        x = lane_carry(carry_tab, x);
+        x = nibble_product(carry_tab, x);
     } else {
         const uint64_t q0 = T0 > B ? T0 : B;
         // State at q0, then each active lane's first position.
@@ -284,9 +273,7 @@ __device__ __forceinline__ bool process_item(const ItemReq &r, uint64_t item, bo
                 }
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
         // Lane l of store instruction i writes 16 bytes of row RPI*i + l/CPR:
         // CPR lanes cover one row, i.e. one whole 64- or 128-byte segment.
         const uint32_t ch = lane % CPR;
@@ -325,9 +312,7 @@ __device__ __forceinline__ bool process_item(const ItemReq &r, uint64_t item, bo
                     obase[P + 1] = v.y;
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
     }
     return full;
 }
@@ -449,9 +434,7 @@ __device__ __forceinline__ void emit_full_tile(uint64_t &x, uint64_t *lds, g_u64
             lds[lane * LDS_ROW + s] = out_word<STAR>(x);
             x = xs_step(x);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
         const uint32_t ch = lane % CPR;
         u64x2 v[CPR];
 #pragma unroll
@@ -468,20 +451,8 @@ __device__ __forceinline__ void emit_full_tile(uint64_t &x, uint64_t *lds, g_u64
             else
                 *(g_u64x2 *)(tile + off) = v[i];
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
     }
-}
-
-// Wait (bounded) until the device's constant-rate clock reaches `due`: at
-// most about 2^16 polls of about 100 ns, so a wait ends whatever the clock
-// does. Uniform across the wavefront (a scalar clock read).
-__device__ __forceinline__ void wait_clock(uint64_t due)
-{
-    uint32_t polls = 0;
-    while (__builtin_amdgcn_s_memrealtime() < due && ++polls < (1u << 16))
-        __builtin_amdgcn_s_sleep(2);
 }
 
 // The grouped order (rngx_batch_cfg.group). The grid's wavefronts form
@@ -539,13 +510,13 @@ __global__ __launch_bounds__(256) void batch_group_kernel(const BatchDesc *__res
             if (item >= n_items)
                 break; // the rest of the region lies further on
             if (delta256) {
-                wait_clock(t0 + (sched >> 8));
+                wait_until(t0 + (sched >> 8));
                 sched += delta256;
             }
             if (carry && cur_T0 + (uint64_t)group * C + C <= cur_E) {
                 // A full tile `group` tiles on in the same request.
                 cur_T0 = uniform64(cur_T0 + (uint64_t)group * C);
-                x = lane_carry(stride_tab, x);
+                x = nibble_product(stride_tab, x);
                 emit_full_tile<S, R, STAR, true>(
                     x, lds, reinterpret_cast<g_u64 *>(cur_obase) + cur_T0, lane);
                 carry = __builtin_amdgcn_readfirstlane(
@@ -736,17 +707,13 @@ __global__ __launch_bounds__(1024) void batch_sweep_kernel(const BatchDesc *__re
             x = xs_step(x);
             stage[4 * lane + (c ^ ((lane >> 1) & 3u))] = w;
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
 #pragma unroll
         for (uint32_t i = 0; i < 4; ++i) {
             const uint32_t row = 16 * i + (lane >> 2); // the lane that made these two values
             v[i] = stage[4 * row + ((lane & 3u) ^ ((row >> 1) & 3u))];
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
     };
 
     if (place >= n_tiles)
@@ -768,7 +735,7 @@ __global__ __launch_bounds__(1024) void batch_sweep_kernel(const BatchDesc *__re
             dst = reinterpret_cast<uintptr_t>(anchors[(tile + waves) / kAnchorTiles].dst);
         }
         if (delta256) {
-            wait_clock(t0 + (sched >> 8));
+            wait_until(t0 + (sched >> 8));
             sched += delta256;
         }
         if (here) {

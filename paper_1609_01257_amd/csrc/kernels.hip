@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "device.h"
 #include "internal.h"
 
 namespace rngx {
@@ -82,18 +83,6 @@ template <bool NT, typename VT> __device__ __forceinline__ void store16(VT *p, V
         __builtin_nontemporal_store(v, p);
     else
         *p = v;
-}
-
-// Wait (bounded) until the device's constant-rate clock reaches `due`.
-// Uniform across the wavefront: the clock is read by a scalar instruction.
-__device__ __forceinline__ void wait_until(uint64_t due)
-{
-    // At most about 2^16 polls of about 100 ns: a wait ends even if the
-    // schedule were far ahead of the clock.
-    uint32_t polls = 0;
-#pragma nounroll
-    while (__builtin_amdgcn_s_memrealtime() < due && ++polls < (1u << 16))
-        __builtin_amdgcn_s_sleep(2);
 }
 
 // What the Infinity Cache holds.
@@ -222,9 +211,9 @@ __global__ __launch_bounds__(1024) void gen_kernel(uint64_t *__restrict__ state,
 // Bound by the memory's writes: 2^22 x 256 u64 7.0 TB/s at a schedule of 7,000
 // GB/s, where a large fill runs at 6.7. Registers decide whether every block
 // the occupancy query promises is resident: all variants stay within 64 vector
-// registers (8 wavefronts per SIMD) but the staged one of two 4-byte chunks
-// and those of four, and within 80 scalar ones (with 88, of 8 wavefronts per
-// SIMD only 7 were resident and a launch took twice its time).
+// registers (8 wavefronts per SIMD) but those of four 4-byte chunks (80-86),
+// and within 80 scalar ones (with 88, of 8 wavefronts per SIMD only 7 were
+// resident and a launch took twice its time).
 //
 // Staged rows (SHIFT). A row that does not start on a 128-byte line has its
 // wavefronts' spans end inside lines, which then reach the memory in parts
@@ -238,7 +227,7 @@ __global__ __launch_bounds__(1024) void gen_kernel(uint64_t *__restrict__ state,
 // Segments (Polys = JumpPolys). A row of n states occupies n / 128 wavefronts
 // (u64); below some 500 they cannot have enough stores under way. So the
 // iterations are cut into segments, each computed by its own blocks from the
-// states jumped ahead by T^(first row) (build_jump, jump_by); the blocks of
+// states jumped ahead by T^(first row) (build_jump, nibble_product); the blocks of
 // the last segment write the new states. 4,096 x 10,000 u64: 1,650 -> 55 us
 // (0.2 -> 6.0 TB/s), 65,536 x 1,000: 173 -> 80 us.
 //
@@ -281,25 +270,6 @@ __device__ __forceinline__ void build_jump(uint64_t poly, uint64_t *cols, uint64
         tab[t] = y;
     }
     __syncthreads();
-}
-
-// T^k x from such a table: the lanes' lookups for one nibble fall into one
-// 128-byte row of LDS, so they never share a bank.
-__device__ __forceinline__ uint64_t jump_by(const uint64_t *tab, uint64_t x)
-{
-    uint64_t y = 0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q)
-        y ^= tab[16 * q + (uint32_t)((x >> (4 * q)) & 15u)];
-    return y;
-}
-
-// Orders a wavefront's own LDS writes before its reads (and the reverse).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // 16 bytes at any word of LDS.
@@ -389,7 +359,8 @@ __device__ __forceinline__ void paced_rows(uint64_t (&x)[P][Vec16<T>::E], uint64
             if (!WHOLE && lane < lim % E && lim < W)
                 dst[(lim & ~(E - 1u)) + lane] = tail;
         } else {
-            // Whole lines: every row is a whole number of them.
+            // Every row is a whole number of 16-byte chunks: of lines, or of an
+            // output that caches hold, or in place.
             T *const dst = row + wbase;
 #pragma unroll
             for (int p = 0; p < P; ++p) {
@@ -511,9 +482,9 @@ gen_paced_kernel(const PacedArgs a, const Polys polys)
             for (int p = 0; p < P; ++p)
 #pragma unroll
                 for (int e = 0; e < E; ++e)
-                    x[p][e] = jump_by(jump_tab, x[p][e]);
+                    x[p][e] = nibble_product(jump_tab, x[p][e]);
             if (SHIFT)
-                xh = jump_by(jump_tab, xh);
+                xh = nibble_product(jump_tab, xh);
         }
         const bool more = a.items - item > gridDim.x;
         const auto ahead = [&] {
