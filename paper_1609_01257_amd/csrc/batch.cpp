@@ -658,13 +658,12 @@ int batch_launch(BatchSlot &slot, const rngx_batch_cfg &cfg_in, bool star, hipSt
         if (e != hipSuccess)
             return hip_fail(e, "batch kernel launch");
     } else {
-        const size_t bytes = kReqOffset + (size_t)slot.m_staged * sizeof(BatchReq);
         take_stray_error("before the batch kernel launch");
         if (cfg.use_graph == kUploadKernel)
-            RNGX_HIP(launch_batch_upload(slot.mapped, slot.devtab, bytes, stream));
+            RNGX_HIP(launch_batch_upload(slot.mapped, slot.devtab, slot.m_staged, stream));
         else
-            RNGX_HIP(hipMemcpyAsync(slot.devtab, slot.staging, bytes, hipMemcpyHostToDevice,
-                                    stream));
+            RNGX_HIP(hipMemcpyAsync(slot.devtab, slot.staging, 16 * table_chunks(slot.m_staged),
+                                    hipMemcpyHostToDevice, stream));
         hipError_t e = launch_batch(cfg, ddesc, tabs, star, stream);
         if (e != hipSuccess)
             return hip_fail(e, "batch kernel launch");

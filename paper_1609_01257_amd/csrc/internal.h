@@ -196,6 +196,9 @@ static_assert(sizeof(BatchDesc) == 64, "BatchDesc layout");
 constexpr size_t kReqOffset = 128;
 static_assert(kReqOffset >= sizeof(BatchDesc) && kReqOffset % 64 == 0, "request offset");
 
+// 16-byte chunks of a staged table of m requests (2^30 requests have 2^32).
+constexpr uint64_t table_chunks(uint64_t m) { return (kReqOffset + m * sizeof(BatchReq)) / 16; }
+
 // A batch of at most kSmallReqs requests travels in the kernel's arguments
 // (3,136 bytes of the 4 KiB a launch takes) instead of being uploaded: one
 // launch, no copy before it.
@@ -333,8 +336,8 @@ hipError_t launch_batch(const rngx_batch_cfg &cfg, const BatchDesc *desc, const 
                         bool star, hipStream_t s);
 hipError_t launch_batch_small(const rngx_batch_cfg &cfg, const SmallTable &tab,
                               const BatchTables &t, bool star, hipStream_t s);
-// Staged table (device-mapped host address) -> device.
-hipError_t launch_batch_upload(const void *src_mapped, void *dst, size_t bytes, hipStream_t s);
+// Staged table of m requests (device-mapped host address) -> device.
+hipError_t launch_batch_upload(const void *src_mapped, void *dst, uint32_t m, hipStream_t s);
 // Checksum sum_i data[i] * (2 i + 1) mod 2^64 into *acc (device, pre-zeroed).
 hipError_t launch_checksum(const uint64_t *data, uint64_t n, uint64_t *acc, hipStream_t s);
 

@@ -66,3 +66,5 @@ extern "C" uint32_t stage_tail_faults(uint32_t E, uint32_t L, uint32_t W)
             }
     return faults;
 }
+
+extern "C" uint64_t table_chunks_query(uint64_t m) { return rngx::table_chunks(m); }

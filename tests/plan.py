@@ -83,3 +83,9 @@ def stage_tail_faults(chunk, line, columns):
     """Reads of a staged row's last words that miss their word or leave the stage."""
     return lib().stage_tail_faults(ctypes.c_uint32(chunk), ctypes.c_uint32(line),
                                    ctypes.c_uint32(columns))
+
+
+def table_chunks(m):
+    """16-byte pieces in which the table of a batch of m requests is uploaded."""
+    lib().table_chunks_query.restype = ctypes.c_uint64
+    return lib().table_chunks_query(ctypes.c_uint64(m))

@@ -109,3 +109,9 @@ def test_rates_of_segments(u32, n, iters, most):
         p = plan.query(n, iters, u32=u32, launch=(512, 2, 1, pace))
         assert p["scheduled"]
         assert p["pace_gbs"] == (min(pace, most) if most < 7500 else pace)
+
+
+@pytest.mark.parametrize("m", [1, 49, 4096, 2**28, 2**30 - 3, 2**30 - 2, 2**30, 2**32 - 1])
+def test_batch_tables_are_uploaded_whole(m):
+    # 128 bytes before the records, 64 bytes each.
+    assert plan.table_chunks(m) * 16 == 128 + 64 * m
