@@ -161,12 +161,18 @@ __device__ __forceinline__ void partial_wave(uint64_t *__restrict__ state, uint3
         for (int p = 0; p < P; ++p) {
             const uint64_t g = wbase + (uint64_t)p * 64 * E + (uint64_t)lane * E;
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
+            for (int e = 0; e < E; ++e)
                 if ((uint32_t)e < cnt[p])
                     row[g + e] = emit<T, STAR>(x[p][e]);
-                x[p][e] = xs_step(x[p][e]);
-            }
         }
+        // Apart from the guarded stores, so that lanes with and without a
+        // word take their steps together (in one loop with the stores the
+        // compiler gave each side its own: 1 x 200 u32 of 4 chunks 102 us, 79).
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                x[p][e] = xs_step(x[p][e]);
     }
 #pragma unroll
     for (int p = 0; p < P; ++p) {
