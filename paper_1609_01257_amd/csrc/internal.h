@@ -361,7 +361,9 @@ void jump_polys(uint64_t rows, uint32_t count, uint64_t *c);
 // status. (Device faults are sticky and are still reported by the launch.)
 void take_stray_error(const char *where);
 
-// ---- kernel launchers (kernels.hip) ---------------------------------------
+// ---- plain launches (plan.cpp, kernels.hip) --------------------------------
+// What the Infinity Cache holds.
+constexpr uint64_t kCacheBytes = 256ull << 20;
 hipError_t launch_init(uint64_t *state, uint32_t n, const SeedMix &mix, hipStream_t s);
 // How one plain launch covers its rows.
 struct GenPlan {

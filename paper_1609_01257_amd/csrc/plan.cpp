@@ -1,0 +1,118 @@
+// How a plain generate call is covered: which kernel, blocks, segments and rate
+// its sizes, its output's alignment and the configured launch come to. Host
+// code only; the kernels are in kernels.hip.
+#include <algorithm>
+
+#include "internal.h"
+
+namespace rngx {
+
+bool launch_cfg_valid(const rngx_launch &cfg)
+{
+    return cfg.block >= 64 && cfg.block <= 1024 && cfg.block % 64 == 0 &&
+           (cfg.chunks == 1 || cfg.chunks == 2 || cfg.chunks == 4) && cfg.nontemporal <= 1 &&
+           (cfg.pace_gbs == 0 || (cfg.pace_gbs >= 1000 && cfg.pace_gbs <= 20000));
+}
+
+GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32_t iters,
+                 const void *out, bool in_place)
+{
+    const uint64_t row = (uint64_t)n * (u32 ? 4 : 8), bytes = row * iters;
+    const uintptr_t at = reinterpret_cast<uintptr_t>(out) | (iters > 1 ? row : 0);
+    const bool lines = at % 128 == 0;
+    GenPlan p;
+    p.cfg = cfg;
+    p.seg_rows = iters;
+    p.aligned16 = at % 16 == 0;
+    // Narrow rows, below 4 MiB (3 on the lines, where 3.4 MiB x 500 is as fast
+    // as configured, but for the heaviest steps): as configured they would leave
+    // wavefronts or whole compute units without work, so every lane takes one
+    // chunk and blocks are small.
+    // Too few wavefronts to fall in with the memory's rate, and at least 64
+    // iterations (24 off the lines; a segment's jump costs about 2.5 us): the
+    // iterations are cut into segments of at least 8.
+    //
+    // How many: an aligned row of 1 KiB takes a wavefront about 55 ns, and at
+    // least 480 of them hold the rate; about 755 where its words are 4 bytes,
+    // twice the steps, or scrambled, 900 where both; staged, a row takes 220 ns
+    // and more. More segments than that are more places written at once, which the
+    // memory takes more slowly (4,096 x 10,000 u64: 54 us in 16 segments, 60
+    // in 32, 68 in 128, 1,650 in one of 512 x 2; 12,800 x 3,276: 53 in 5, 62 in
+    // 6; 65,536 x 640: 51 in two, 63 in one; scrambled 4,096 x 10,000: 73 in
+    // 16, 53 in 24, 61 in 32; u32 51,200 x 1,638: 66 in 3, 68 in 5). Outputs
+    // that the Infinity Cache takes wait for the rows alone, and run at 1,024
+    // (4,096 x 1,000: 9.6 us, 11.4 in half as many); unaligned, they are better
+    // off word by word where one segment keeps the device busy (262,273 x 99
+    // u64: 34 us, 40 in two staged ones; 65,537 x 399: 65 and 44 in three).
+    const uint64_t waves = (row + 1023) / 1024;
+    // In place there are no segments and no staging; rows that would be staged
+    // then run as configured from 768 wavefronts on (1,800 of 4-byte words): 262,146
+    // x 500 u64 245 us so, 280 narrow; 98,306 x 1,300 232 and 254; 65,538 x 1,000
+    // 178 and 121; u32 524,292 x 500 277 and 282; 400,004 x 660 299 and 285.
+    const bool heaviest = u32 && star, heavy = u32 || star;
+    const uint32_t wide = in_place && !lines && bytes > kCacheBytes ? (u32 ? 1800u : 768u)
+                          : lines && !heaviest                      ? 3072u
+                                                                    : 4096u;
+    const bool narrow = cfg.pace_gbs && iters >= 2 && waves < wide;
+    const bool cached = bytes <= kCacheBytes * 3 / 4;
+    if (narrow && !in_place && iters >= (lines ? 64u : 24u)) {
+        uint64_t segs = 1;
+        if (!lines && !(bytes <= kCacheBytes && waves >= (heavy ? 1800u : 768u)))
+            segs = ((u32 && !cached && waves >= 200 && waves < 1600 ? 6144 : 4096) + waves / 2) /
+                   waves;
+        else if (lines && cached && waves < 512)
+            segs = (1024 + waves / 2) / waves;
+        else if (lines && !cached && waves < 768)
+            segs = std::max<uint64_t>(2, heavy ? ((heaviest ? 900 : 755) + waves / 2) / waves
+                                               : (480 + waves - 1) / waves);
+        segs = std::min<uint64_t>({segs, iters / 8, kMaxSegs});
+        if (segs > 1) {
+            p.seg_rows = (uint32_t)((iters + segs - 1) / segs);
+            p.segs = (uint32_t)(((uint64_t)iters + p.seg_rows - 1) / p.seg_rows);
+        }
+    }
+    // Rows off the 128-byte lines are staged where the memory takes the
+    // values: stored where it lies, such a row writes its lines in parts
+    // (10^6 + 3 states x 256 u64: 6.89 TB/s staged, 4.13 not; 10^6 + 2, 16-byte
+    // aligned: 6.9 and 4.3). Below 256 MiB the Infinity Cache puts the parts
+    // together and staging only costs (2^22 + 1 x 8: 54.7 us staged, 51.6 not).
+    p.shift = !in_place && !lines && iters >= 2 && (bytes > kCacheBytes || p.segs > 1);
+    // A few iterations of long rows end before a schedule orders anything;
+    // they run as fast without one, or faster, up to 32 bytes a stream and up
+    // to 48 where rows are on lines and the output is about the cache's size
+    // (2^26 states x 4 u64 578 us free, 600 scheduled; 2^25 x 8 u32 229 and
+    // 234; 10^7 x 12 u32 96 and 100, but 2,200,000 x 12 u32 26 and 24, and
+    // 3,000,002 x 6 u64, off lines, 36 and 34; 2^24 x 8 u64 201 and 190).
+    const bool mid = lines && bytes > kCacheBytes / 2 && bytes <= 2 * kCacheBytes;
+    const bool few = !p.shift && !narrow && row / n * iters <= (mid ? 48u : 32u);
+    p.scheduled = p.shift || (cfg.pace_gbs && iters >= 2 && p.aligned16 && !few);
+    if (narrow && p.scheduled) {
+        // From 1,536 wavefronts blocks of 512 (262,144 x 1,000 u64: 303 us,
+        // 322 with 256; below, 102,400 x 1,000 u32: 122 with 256, 131).
+        p.cfg.chunks = 1;
+        p.cfg.block =
+            std::min(cfg.block, lines && !cached && !heaviest && waves >= 1536 ? 512u : 256u);
+        // Outputs well inside that cache run ahead of HBM's rate, so a
+        // schedule only holds them back (131,072 x 100 u64: 5.25 TB/s free,
+        // below 5.1 scheduled; 65,536 x 1,000: 5.5 free, 6.5 scheduled).
+        // Many segments: at most a rate that they hold, above which they fall
+        // behind for good (at 6,000, 6,500 and 7,000 GB/s: 16,387 x 10,000
+        // u64, 32 segments, 230, 214, 264 us; 4,099 x 10,000, 124, 66, 73, 79;
+        // 131,073 x 2,000, 4, 354, 327, 308; 65,537 x 1,000 u32, 24, 48, 52,
+        // 54; 131,073 x 2,000 u32, 12, 179, 166, 189; aligned, at 6,500, 6,750
+        // and 7,000: 25,600 x 6,553 u32, 8, 107, 106, 123; 32,768 x 5,120, 6,
+        // 107, 104, 104; scrambled u64 12,800 x 6,553, 8, 107, 104, 116).
+        const uint32_t pace = cfg.pace_gbs;
+        if (cached)
+            p.cfg.pace_gbs = 0;
+        else if (lines && heavy && p.segs > 1)
+            p.cfg.pace_gbs = std::min(pace, 6750u);
+        else if (!lines && p.segs >= (u32 ? 20u : 64u))
+            p.cfg.pace_gbs = std::min(pace, 6000u);
+        else if (!lines && p.segs >= (u32 ? 2u : 6u))
+            p.cfg.pace_gbs = std::min(pace, 6500u);
+    }
+    return p;
+}
+
+} // namespace rngx

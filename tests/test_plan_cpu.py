@@ -115,3 +115,12 @@ def test_rates_of_segments(u32, n, iters, most):
 def test_batch_tables_are_uploaded_whole(m):
     # 128 bytes before the records, 64 bytes each.
     assert plan.table_chunks(m) * 16 == 128 + 64 * m
+
+
+# The headline shape runs as configured: scheduled, in place, one segment of unstaged rows. (The
+# committed counters are of that launch.)
+def test_headline_plan():
+    for launch in [(512, 2, 1, 7000), (512, 2, 1, 7500), (256, 4, 1, 7500), (256, 1, 1, 7000)]:
+        p = plan.query(1 << 26, 256, launch=launch)
+        assert (p["block"], p["chunks"], p["nontemporal"], p["pace_gbs"]) == launch
+        assert p["scheduled"] and not p["shift"] and (p["segs"], p["seg_rows"]) == (1, 256)
