@@ -174,7 +174,8 @@ int rngx_hip_notes(uint64_t *released, uint64_t *stray, char *text, size_t cap, 
  *         device, and without waits if its output stays below 192 MiB.
  * Rows that do not start on 128-byte lines (an odd or ragged n_states, an
  * output offset) are staged through LDS into whole lines when the output is
- * larger than 256 MiB or cut into segments, with at most 2 chunks. Staged
+ * larger than 256 MiB (without a schedule 640 MiB, and rows of 2 MiB or more)
+ * or cut into segments, with at most 2 chunks. Staged
  * rows and segments keep a second buffer of 8 * n_states bytes from the first
  * such call on, as long as the state's own is kept; if it cannot be allocated,
  * or once a generate call of this state was captured into a graph, such calls

@@ -76,7 +76,14 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     // (10^6 + 3 states x 256 u64: 6.89 TB/s staged, 4.13 not; 10^6 + 2, 16-byte
     // aligned: 6.9 and 4.3). Below 256 MiB the Infinity Cache puts the parts
     // together and staging only costs (2^22 + 1 x 8: 54.7 us staged, 51.6 not).
-    p.shift = !in_place && !lines && iters >= 2 && (bytes > kCacheBytes || p.segs > 1);
+    // Without a schedule the staged kernel needs wide rows to fill the device
+    // and outputs well beyond that cache (block 256, 1 chunk, 39,240 x 1,207 u64
+    // 307 us staged, 97 not; 512 and 2, 300,001 x 224 114 and 92, x 374 190 and
+    // 230).
+    const uint64_t stage_from = cfg.pace_gbs ? kCacheBytes
+                                : waves >= 2048 ? kCacheBytes / 2 * 5
+                                                : UINT64_MAX;
+    p.shift = !in_place && !lines && iters >= 2 && (bytes > stage_from || p.segs > 1);
     // A few iterations of long rows end before a schedule orders anything;
     // they run as fast without one, or faster, up to 32 bytes a stream and up
     // to 48 where rows are on lines and the output is about the cache's size

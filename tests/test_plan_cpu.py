@@ -124,3 +124,16 @@ def test_headline_plan():
         p = plan.query(1 << 26, 256, launch=launch)
         assert (p["block"], p["chunks"], p["nontemporal"], p["pace_gbs"]) == launch
         assert p["scheduled"] and not p["shift"] and (p["segs"], p["seg_rows"]) == (1, 256)
+
+
+# Without a schedule, rows run where they lie and as configured, but for wide rows of outputs well
+# beyond the cache, which are staged.
+@pytest.mark.parametrize("launch", [(256, 1, 1, 0), (128, 2, 0, 0), (1024, 4, 0, 0)])
+def test_unscheduled_plans(launch):
+    for u32, n, iters in [(False, 39239, 1207), (False, 75649, 3269), (True, 9215, 16422),
+                          (True, 167153, 837), (False, 448631, 97), (False, 2648055, 13),
+                          (False, 4099, 10000), (False, 4096, 10000)]:
+        p = plan.query(n, iters, u32=u32, launch=launch)
+        assert not p["scheduled"] and not p["shift"] and p["segs"] == 1, (n, iters)
+        assert (p["block"], p["chunks"], p["nontemporal"], p["pace_gbs"]) == launch
+    assert plan.query(1000003, 256, launch=launch)["shift"]
