@@ -171,7 +171,8 @@ int rngx_hip_notes(uint64_t *released, uint64_t *stray, char *text, size_t cap, 
  *         runs with one chunk and blocks of at most 256 or 512, its iterations
  *         cut into segments that run side by side, many of them at no more
  *         than 6000 to 6750 GB/s, where the rows alone would not fill the
- *         device, and without waits if its output stays below 192 MiB.
+ *         device, and without waits if its output stays below 192 MiB (64
+ *         MiB where a row has 1,280 KiB and more).
  * Rows that do not start on 128-byte lines (an odd or ragged n_states, an
  * output offset) are staged through LDS into whole lines when the output is
  * larger than 256 MiB (without a schedule 640 MiB, and rows of 2 MiB or more)

@@ -94,14 +94,19 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     const bool few = !p.shift && !narrow && row / n * iters <= (mid ? 48u : 32u);
     p.scheduled = p.shift || (cfg.pace_gbs && iters >= 2 && p.aligned16 && !few);
     if (narrow && p.scheduled) {
+        // Outputs well inside that cache run ahead of HBM's rate, so a
+        // schedule only holds them back (131,072 x 100 u64: 5.25 TB/s free,
+        // below 5.1 scheduled; 65,536 x 1,000: 5.5 free, 6.5 scheduled): up to
+        // 192 MiB, of wide rows in one segment 64 MiB, as more wavefronts write
+        // than the cache takes in any order (332,800 x 71 u64, 190 MB, 39.3 us
+        // free, 34.3 scheduled; 243,200 x 97 38.9 and 34.5).
+        const bool free =
+            bytes <= (waves < 1280 || p.segs > 1 ? kCacheBytes / 4 * 3 : kCacheBytes / 4);
         // From 1,536 wavefronts blocks of 512 (262,144 x 1,000 u64: 303 us,
         // 322 with 256; below, 102,400 x 1,000 u32: 122 with 256, 131).
         p.cfg.chunks = 1;
         p.cfg.block =
-            std::min(cfg.block, lines && !cached && !heaviest && waves >= 1536 ? 512u : 256u);
-        // Outputs well inside that cache run ahead of HBM's rate, so a
-        // schedule only holds them back (131,072 x 100 u64: 5.25 TB/s free,
-        // below 5.1 scheduled; 65,536 x 1,000: 5.5 free, 6.5 scheduled).
+            std::min(cfg.block, lines && !free && !heaviest && waves >= 1536 ? 512u : 256u);
         // Many segments: at most a rate that they hold, above which they fall
         // behind for good (at 6,000, 6,500 and 7,000 GB/s: 16,387 x 10,000
         // u64, 32 segments, 230, 214, 264 us; 4,099 x 10,000, 124, 66, 73, 79;
@@ -110,7 +115,7 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
         // and 7,000: 25,600 x 6,553 u32, 8, 107, 106, 123; 32,768 x 5,120, 6,
         // 107, 104, 104; scrambled u64 12,800 x 6,553, 8, 107, 104, 116).
         const uint32_t pace = cfg.pace_gbs;
-        if (cached)
+        if (free)
             p.cfg.pace_gbs = 0;
         else if (lines && heavy && p.segs > 1)
             p.cfg.pace_gbs = std::min(pace, 6750u);

@@ -137,3 +137,14 @@ def test_unscheduled_plans(launch):
         assert not p["scheduled"] and not p["shift"] and p["segs"] == 1, (n, iters)
         assert (p["block"], p["chunks"], p["nontemporal"], p["pace_gbs"]) == launch
     assert plan.query(1000003, 256, launch=launch)["shift"]
+
+
+# Rows of 1,280 wavefronts and more in one segment keep to their schedule above 64 MiB; shorter
+# ones, and segments, run free while the cache holds their output.
+@pytest.mark.parametrize("u32,n,iters,free", [
+    (False, 65536, 300, True), (False, 131072, 180, True), (False, 4096, 1000, True),
+    (False, 179200, 40, True), (False, 179200, 60, False), (False, 332800, 71, False),
+    (True, 486400, 97, False), (False, 332800, 20, True), (False, 131072, 250, False)])
+def test_free_running_rows(u32, n, iters, free):
+    p = plan.query(n, iters, u32=u32)
+    assert p["scheduled"] and p["chunks"] == 1 and (p["pace_gbs"] == 0) == free
