@@ -45,14 +45,19 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     // off word by word where one segment keeps the device busy (262,273 x 99
     // u64: 34 us, 40 in two staged ones; 65,537 x 399: 65 and 44 in three).
     const uint64_t waves = (row + 1023) / 1024;
-    // In place there are no segments and no staging; rows that would be staged
-    // then run as configured from 768 wavefronts on (1,800 of 4-byte words): 262,146
-    // x 500 u64 245 us so, 280 narrow; 98,306 x 1,300 232 and 254; 65,538 x 1,000
-    // 178 and 121; u32 524,292 x 500 277 and 282; 400,004 x 660 299 and 285.
+    // Rows off the lines that are stored where they lie (in place, or in outputs
+    // that the cache puts together) run as configured from fewer wavefronts on,
+    // of 8-byte words above all (179,202 x 118 u64 38.3 us so, 46.2 narrow;
+    // 332,802 x 71 40.7 and 51.6; in place, 262,146 x 500 245 and 280, 131,074 x
+    // 1,000 268 and 256; u32 524,292 x 500 277 and 282; 400,004 x 660 299 and
+    // 285). Rows that are not 16-byte aligned take no schedule there, nor, from
+    // here on, segments.
     const bool heaviest = u32 && star, heavy = u32 || star;
-    const uint32_t wide = in_place && !lines && bytes > kCacheBytes ? (u32 ? 1800u : 768u)
-                          : lines && !heaviest                      ? 3072u
-                                                                    : 4096u;
+    const bool bare = !lines && (in_place || bytes <= kCacheBytes);
+    const uint32_t wide = !bare ? (lines && !heaviest ? 3072u : 4096u)
+                          : u32 ? (p.aligned16 && bytes <= kCacheBytes ? 4096u : 1800u)
+                          : star ? (p.aligned16 && bytes <= kCacheBytes ? 2304u : 1200u)
+                                 : (p.aligned16 ? 1200u : 768u);
     const bool narrow = cfg.pace_gbs && iters >= 2 && waves < wide;
     const bool cached = bytes <= kCacheBytes * 3 / 4;
     if (narrow && !in_place && iters >= (lines ? 64u : 24u)) {

@@ -148,3 +148,17 @@ def test_unscheduled_plans(launch):
 def test_free_running_rows(u32, n, iters, free):
     p = plan.query(n, iters, u32=u32)
     assert p["scheduled"] and p["chunks"] == 1 and (p["pace_gbs"] == 0) == free
+
+
+# Rows off the lines that the cache puts together, 16-byte aligned: from some width on as
+# configured, below in one chunk and small blocks.
+@pytest.mark.parametrize("u32,star,n,iters,narrow", [
+    (False, False, 128002, 190, True), (False, False, 179202, 118, False),
+    (False, False, 332802, 71, False), (False, True, 179202, 20, True),
+    (False, True, 332802, 71, False), (True, False, 486404, 97, True),
+    (True, True, 486404, 97, True)])
+def test_rows_off_the_lines_in_the_cache(u32, star, n, iters, narrow):
+    p = plan.query(n, iters, u32=u32, star=star)
+    assert p["scheduled"] and not p["shift"] and p["segs"] == 1
+    assert (p["block"], p["chunks"]) == ((256, 1) if narrow else (512, 2))
+    assert narrow or p["pace_gbs"] == 7000
