@@ -24,6 +24,34 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     p.cfg = cfg;
     p.seg_rows = iters;
     p.aligned16 = at % 16 == 0;
+    const bool heaviest = u32 && star, heavy = u32 || star;
+    const uint64_t waves = (row + 1023) / 1024;
+    // Rows off the 128-byte lines are staged where the memory takes the
+    // values: stored where it lies, such a row writes its lines in parts
+    // (10^6 + 3 states x 256 u64: 6.89 TB/s staged, 4.13 not; 10^6 + 2, 16-byte
+    // aligned: 6.9 and 4.3). Below 256 MiB the Infinity Cache puts the parts
+    // together and staging only costs (2^22 + 1 x 8: 54.7 us staged, 51.6 not).
+    // It still does most of that somewhat above, for rows that are not 16-byte
+    // aligned and so take no schedule unstaged: of 4-byte words from 2,304
+    // wavefronts on up to 352 MiB, very wide rows up to 416 MiB, of 8-byte
+    // words up to 512 MiB in the rows that would be staged in two or three
+    // segments (us, where it lies and staged: 179,201 x 216 u64 56.5
+    // and 64.9, 332,801 x 116 53.0 and 60.2, but 537,601 x 72 61.0 and 52.3;
+    // 7,040,001 x 6 69.0 and 72.0; u32 4,096,001 x 18 56.5 and 64.8; 2,304,001 x
+    // 33 57.4 and 63.8, x 46 104.7 and 80.4).
+    uint64_t stage_from = kCacheBytes;
+    if (!p.aligned16) {
+        if (u32)
+            stage_from = kCacheBytes / 8 * (waves < 2304 ? 8 : waves < 64000 ? 11 : 13);
+        else if (waves >= (star ? 1200 : 900))
+            stage_from = kCacheBytes / 8 * (waves < 3072 ? 16 : waves < 24000 ? 8 : 13);
+    }
+    // Without a schedule the staged kernel needs wide rows to fill the device
+    // and outputs well beyond that cache (block 256, 1 chunk, 39,240 x 1,207 u64
+    // 307 us staged, 97 not; 512 and 2, 300,001 x 224 114 and 92, x 374 190 and
+    // 230).
+    if (!cfg.pace_gbs)
+        stage_from = waves >= 2048 ? kCacheBytes / 2 * 5 : UINT64_MAX;
     // Narrow rows, below 4 MiB (3 on the lines, where 3.4 MiB x 500 is as fast
     // as configured, but for the heaviest steps): as configured they would leave
     // wavefronts or whole compute units without work, so every lane takes one
@@ -44,7 +72,6 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     // (4,096 x 1,000: 9.6 us, 11.4 in half as many); unaligned, they are better
     // off word by word where one segment keeps the device busy (262,273 x 99
     // u64: 34 us, 40 in two staged ones; 65,537 x 399: 65 and 44 in three).
-    const uint64_t waves = (row + 1023) / 1024;
     // Rows off the lines that are stored where they lie (in place, or in outputs
     // that the cache puts together) run as configured from fewer wavefronts on,
     // of 8-byte words above all (179,202 x 118 u64 38.3 us so, 46.2 narrow;
@@ -52,8 +79,7 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     // 1,000 268 and 256; u32 524,292 x 500 277 and 282; 400,004 x 660 299 and
     // 285). Rows that are not 16-byte aligned take no schedule there, nor, from
     // here on, segments.
-    const bool heaviest = u32 && star, heavy = u32 || star;
-    const bool bare = !lines && (in_place || bytes <= kCacheBytes);
+    const bool bare = !lines && (in_place || bytes <= stage_from);
     const uint32_t wide = !bare ? (lines && !heaviest ? 3072u : 4096u)
                           : u32 ? (p.aligned16 && bytes <= kCacheBytes ? 4096u : 1800u)
                           : star ? (p.aligned16 && bytes <= kCacheBytes ? 2304u : 1200u)
@@ -62,7 +88,7 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     const bool cached = bytes <= kCacheBytes * 3 / 4;
     if (narrow && !in_place && iters >= (lines ? 64u : 24u)) {
         uint64_t segs = 1;
-        if (!lines && !(bytes <= kCacheBytes && waves >= (heavy ? 1800u : 768u)))
+        if (!lines && !(bytes <= stage_from && waves >= (heavy ? 1800u : 768u)))
             segs = ((u32 && !cached && waves >= 200 && waves < 1600 ? 6144 : 4096) + waves / 2) /
                    waves;
         else if (lines && cached && waves < 512)
@@ -76,18 +102,6 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
             p.segs = (uint32_t)(((uint64_t)iters + p.seg_rows - 1) / p.seg_rows);
         }
     }
-    // Rows off the 128-byte lines are staged where the memory takes the
-    // values: stored where it lies, such a row writes its lines in parts
-    // (10^6 + 3 states x 256 u64: 6.89 TB/s staged, 4.13 not; 10^6 + 2, 16-byte
-    // aligned: 6.9 and 4.3). Below 256 MiB the Infinity Cache puts the parts
-    // together and staging only costs (2^22 + 1 x 8: 54.7 us staged, 51.6 not).
-    // Without a schedule the staged kernel needs wide rows to fill the device
-    // and outputs well beyond that cache (block 256, 1 chunk, 39,240 x 1,207 u64
-    // 307 us staged, 97 not; 512 and 2, 300,001 x 224 114 and 92, x 374 190 and
-    // 230).
-    const uint64_t stage_from = cfg.pace_gbs ? kCacheBytes
-                                : waves >= 2048 ? kCacheBytes / 2 * 5
-                                                : UINT64_MAX;
     p.shift = !in_place && !lines && iters >= 2 && (bytes > stage_from || p.segs > 1);
     // A few iterations of long rows end before a schedule orders anything;
     // they run as fast without one, or faster, up to 32 bytes a stream and up

@@ -777,8 +777,8 @@ LAUNCHES = [(64, 1, 1, 7000), (1024, 4, 0, 3000), (256, 2, 0, 0), (1024, 1, 1, 0
                                          (True, 16384, 300)])
 def test_staged_rows_and_segments_under_every_launch(oracle, launch, u32, n, iters):
     from tests import plan
-    if n > 1 << 20 and launch[3] == 0:
-        iters = 21  # staged only well beyond the cache
+    if n > 1 << 20:  # staged only beyond the cache, without a schedule well beyond
+        iters = 21 if launch[3] == 0 else 12 if u32 else 14
     p = plan.query(n, iters, u32=u32, launch=launch)
     assert p["shift"] if n > 1 << 20 else (p["segs"] > 1) == (launch[3] > 0)
     default = rngx.get_launch(u32)
@@ -791,3 +791,25 @@ def test_staged_rows_and_segments_under_every_launch(oracle, launch, u32, n, ite
     assert np.array_equal(got, want(14, n, iters, cursor=1))
     st, _, c = rngx.get_state()
     assert c == iters + 1 and np.array_equal(st, oracle.generate(14, n, 1, cursor=c).ravel())
+
+
+# Staged rows of wide outputs (which the plan confirms): the last wavefront has a whole line's
+# states right of it, some, or none; 16-byte aligned rows and others.
+@pytest.mark.parametrize("scrambled", [False, True])
+@pytest.mark.parametrize("u32,n,iters,offset", [
+    (False, (1 << 22) + 1, 14, 0), (False, (1 << 22) - 14, 9, 2), (False, (1 << 22) + 240, 14, 5),
+    (False, 537601, 72, 0), (True, (1 << 23) + 33, 12, 0), (True, (1 << 23) - 31, 12, 7),
+    (True, (1 << 23) + 4, 9, 0)])
+def test_staged_rows_of_wide_outputs(oracle, scrambled, u32, n, iters, offset):
+    from tests import plan
+    p = plan.query(n, iters, u32=u32, star=scrambled, out=offset * (4 if u32 else 8))
+    assert p["shift"] and p["segs"] == 1 and p["chunks"] == 2
+    want = getattr(oracle, "generate" + ("_star" if scrambled else "") + ("_u32" if u32 else ""))
+    rngx.set_scrambler(rngx.SCRAMBLE_STAR if scrambled else rngx.SCRAMBLE_NONE)
+    try:
+        got = run(6, n, iters, u32=u32, offset=offset, pre=1)
+    finally:
+        rngx.set_scrambler(rngx.SCRAMBLE_NONE)
+    assert np.array_equal(got, want(6, n, iters, cursor=1))
+    st, _, c = rngx.get_state()
+    assert c == iters + 1 and np.array_equal(st, oracle.generate(6, n, 1, cursor=c).ravel())

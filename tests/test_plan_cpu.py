@@ -162,3 +162,20 @@ def test_rows_off_the_lines_in_the_cache(u32, star, n, iters, narrow):
     assert p["scheduled"] and not p["shift"] and p["segs"] == 1
     assert (p["block"], p["chunks"]) == ((256, 1) if narrow else (512, 2))
     assert narrow or p["pace_gbs"] == 7000
+
+
+# Rows that are not 16-byte aligned stay where they lie somewhat beyond the cache's size, as far as
+# that is faster; aligned ones do not.
+@pytest.mark.parametrize("u32,star,n,iters,staged", [
+    (False, False, 179201, 216, False), (False, True, 332801, 116, False),
+    (False, False, 179201, 418, True), (False, False, 537601, 72, True),
+    (False, False, 7040001, 6, False), (False, False, 7040001, 9, True),
+    (False, False, 102401, 400, True), (True, False, 2304001, 33, False),
+    (True, True, 2304001, 46, True), (True, False, 19200001, 5, False),
+    (True, False, 300001, 250, True), (False, False, 332802, 116, True),
+    (True, False, 2304004, 33, True)])
+def test_where_staging_begins(u32, star, n, iters, staged):
+    p = plan.query(n, iters, u32=u32, star=star)
+    assert bool(p["shift"]) == staged
+    if not staged:
+        assert p["segs"] == 1 and not p["scheduled"] and (p["block"], p["chunks"]) == (512, 2)
