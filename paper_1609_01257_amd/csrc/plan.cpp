@@ -57,8 +57,10 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     // wavefronts or whole compute units without work, so every lane takes one
     // chunk and blocks are small.
     // Too few wavefronts to fall in with the memory's rate, and at least 64
-    // iterations (24 off the lines; a segment's jump costs about 2.5 us): the
-    // iterations are cut into segments of at least 8.
+    // iterations (off the lines 48, scrambled 32, of 4-byte words 28, where both
+    // 24; a segment's jump costs about 2.5 us): the iterations are cut into
+    // segments of at least 8. (Off the lines, us a call: 1,001 x 28 u64 9.9 in
+    // one, 11.6 in three; x 64 13.5 and 11.4; 1,001 x 24 u32 10.9 and 11.8.)
     //
     // How many: an aligned row of 1 KiB takes a wavefront about 55 ns, and at
     // least 480 of them hold the rate; about 755 where its words are 4 bytes,
@@ -86,7 +88,8 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
                                  : (p.aligned16 ? 1200u : 768u);
     const bool narrow = cfg.pace_gbs && iters >= 2 && waves < wide;
     const bool cached = bytes <= kCacheBytes * 3 / 4;
-    if (narrow && !in_place && iters >= (lines ? 64u : 24u)) {
+    const uint32_t least = lines ? 64u : heaviest ? 24u : u32 ? 28u : star ? 32u : 48u;
+    if (narrow && !in_place && iters >= least) {
         uint64_t segs = 1;
         if (!lines && !(bytes <= stage_from && waves >= (heavy ? 1800u : 768u)))
             segs = ((u32 && !cached && waves >= 200 && waves < 1600 ? 6144 : 4096) + waves / 2) /

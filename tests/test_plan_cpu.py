@@ -179,3 +179,14 @@ def test_where_staging_begins(u32, star, n, iters, staged):
     assert bool(p["shift"]) == staged
     if not staged:
         assert p["segs"] == 1 and not p["scheduled"] and (p["block"], p["chunks"]) == (512, 2)
+
+
+# Short rows: segments from 64 iterations on, off the lines from where their jumps pay.
+@pytest.mark.parametrize("u32,star,n,least", [
+    (False, False, 4096, 64), (True, True, 4096, 64), (False, False, 1001, 48),
+    (False, True, 1001, 32), (True, False, 1001, 28), (True, True, 1001, 24),
+    (False, False, 4098, 48)])
+def test_where_segments_begin(u32, star, n, least):
+    assert plan.query(n, least - 1, u32=u32, star=star)["segs"] == 1
+    p = plan.query(n, least, u32=u32, star=star)
+    assert p["segs"] > 1 and p["seg_rows"] >= 8
