@@ -173,11 +173,11 @@ int rngx_hip_notes(uint64_t *released, uint64_t *stray, char *text, size_t cap, 
  *         than 6000 to 6750 GB/s, where the rows alone would not fill the
  *         device, and without waits if its output stays below 192 MiB (64
  *         MiB where a row has 1,280 KiB and more).
- * Rows that do not start on 128-byte lines (an odd or ragged n_states, an
- * output offset) are staged through LDS into whole lines when the output is
- * larger than 256 MiB (rows that are not 16-byte aligned up to 512 MiB; without
- * a schedule 640 MiB, and rows of 2 MiB or more) or cut into segments, with at
- * most 2 chunks. Staged
+ * Rows that do not start on 128-byte lines or their middle (an odd or ragged
+ * n_states, an output offset) are staged through LDS into whole lines when the
+ * output is larger than 256 MiB (rows that are not 16-byte aligned up to 512
+ * MiB; without a schedule 640 MiB, and rows of 2 MiB or more) or cut into
+ * segments, with at most 2 chunks. Staged
  * rows and segments keep a second buffer of 8 * n_states bytes from the first
  * such call on, as long as the state's own is kept; if it cannot be allocated,
  * or once a generate call of this state was captured into a graph, such calls

@@ -813,3 +813,22 @@ def test_staged_rows_of_wide_outputs(oracle, scrambled, u32, n, iters, offset):
     assert np.array_equal(got, want(6, n, iters, cursor=1))
     st, _, c = rngx.get_state()
     assert c == iters + 1 and np.array_equal(st, oracle.generate(6, n, 1, cursor=c).ravel())
+
+
+# Rows on 64-byte halves of lines, in segments, in one and in wide ones.
+@pytest.mark.parametrize("scrambled", [False, True])
+@pytest.mark.parametrize("u32,n,iters", [(False, 4104, 300), (False, 8, 700), (False, 65544, 1000),
+                                         (False, 179208, 200), (False, (1 << 22) + 8, 9),
+                                         (True, 4112, 300), (True, 262160, 400),
+                                         (True, (1 << 23) + 16, 13)])
+def test_rows_on_half_lines(oracle, scrambled, u32, n, iters):
+    from tests import plan
+    assert not plan.query(n, iters, u32=u32, star=scrambled)["shift"]
+    want = getattr(oracle, "generate" + ("_star" if scrambled else "") + ("_u32" if u32 else ""))
+    rngx.set_scrambler(rngx.SCRAMBLE_STAR if scrambled else rngx.SCRAMBLE_NONE)
+    try:
+        for offset in (0, 16 if u32 else 8):
+            got = run(9, n, iters, u32=u32, offset=offset, pre=1)
+            assert np.array_equal(got, want(9, n, iters, cursor=1)), offset
+    finally:
+        rngx.set_scrambler(rngx.SCRAMBLE_NONE)

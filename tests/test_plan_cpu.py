@@ -190,3 +190,15 @@ def test_where_segments_begin(u32, star, n, least):
     assert plan.query(n, least - 1, u32=u32, star=star)["segs"] == 1
     p = plan.query(n, least, u32=u32, star=star)
     assert p["segs"] > 1 and p["seg_rows"] >= 8
+
+
+# Rows on 64-byte halves of lines run as rows on the lines do.
+@pytest.mark.parametrize("u32,star,n,iters", [
+    (False, False, 4096, 1000), (False, False, 131072, 500), (False, True, 179200, 250),
+    (True, True, 1075200, 200), (False, False, 1 << 20, 256), (True, False, 19200000, 10)])
+def test_half_lines(u32, star, n, iters):
+    p = plan.query(n + (16 if u32 else 8), iters, u32=u32, star=star)
+    q = plan.query(n, iters, u32=u32, star=star, out=64)
+    assert q == plan.query(n, iters, u32=u32, star=star)
+    assert p["scheduled"] and not p["shift"]
+    assert all(p[k] == q[k] for k in ("block", "chunks", "pace_gbs"))
