@@ -49,6 +49,19 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
         else if (waves >= (star ? 1200 : 900))
             stage_from = kCacheBytes / 8 * (waves < 3072 ? 16 : waves < 24000 ? 8 : 13);
     }
+    // Staged calls keep two copies of the states. Where one fits in that cache
+    // and two do not, a few iterations are better off in place, to up to 12 of
+    // 16-byte aligned rows and 4 of others of 8-byte words, beyond that 2 of the
+    // latter (us, in place and staged: 32,000,002 x 3 u64 193 and 259, x 6 332
+    // and 403, x 13 742 and 748; 28,160,004 x 6 u32 174 and 217; 25,600,001 x 3
+    // u64 193 and 211, x 5 298 and 293).
+    const uint64_t states = 8ull * n;
+    uint64_t few_rows = 0;
+    if (states > kCacheBytes)
+        few_rows = p.aligned16 || u32 ? 0 : 2;
+    else if (states > kCacheBytes / 2)
+        few_rows = p.aligned16 ? 12 : u32 ? 0 : 4;
+    stage_from = std::max(stage_from, few_rows * row);
     // Without a schedule the staged kernel needs wide rows to fill the device
     // and outputs well beyond that cache (block 256, 1 chunk, 39,240 x 1,207 u64
     // 307 us staged, 97 not; 512 and 2, 300,001 x 224 114 and 92, x 374 190 and

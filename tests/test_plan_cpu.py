@@ -202,3 +202,14 @@ def test_half_lines(u32, star, n, iters):
     assert q == plan.query(n, iters, u32=u32, star=star)
     assert p["scheduled"] and not p["shift"]
     assert all(p[k] == q[k] for k in ("block", "chunks", "pace_gbs"))
+
+
+# Few iterations of so many states that the cache holds one copy of them and not two stay in place.
+@pytest.mark.parametrize("u32,n,most", [
+    (False, 32000002, 12), (False, 25600001, 4), (True, 28160004, 12), (False, 40000001, 2),
+    (False, 40000002, 1), (True, 51200004, 1)])
+def test_few_iterations_of_many_states(u32, n, most):
+    for iters in (most, most + 1):
+        p = plan.query(n, iters, u32=u32)
+        assert bool(p["shift"]) == (iters > most), iters
+        assert p["shift"] or p["segs"] == 1
