@@ -90,18 +90,18 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
     // (4,096 x 1,000: 9.6 us, 11.4 in half as many); unaligned, they are better
     // off word by word where one segment keeps the device busy (262,273 x 99
     // u64: 34 us, 40 in two staged ones; 65,537 x 399: 65 and 44 in three).
-    // Rows off the lines that are stored where they lie (in place, or in outputs
-    // that the cache puts together) run as configured from fewer wavefronts on,
-    // of 8-byte words above all (179,202 x 118 u64 38.3 us so, 46.2 narrow;
-    // 332,802 x 71 40.7 and 51.6; in place, 262,146 x 500 245 and 280, 131,074 x
-    // 1,000 268 and 256; u32 524,292 x 500 277 and 282; 400,004 x 660 299 and
-    // 285). Rows that are not 16-byte aligned take no schedule there, nor, from
-    // here on, segments.
+    // Rows off the lines that are stored where they lie run narrow in outputs
+    // that the cache holds. Beyond (in place) and where they take no schedule
+    // (not 16-byte aligned) they run as configured from 768 to 1,800 wavefronts
+    // on: in place, 262,146 x 500 u64 231 us so, 296 narrow; 163,842 x 800 255
+    // and 295; 65,538 x 1,000 178 and 121; u32 524,292 x 500 272 and 300;
+    // 400,004 x 660 299 and 285.
     const bool bare = !lines && (in_place || bytes <= stage_from);
     const uint32_t wide = !bare ? (lines && !heaviest ? 3072u : 4096u)
-                          : u32 ? (p.aligned16 && bytes <= kCacheBytes ? 4096u : 1800u)
-                          : star ? (p.aligned16 && bytes <= kCacheBytes ? 2304u : 1200u)
-                                 : (p.aligned16 ? 1200u : 768u);
+                          : p.aligned16 && bytes <= kCacheBytes ? 4096u
+                          : u32                                 ? 1800u
+                          : star || p.aligned16                 ? 1200u
+                                                                : 768u;
     const bool narrow = cfg.pace_gbs && iters >= 2 && waves < wide;
     const bool cached = bytes <= kCacheBytes * 3 / 4;
     const uint32_t least = lines ? 64u : heaviest ? 24u : u32 ? 28u : star ? 32u : 48u;
@@ -162,6 +162,11 @@ GenPlan plan_gen(const rngx_launch &cfg, bool u32, bool star, uint32_t n, uint32
         else if (!lines && p.segs >= (u32 ? 2u : 6u))
             p.cfg.pace_gbs = std::min(pace, 6500u);
     }
+    // Neighbouring wavefronts of one chunk share a line of each row off the
+    // lines. Normal stores let the caches put it together (300,000 x 100 u64,
+    // 16-byte aligned, 41.9 us, 60 non-temporal; with two chunks 54, narrow 42).
+    if (p.scheduled && !p.shift && !lines && bytes <= kCacheBytes && p.cfg.chunks == 1)
+        p.cfg.nontemporal = 0;
     return p;
 }
 

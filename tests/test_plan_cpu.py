@@ -150,18 +150,22 @@ def test_free_running_rows(u32, n, iters, free):
     assert p["scheduled"] and p["chunks"] == 1 and (p["pace_gbs"] == 0) == free
 
 
-# Rows off the lines that the cache puts together, 16-byte aligned: from some width on as
-# configured, below in one chunk and small blocks.
+# Rows off the lines that the cache puts together, 16-byte aligned: narrow rows in one chunk, with
+# normal stores (a launch of one chunk too), others as configured.
 @pytest.mark.parametrize("u32,star,n,iters,narrow", [
-    (False, False, 128002, 190, True), (False, False, 179202, 118, False),
-    (False, False, 332802, 71, False), (False, True, 179202, 20, True),
-    (False, True, 332802, 71, False), (True, False, 486404, 97, True),
-    (True, True, 486404, 97, True)])
+    (False, False, 128002, 190, True), (False, False, 179202, 118, True),
+    (False, False, 332802, 71, True), (False, True, 332802, 71, True),
+    (True, False, 486404, 97, True), (True, True, 800004, 60, True),
+    (False, False, 600002, 40, False), (True, True, 1200004, 40, False)])
 def test_rows_off_the_lines_in_the_cache(u32, star, n, iters, narrow):
     p = plan.query(n, iters, u32=u32, star=star)
     assert p["scheduled"] and not p["shift"] and p["segs"] == 1
-    assert (p["block"], p["chunks"]) == ((256, 1) if narrow else (512, 2))
-    assert narrow or p["pace_gbs"] == 7000
+    assert (p["block"], p["chunks"], p["nontemporal"]) == ((256, 1, 0) if narrow else (512, 2, 1))
+    p = plan.query(n, iters, u32=u32, star=star, launch=(1024, 1, 1, 7500))
+    assert p["scheduled"] and (p["chunks"], p["nontemporal"]) == (1, 0)
+    # On the lines, or staged, the stores are as configured.
+    assert plan.query(n & ~31, iters, u32=u32, star=star)["nontemporal"]
+    assert plan.query(n, 4 * iters, u32=u32, star=star)["nontemporal"]
 
 
 # Rows that are not 16-byte aligned stay where they lie somewhat beyond the cache's size, as far as
