@@ -29,8 +29,8 @@ GIB = 1 << 30
 # pace_gbs); u32 block 0 = chosen by size.
 LIB_DEFAULT_U64 = (512, 2, 1, 7000)
 LIB_DEFAULT_U32 = (0, 0, 0, 0)
-# The request server's launch configuration (the values that leave the order
-# to the library), used by the in-pool batched comparator.
+# The library's own order, used by the in-pool batched comparator of the server
+# (which runs large batches in the grouped order that these values name).
 SERVER_LARGE_BATCH_CFG = dict(values_per_lane=16, waves_per_block=4, blocks=0, use_graph=False,
                               row_values=16, run_items=0, per_item=False, group=32,
                               group_steps=8, pace_gbs=6250)
@@ -336,12 +336,11 @@ def serving(torch, rngx, seconds, plain_gbs):
         res["saturation"]["served_vs_plain"] = round(st["gbs"] / plain_gbs, 4)
         rngx.serve_stop()
         # The same requests, in consecutive batches of the server's mean
-        # batch size, each written by the batched kernel into the pool in the
-        # schedule the server uses for large batches (the grouped order,
-        # SERVER_LARGE_BATCH_CFG). Its rate over the kernels' own durations (HIP events on
-        # their stream) is what the server would reach with no overhead of
-        # its own: the ratio isolates the server from kernel speed and from
-        # where the pool lies in HBM.
+        # batch size, each written by the batch call into the pool in the
+        # library's own order (SERVER_LARGE_BATCH_CFG: the sweep order at these
+        # sizes), one after the other. The ratio to its rate over the kernels'
+        # own durations (HIP events on their stream) does not depend on where
+        # the pool lies in HBM.
         per = max(1, int(round(st["mean_batch_requests"])))
         chunks = []
         for a in range(0, len(L), per):

@@ -154,7 +154,9 @@ int rngx_hip_notes(uint64_t *released, uint64_t *stray, char *text, size_t cap, 
  * chunks: 16-byte stores per lane per iteration (1, 2 or 4); a lane then
  *         owns 2*chunks (u64) or 4*chunks (u32) work-items, and every store
  *         instruction of a wavefront covers 1 KiB of contiguous output.
- * nontemporal: 1 to use non-temporal (streaming) stores.
+ * nontemporal: 1 to use non-temporal (streaming) stores (rows off the lines
+ *         that the schedule writes in one chunk, in outputs of up to 256 MiB,
+ *         always take normal ones).
  * pace_gbs: 0, or a row schedule for the launch, 1000..20000 (GB/s). With a
  *         schedule the kernel runs on a persistent grid of at most the blocks
  *         that fit on the device at once, the blocks walking strips of
@@ -176,9 +178,10 @@ int rngx_hip_notes(uint64_t *released, uint64_t *stray, char *text, size_t cap, 
  * Rows that do not start on 128-byte lines or their middle (an odd or ragged
  * n_states, an output offset) are staged through LDS into whole lines when the
  * output is larger than 256 MiB (rows that are not 16-byte aligned up to 512
- * MiB; without a schedule 640 MiB, and rows of 2 MiB or more) or cut into
- * segments, with at most 2 chunks. Staged
- * rows and segments keep a second buffer of 8 * n_states bytes from the first
+ * MiB; without a schedule 640 MiB, and rows of 2 MiB or more; not for up to 12
+ * iterations of so many states that the device's last cache holds one copy of
+ * them and not two) or cut into segments, with at most 2 chunks. Staged rows
+ * and segments keep a second buffer of 8 * n_states bytes from the first
  * such call on, as long as the state's own is kept; if it cannot be allocated,
  * or once a generate call of this state was captured into a graph, such calls
  * run in one segment, their rows written where they lie (on the schedule if
